@@ -470,7 +470,8 @@ kmc_status kmc_zone_load_occupancy(kmc_zone_ctx *ctx);
 kmc_status kmc_zone_set_bias_protocol(kmc_zone_ctx *ctx, const double *t_s, const double *v_volt,
                                       int32_t n_knots);
 
-/* Advance n_steps steps (SI S2.1, the loop; one kernel launch per step).
+/* Advance n_steps steps (SI S2.1, the loop; one launch per 4096 steps while
+ * the lattice fits the GPU's registers, else one per step).
  *   net_dev:  NULL or device int32 [n_steps]: moves toward column 1 minus
  *             moves toward column `sites` in each step.
  *   zone_dev: NULL or device int32 [n_steps][zones]: ions in each zone after
@@ -480,6 +481,13 @@ kmc_status kmc_zone_run_steps(kmc_zone_ctx *ctx, int64_t n_steps, int32_t *net_d
 /* Copy X to host int32 [rails][ions_per_rail] (count >= rails * ions).
  * Synchronises. */
 kmc_status kmc_zone_read_positions(kmc_zone_ctx *ctx, int32_t *X_host, size_t count);
+
+/* How long the workgroups of a multi-step launch wait for one another to be
+ * resident before they leave the steps to a single workgroup (default 100 ms;
+ * 0: a launch of more than one workgroup leaves at once).  Other work that
+ * holds the GPU can make that happen; the results are the same.  In [0, 10^7]
+ * microseconds.  Takes effect for launches enqueued after it. */
+kmc_status kmc_zone_set_gate_limit(kmc_zone_ctx *ctx, int32_t microseconds);
 
 /* Current step counter of a zone-model context. */
 kmc_status kmc_zone_get_step(kmc_zone_ctx *ctx, int64_t *step);

@@ -115,6 +115,7 @@ def lib():
         L.kmc_zone_run_steps.argtypes = [vp, C.c_int64, vp, vp]
         L.kmc_zone_read_positions.argtypes = [vp, P(C.c_int32), C.c_size_t]
         L.kmc_zone_get_step.argtypes = [vp, P(C.c_int64)]
+        L.kmc_zone_set_gate_limit.argtypes = [vp, C.c_int32]
         L.kmc_zone_destroy.argtypes = [vp]
         L.kmc_zone_destroy.restype = None
         L.kmc_fit_decay.argtypes = [P(C.c_double), P(C.c_double), C.c_int64, C.c_double, P(C.c_double),
@@ -131,7 +132,8 @@ def lib():
                      "kmc_autotune", "kmc_fit_decay", "kmc_score_replay_noalloc", "kmc_record_bytes",
                      "kmc_record_hops", "kmc_zone_workspace_bytes",
                      "kmc_zone_init", "kmc_zone_load_occupancy", "kmc_zone_set_bias_protocol", "kmc_zone_run_steps",
-                     "kmc_zone_read_positions", "kmc_zone_get_step"):
+                     "kmc_zone_read_positions", "kmc_zone_set_gate_limit",
+                     "kmc_zone_get_step"):
             getattr(L, name).restype = C.c_int
         _LIB = L
     return _LIB
@@ -531,6 +533,11 @@ class ZoneSimulator:
         _check(lib().kmc_zone_run_steps(C.c_void_p(self.ctx), n_steps, C.c_void_p(net.data_ptr()),
                                         C.c_void_p(zones.data_ptr())))
         return net, zones
+
+    def set_gate_limit(self, microseconds: int) -> None:
+        """Wait for a multi-step launch's workgroups to be resident together
+        (kmc_zone_set_gate_limit; 0: leave the steps to one workgroup)."""
+        _check(lib().kmc_zone_set_gate_limit(C.c_void_p(self.ctx), microseconds))
 
     def read_positions(self) -> np.ndarray:
         out = np.zeros((self.rails, self.ions), dtype=np.int32)

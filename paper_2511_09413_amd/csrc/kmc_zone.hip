@@ -99,6 +99,18 @@ __device__ __forceinline__ uint32_t word_threshold(double p) {
     return t >= 4294967295.0 ? 0xFFFFFFFFu : (t <= 0.0 ? 0u : (uint32_t)t);
 }
 
+// Directional probabilities of a zone with the excess populations below and
+// above it (Eqs. S1-S4), binary64, the operations in the order of the text.
+__device__ __forceinline__ void zone_probabilities(double below, double above, double V, double p0, double kT, double hot,
+                                                   double v_factor, double *pl_out, double *pr_out) {
+    const double dv = V - v_factor * (below - above);
+    const double dE = dv * hot;
+    const double B = exp(-dE / kT);
+    const double pl = p0 / (1.0 + B);
+    *pl_out = pl;
+    *pr_out = B * pl;
+}
+
 // Table entry of zone z for bias V and populations pop (Eqs. S1-S4 with the
 // space-charge drop), binary64, the operations in the order of the text.
 __device__ inline void zone_entry(int z, int Z, const int64_t *pop, double V, double p0, double kT, double hot,
@@ -109,12 +121,7 @@ __device__ inline void zone_entry(int z, int Z, const int64_t *pop, double V, do
     double below = 0.0, above = 0.0;
     for (int y = 0; y < z; ++y) below += (double)pop[y] - mean;
     for (int y = z + 1; y < Z; ++y) above += (double)pop[y] - mean;
-    const double dv = V - v_factor * (below - above);
-    const double dE = dv * hot;
-    const double B = exp(-dE / kT);
-    const double pl = p0 / (1.0 + B);
-    *pl_out = pl;
-    *pr_out = B * pl;
+    zone_probabilities(below, above, V, p0, kT, hot, v_factor, pl_out, pr_out);
 }
 
 __global__ __launch_bounds__(kZoneBlock) void zone_step(ZoneArgs a) {
@@ -280,6 +287,428 @@ __global__ __launch_bounds__(kZoneBlock) void zone_step(ZoneArgs a) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// zone_run: up to kZoneRunSteps steps in one launch, every ion in registers.
+//
+// One launch per step left the step's time to everything but its work: at
+// 128,000 x 60 ions 33 us (15 MB read and written again, the division-free zone
+// index four times per lane, 250 VALU per rail pair) and at 500 rails 12 us, all
+// of it launch, ticket chain and table latency.  Here a wavefront owns P rail
+// pairs for the launch and keeps each ion's column and zone in registers, so a
+// step touches no memory but the zone sums, and its VALU work is mostly the
+// Philox block (34 instructions: what depends on the lane or on the step alone
+// is computed once) and the compares; trials, gap tests and conflicts are
+// wavefront masks combined by the scalar unit.  Thresholds are looked up by the
+// ion's zone (LDS), the zone by its column (a byte table in LDS), and only ions
+// that change zone touch the populations.
+//
+// Between two steps the workgroups add their population changes and net hops
+// to kZoneAcc accumulator rows (64-bit words: arrivals in the upper 24 bits, the
+// biased sum below) and every workgroup polls those rows until all members of
+// a row have arrived.  Rows alternate by the step's parity: a workgroup adds to
+// a row again only after every workgroup has added the step in between, hence
+// after all have read it.  Every workgroup then evaluates the table itself.
+// Measured, us per step: 500 rails x 200 12.2 -> 2.7 (two round trips between
+// workgroups and the table's serial binary64), 128,000 rails 32.7 -> 13.7 (VALU,
+// about 120 instructions per rail pair).
+//
+// The launch needs all its workgroups resident at once.  It is sized for an
+// idle GPU; when other work holds the CUs, the workgroups first meet at a gate,
+// and if they have not all arrived after a bounded time they leave without
+// having changed anything (one atomic word decides, so all leave or none).
+// zone_rescue, launched behind it, then runs the same steps in one workgroup,
+// which needs no other workgroup to make progress.
+constexpr int kZoneAcc = 8;               // accumulator rows (workgroup index modulo 8: one XCD each)
+constexpr int kZoneAccStride = 72;        // 64-bit words per row (zones, then net)
+constexpr int kZoneRunSteps = 4096;       // steps per launch (the biased sums stay below 2^40)
+constexpr int kZonePairsMixed = 1;        // rail pairs of a wavefront whose work is interleaved
+constexpr int kZoneRunMaxPairs = 16;      // rail pairs per wavefront
+constexpr uint32_t kZoneAbort = 0x80000000u;
+constexpr int64_t kZoneBias = 1 << 20;    // above any workgroup's change in one step
+
+struct ZoneRunArgs {
+    uint16_t *X;                // [rails][ions]
+    int32_t rails, ions, sites, zones;
+    double p0, kT, hot, v_factor, dt;
+    uint32_t key0, key1;
+    const double *knot_t, *knot_v;
+    int32_t n_knots, n_steps;
+    int64_t n_set;
+    int64_t n0;                 // absolute step of the launch's first step
+    int64_t row0;               // its output row
+    double *table;              // [2][Z] of the first step; replaced by the one after the last step
+    int64_t *pop;               // [Z] zone populations, replaced likewise
+    unsigned long long *acc;    // [2][kZoneAcc][kZoneAccStride], zero on entry
+    uint32_t *gate;             // arrivals, and kZoneAbort when the launch left undone; zero on entry
+    int32_t *bad;               // raised when a wait of the loop timed out
+    int32_t *net_out, *zone_out;
+    int64_t *net_total;
+    int32_t gate_ticks;         // 10 ns ticks a workgroup waits at the gate
+};
+
+// The kernel arguments, read again from the argument segment where a step's
+// end needs them (scalar loads): held across the pairs' work they would fill
+// the scalar registers.
+typedef const __attribute__((address_space(4))) ZoneRunArgs *ZoneKArgs;
+__device__ __forceinline__ ZoneKArgs zone_kargs() {
+    ZoneKArgs p = (ZoneKArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// LDS of one workgroup; the zone byte of every column follows it.
+struct ZoneLds {
+    uint32_t thr[2][kZoneMaxZones];    // right, left thresholds of the zones
+    int32_t dpop[2][kZoneMaxZones];    // the workgroup's population changes, by the step's parity
+    int32_t dnet[2];
+    int32_t sum[2][kZoneMaxZones + 1]; // the lattice's changes, by the step's parity
+    int32_t pop[kZoneMaxZones];
+    int64_t before[2][kZoneAcc * (kZoneMaxZones + 1)];  // the accumulators' sums when last read
+    double kt[kMaxKnots], kv[kMaxKnots];
+    int64_t net;
+    int32_t go;
+};
+
+struct ZoneStepConst {  // of one step: Philox values that do not depend on the rail
+    uint32_t s_y0;       // hi(M1 n) ^ k0
+    uint32_t lo2, hi2;   // round 2: M0 x0
+};
+struct ZoneLaneConst {  // of one lane
+    uint32_t r1_lo_k;    // lo(M1 x2) of round 0's output ^ k0 + 2 W0
+    uint32_t r1_hi_k;    // hi(M1 x2) ^ k0 + W0
+    uint32_t y3_k;       // lo(M0 l) ^ k1 + W1
+};
+constexpr uint32_t kZM0 = 0xD2511F53u, kZM1 = 0xCD9E8D57u, kZW0 = 0x9E3779B9u, kZW1 = 0xBB67AE85u;
+
+__device__ __forceinline__ ZoneLaneConst zone_lane_const(uint32_t l, uint32_t k0, uint32_t k1) {
+    const uint64_t m0 = (uint64_t)kZM0 * l;
+    const uint64_t m1 = (uint64_t)kZM1 * ((uint32_t)(m0 >> 32) ^ (2u << 1) ^ k1);
+    return {(uint32_t)m1 ^ (k0 + 2u * kZW0), (uint32_t)(m1 >> 32) ^ (k0 + kZW0), (uint32_t)m0 ^ (k1 + kZW1)};
+}
+__device__ __forceinline__ ZoneStepConst zone_step_const(const ZoneLaneConst &c, uint32_t n, uint32_t k0, uint32_t k1) {
+    const uint64_t m1 = (uint64_t)kZM1 * n;
+    const uint64_t a2 = (uint64_t)kZM0 * (c.r1_hi_k ^ (uint32_t)m1);
+    return {(uint32_t)(m1 >> 32) ^ k0, (uint32_t)a2, (uint32_t)(a2 >> 32) ^ (k1 + 2u * kZW1)};
+}
+// The words of philox4x32_10(l, rail, n, 2 << 1, k0, k1).
+__device__ __forceinline__ uint4 zone_words(const ZoneLaneConst &c, const ZoneStepConst &s, uint32_t rail, uint32_t k0,
+                                            uint32_t k1) {
+    const uint64_t a1 = (uint64_t)kZM0 * (s.s_y0 ^ rail);
+    const uint64_t b2 = (uint64_t)kZM1 * ((uint32_t)(a1 >> 32) ^ c.y3_k);
+    uint32_t x0 = (uint32_t)(b2 >> 32) ^ c.r1_lo_k, x1 = (uint32_t)b2;
+    uint32_t x2 = s.hi2 ^ (uint32_t)a1, x3 = s.lo2;
+    uint32_t kr0 = k0 + 2u * kZW0, kr1 = k1 + 2u * kZW1;
+#pragma unroll
+    for (int round = 3; round < 10; ++round) {
+        kr0 += kZW0;
+        kr1 += kZW1;
+        const uint64_t m0 = (uint64_t)kZM0 * x0;
+        const uint64_t m1 = (uint64_t)kZM1 * x2;
+        const uint32_t y0 = kmc::xor3((uint32_t)(m1 >> 32), x1, kr0);
+        const uint32_t y2 = kmc::xor3((uint32_t)(m0 >> 32), x3, kr1);
+        x1 = (uint32_t)m1;
+        x3 = (uint32_t)m0;
+        x0 = y0;
+        x2 = y2;
+    }
+    return make_uint4(x0, x1, x2, x3);
+}
+
+constexpr uint64_t kFirstLanes = 0x0000000100000001ull, kLastLanes = 0x8000000080000000ull;
+
+// One step of a rail pair: lane l of each half holds ions 2l and 2l + 1 of its
+// rail (columns x0, x1; absent ions at sites + 1; z0, z1: four times the
+// zero-based zone).  v0, v1: the lanes whose ions exist.  Returns the pair's net
+// hops (left moves minus right moves).
+__device__ __forceinline__ int zone_pair(uint32_t &x0, uint32_t &x1, uint32_t &z0, uint32_t &z1, const uint4 &w,
+                                         uint64_t v0, uint64_t v1, uint32_t wall, bool last_lane, const uint32_t *thr,
+                                         int32_t *dpop, const uint8_t *zone_at) {
+    auto at = [](const uint32_t *p, uint32_t z) { return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(p) + z); };
+    // gaps to the right neighbours; the left gap of a lane's first ion is the
+    // previous lane's right gap (or the wall)
+    const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)wall, (int)x0, 0x130, 0xf, 0xf, false);  // lane + 1
+    const uint32_t gn = (last_lane ? wall : next) - x1;
+    const uint32_t gi = x1 - x0;
+    const uint64_t gn_free = __ballot(gn > 1u), gi_free = __ballot(gi > 1u);
+    const uint64_t gn_two = __ballot(gn == 2u) & ~kLastLanes, gi_two = __ballot(gi == 2u);
+    const uint64_t gp_free = ((gn_free << 1) & ~kFirstLanes) | (__ballot(x0 > 1u) & kFirstLanes);
+    const uint64_t right0 = __ballot(w.x <= at(thr, z0)) & gi_free & v0;
+    const uint64_t left0 = __ballot(w.y <= at(thr + kZoneMaxZones, z0)) & gp_free & v0;
+    const uint64_t right1 = __ballot(w.z <= at(thr, z1)) & gn_free & v1;
+    const uint64_t left1 = __ballot(w.w <= at(thr + kZoneMaxZones, z1)) & gi_free & v1;
+    // a move is M_right - M_left; two ions aiming at one column both stay
+    uint64_t r0 = right0 & ~left0, l0 = left0 & ~right0, r1 = right1 & ~left1, l1 = left1 & ~right1;
+    const uint64_t in = r0 & l1 & gi_two, out = r1 & (l0 >> 1) & gn_two;
+    r0 &= ~in;
+    l1 &= ~in;
+    r1 &= ~out;
+    l0 &= ~(out << 1);
+    x0 += __builtin_amdgcn_inverse_ballot_w64(r0) ? 1u : 0u;
+    x0 -= __builtin_amdgcn_inverse_ballot_w64(l0) ? 1u : 0u;
+    x1 += __builtin_amdgcn_inverse_ballot_w64(r1) ? 1u : 0u;
+    x1 -= __builtin_amdgcn_inverse_ballot_w64(l1) ? 1u : 0u;
+    const uint32_t y0 = zone_at[x0], y1 = zone_at[x1];
+    auto cross = [&](uint32_t &z, uint32_t y) {
+        if (z != y) {
+            atomicAdd(reinterpret_cast<int32_t *>(reinterpret_cast<char *>(dpop) + y), 1);
+            atomicAdd(reinterpret_cast<int32_t *>(reinterpret_cast<char *>(dpop) + z), -1);
+            z = y;
+        }
+    };
+    cross(z0, y0);
+    cross(z1, y1);
+    return (__popcll(l0) + __popcll(l1)) - (__popcll(r0) + __popcll(r1));
+}
+
+// The workgroup's tables, before the first step (ends with a barrier).
+__device__ inline void zone_setup(const ZoneRunArgs &a, ZoneLds &s, uint8_t *zone_at) {
+    const int tid = threadIdx.x, Z = a.zones;
+    for (int i = tid; i < kZoneMaxZones; i += blockDim.x) {
+        s.thr[0][i] = i < Z ? word_threshold(a.table[Z + i]) : 0u;
+        s.thr[1][i] = i < Z ? word_threshold(a.table[i]) : 0u;
+        s.dpop[0][i] = s.dpop[1][i] = 0;
+        s.pop[i] = i < Z ? (int32_t)a.pop[i] : 0;
+    }
+    for (int i = tid; i < kMaxKnots; i += blockDim.x) {
+        s.kt[i] = a.knot_t[i];
+        s.kv[i] = a.knot_v[i];
+    }
+    for (int i = tid; i <= kZoneMaxZones; i += blockDim.x) s.sum[0][i] = s.sum[1][i] = 0;
+    if (tid < 2) s.dnet[tid] = 0;
+    if (tid == 0) s.net = 0;
+    const float inv_sites = 1.0f / (float)a.sites;
+    for (int x = tid; x < a.sites + 2; x += blockDim.x)
+        zone_at[x] = x >= 1 && x <= a.sites ? (uint8_t)(4 * (zone_fast((uint32_t)x, (uint32_t)a.sites, (uint32_t)Z, inv_sites) - 1)) : 0;
+    __syncthreads();
+}
+
+// The end of step k in the first wavefront: populations, the output row (one
+// workgroup), the thresholds of step k + 1; V is the bias at that step.
+__device__ inline void zone_end_step(ZoneLds &s, int k, double V, bool writer) {
+    const ZoneKArgs ap = zone_kargs();
+    const auto &a = *ap;
+    const int tid = threadIdx.x, Z = a.zones, par = k & 1;
+    if (tid >= 64) return;
+    int64_t pop = 0;
+    if (tid < Z) {
+        pop = s.pop[tid] + s.sum[par][tid];
+        s.pop[tid] = (int32_t)pop;
+    }
+    const int32_t net = s.sum[par][Z];
+    s.sum[par ^ 1][tid] = 0;
+    if (tid == 0) s.sum[par ^ 1][kZoneMaxZones] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (tid < Z) {
+        // the table's space-charge sums in the order of zone_entry (the total
+        // is the ion count, exact in binary64)
+        const double mean = (double)((int64_t)a.rails * a.ions) / (double)Z;
+        double below = 0.0, above = 0.0;
+#pragma unroll 4
+        for (int y = 0; y < Z; ++y) {
+            const double rho = (double)s.pop[y] - mean;
+            if (y < tid) below += rho;
+            if (y > tid) above += rho;
+        }
+        double pl, pr;
+        zone_probabilities(below, above, V, a.p0, a.kT, a.hot, a.v_factor, &pl, &pr);
+        s.thr[0][tid] = word_threshold(pr);
+        s.thr[1][tid] = word_threshold(pl);
+        if (writer) {
+            if (a.zone_out) a.zone_out[(a.row0 + k) * Z + tid] = (int32_t)pop;
+            if (k == a.n_steps - 1) {
+                a.pop[tid] = pop;
+                a.table[tid] = pl;
+                a.table[Z + tid] = pr;
+            }
+        }
+    }
+    if (writer && tid == 0) {
+        s.net += net;
+        if (a.net_out) a.net_out[a.row0 + k] = net;
+        if (k == a.n_steps - 1) *a.net_total += s.net;
+    }
+}
+
+template <int P>
+__global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    ZoneLds &s = *reinterpret_cast<ZoneLds *>(smem);
+    uint8_t *zone_at = smem + sizeof(ZoneLds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int waves = blockDim.x >> 6;
+    // the gate: all workgroups are resident, or none runs
+    if (tid == 0) {
+        uint32_t seen = __hip_atomic_fetch_add(a.gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+        while (!(seen & kZoneAbort) && seen < gridDim.x) {
+            if ((int64_t)(__builtin_amdgcn_s_memrealtime() - t0) >= (int64_t)a.gate_ticks) {
+                // give up, unless the last workgroup arrives first
+                uint32_t expect = seen;
+                if (__hip_atomic_compare_exchange_strong(a.gate, &expect, seen | kZoneAbort, __ATOMIC_RELAXED,
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    expect = seen | kZoneAbort;
+                seen = expect;
+                continue;
+            }
+            __builtin_amdgcn_s_sleep(1);
+            seen = __hip_atomic_load(a.gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        s.go = seen & kZoneAbort ? 0 : 1;
+    }
+    zone_setup(a, s, zone_at);
+    if (!s.go) return;
+
+    // the wavefront's ions
+    const int half = lane >> 5, l = lane & 31, j0 = 2 * l, j1 = 2 * l + 1;
+    const int64_t pairs = ((int64_t)a.rails + 1) / 2;
+    const int64_t pair0 = ((int64_t)blockIdx.x * waves + wave) * P;
+    const uint32_t wall = (uint32_t)a.sites + 1u;
+    const bool last_lane = l == 31;
+    const uint64_t has0 = __ballot(j0 < a.ions), has1 = __ballot(j1 < a.ions);
+    uint32_t x0[P], x1[P], z0[P], z1[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const int64_t rail = 2 * (pair0 + k) + half;
+        const bool ok = rail < a.rails;
+        const uint16_t *row = a.X + rail * a.ions;
+        x0[k] = ok && j0 < a.ions ? row[j0] : wall;
+        x1[k] = ok && j1 < a.ions ? row[j1] : wall;
+    }
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        z0[k] = zone_at[x0[k]];
+        z1[k] = zone_at[x1[k]];
+    }
+    const uint32_t rail0 = (uint32_t)(2 * pair0 + half);
+    const int mine = (int)(pairs - pair0 < P ? (pairs - pair0 > 0 ? pairs - pair0 : 0) : P);  // pairs of this wavefront
+    const int odd_at = (a.rails & 1) ? (int)(pairs - 1 - pair0 < P ? pairs - 1 - pair0 : P) : P;  // the pair without a second rail
+    const ZoneLaneConst lc = zone_lane_const((uint32_t)l, a.key0, a.key1);
+    for (int i = tid; i < 2 * kZoneAcc * (kZoneMaxZones + 1); i += blockDim.x) (&s.before[0][0])[i] = 0;  // each its own reader
+    for (int k = 0; k < a.n_steps; ++k) {
+        const int par = k & 1;
+        // opaque: what is derived from these for every pair is not held over the steps
+        uint32_t rail_k = rail0;
+        int mine_k = __builtin_amdgcn_readfirstlane(mine), odd_k = __builtin_amdgcn_readfirstlane(odd_at);
+        asm volatile("" : "+v"(rail_k), "+s"(mine_k), "+s"(odd_k));
+        const uint32_t key0 = zone_kargs()->key0, key1 = zone_kargs()->key1;
+        const ZoneStepConst sc = zone_step_const(lc, (uint32_t)zone_kargs()->n0 + (uint32_t)k, key0, key1);
+        int net = 0;
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            if (q < mine_k) {
+                const uint4 w = zone_words(lc, sc, rail_k + 2u * (uint32_t)q, key0, key1);
+                const uint64_t v = q == odd_k ? 0xFFFFFFFFull : ~0ull;
+                net += zone_pair(x0[q], x1[q], z0[q], z1[q], w, has0 & v, has1 & v, wall, last_lane, &s.thr[0][0],
+                                 s.dpop[par], zone_at);
+            }
+            // no mixing of more pairs: their words would spill
+            if (q % kZonePairsMixed == kZonePairsMixed - 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        if (lane == 0 && net != 0) atomicAdd(&s.dnet[par], net);
+        kmc::lds_barrier();
+        const ZoneKArgs ka = zone_kargs();
+        const int Z = ka->zones;
+        unsigned long long *rows_at = ka->acc + par * kZoneAcc * kZoneAccStride;
+        if (tid <= Z) {
+            int32_t *at = tid < Z ? &s.dpop[par][tid] : &s.dnet[par];
+            const int64_t v = *at;
+            *at = 0;
+            __hip_atomic_fetch_add(rows_at + (blockIdx.x % kZoneAcc) * kZoneAccStride + tid,
+                                   (1ull << 40) + (unsigned long long)(v + kZoneBias), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // the bias of the next step, while the sums travel
+        double V = 0.0;
+        if (tid < 64) V = protocol_voltage(s.kt, s.kv, ka->n_knots, (double)(ka->n0 + k + 1 - ka->n_set) * ka->dt);
+        const int words = min((int)gridDim.x, kZoneAcc) * (Z + 1);
+        for (int e = tid; e < words; e += blockDim.x) {
+            const int row = e / (Z + 1), q = e - row * (Z + 1);
+            const int64_t members = ((int)gridDim.x - row + kZoneAcc - 1) / kZoneAcc;
+            const uint64_t want = (uint64_t)(members * (k / 2 + 1));
+            uint64_t v = 0;
+            int spins = 0;
+            while (((v = __hip_atomic_load(rows_at + row * kZoneAccStride + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >>
+                    40) != want) {
+                if (++spins > (1 << 22)) {
+                    s.go = 0;
+                    __hip_atomic_store(ka->bad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+            const int64_t low = (int64_t)(v & ((1ull << 40) - 1ull));
+            atomicAdd(&s.sum[par][q], (int32_t)(low - s.before[par][e] - members * kZoneBias));
+            s.before[par][e] = low;
+        }
+        kmc::lds_barrier();
+        zone_end_step(s, k, V, blockIdx.x == 0);
+        kmc::lds_barrier();
+        if (!s.go) return;
+    }
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const int64_t rail = 2 * (pair0 + k) + half;
+        uint16_t *row = a.X + rail * a.ions;
+        if (rail < a.rails) {
+            if (j0 < a.ions) row[j0] = (uint16_t)x0[k];
+            if (j1 < a.ions) row[j1] = (uint16_t)x1[k];
+        }
+    }
+}
+
+// Behind every zone_run: the same steps in one workgroup when the launch left
+// them undone (the ions in memory), and the accumulators and the gate cleared
+// for the next launch.
+__global__ __launch_bounds__(1024) void zone_rescue(ZoneRunArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x;
+    const bool undone = (*a.gate & kZoneAbort) != 0;
+    if (undone) {
+        ZoneLds &s = *reinterpret_cast<ZoneLds *>(smem);
+        uint8_t *zone_at = smem + sizeof(ZoneLds);
+        const int lane = tid & 63, half = lane >> 5, l = lane & 31, j0 = 2 * l, j1 = 2 * l + 1, Z = a.zones;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        zone_setup(a, s, zone_at);
+        const int64_t pairs = ((int64_t)a.rails + 1) / 2;
+        const uint32_t wall = (uint32_t)a.sites + 1u;
+        const ZoneLaneConst lc = zone_lane_const((uint32_t)l, a.key0, a.key1);
+            for (int k = 0; k < a.n_steps; ++k) {
+            const int par = k & 1;
+            const ZoneStepConst sc = zone_step_const(lc, (uint32_t)(a.n0 + k), a.key0, a.key1);
+            int net = 0;
+            for (int64_t pr = wave; pr < pairs; pr += blockDim.x >> 6) {
+                const int64_t rail = 2 * pr + half;
+                const bool h0 = rail < a.rails && j0 < a.ions, h1 = rail < a.rails && j1 < a.ions;
+                uint16_t *row = a.X + rail * a.ions;
+                uint32_t x0 = h0 ? row[j0] : wall, x1 = h1 ? row[j1] : wall;
+                uint32_t z0 = zone_at[x0], z1 = zone_at[x1];
+                const uint4 w = zone_words(lc, sc, (uint32_t)rail, a.key0, a.key1);
+                net += zone_pair(x0, x1, z0, z1, w, __ballot(h0), __ballot(h1), wall, l == 31, &s.thr[0][0], s.dpop[par],
+                                 zone_at);
+                if (h0) row[j0] = (uint16_t)x0;
+                if (h1) row[j1] = (uint16_t)x1;
+            }
+            if (lane == 0 && net != 0) atomicAdd(&s.dnet[par], net);
+            __syncthreads();
+            if (tid <= Z) {
+                int32_t *at = tid < Z ? &s.dpop[par][tid] : &s.dnet[par];
+                s.sum[par][tid] = *at;
+                *at = 0;
+            }
+            __syncthreads();
+            const double V = protocol_voltage(s.kt, s.kv, a.n_knots, (double)(a.n0 + k + 1 - a.n_set) * a.dt);
+            zone_end_step(s, k, V, true);
+            __syncthreads();
+        }
+    }
+    for (int i = tid; i < 2 * kZoneAcc * kZoneAccStride; i += blockDim.x) a.acc[i] = 0;
+    __syncthreads();
+    if (tid == 0) *a.gate = 0;
+}
+
 // The table of the step n from the populations pop (one workgroup).
 __global__ void zone_make_table(const int64_t *pop, int Z, const double *knot_t, const double *knot_v, int n_knots,
                                 int64_t n, int64_t n_set, double dt, double p0, double kT, double hot,
@@ -373,7 +802,9 @@ struct kmc_zone_ctx {
     int32_t n_knots = 1;
     int cur = 0;                // population buffer holding the current state
     // workspace layout
-    size_t off_X, off_pop, off_table, off_bucket, off_ticket, off_knots, off_total, off_bad, total;
+    int cus = 0;                // compute units of the GPU (0: the runs go step by step)
+    int32_t gate_ticks = 10000000;  // 0.1 s
+    size_t off_X, off_pop, off_table, off_bucket, off_ticket, off_knots, off_total, off_bad, off_acc, total;
     template <typename T>
     T *at(size_t off) { return reinterpret_cast<T *>(ws + off); }
 };
@@ -413,7 +844,8 @@ void zone_layout(kmc_zone_ctx *c) {
     c->off_ticket = take(sizeof(uint32_t) * (kZoneBuckets + 1) * 32);
     c->off_knots = take(sizeof(double) * 2 * kMaxKnots);
     c->off_total = take(sizeof(int64_t));
-    c->off_bad = take(sizeof(int32_t));
+    c->off_bad = take(sizeof(int32_t) * 4);  // rejected occupancy, -, timed-out wait, gate
+    c->off_acc = take(sizeof(uint64_t) * 2 * kZoneAcc * kZoneAccStride);
     c->total = off;
 }
 
@@ -451,6 +883,65 @@ kmc_status zone_refresh_table(kmc_zone_ctx *c) {
                        c->p.kT_ev, c->p.hop_over_thickness, c->p.v_factor,
                        c->at<double>(c->off_table) + c->cur * 2 * kZoneMaxZones);
     ZONE_HIP(c, hipGetLastError());
+    return KMC_OK;
+}
+
+size_t zone_run_lds(int sites) { return sizeof(ZoneLds) + (((size_t)sites + 2 + 15) & ~(size_t)15); }
+
+const void *zone_run_fn(int pairs) {
+    switch (pairs) {
+        case 1: return (const void *)zone_run<1>;
+        case 2: return (const void *)zone_run<2>;
+        case 4: return (const void *)zone_run<4>;
+        case 8: return (const void *)zone_run<8>;
+        default: return (const void *)zone_run<16>;
+    }
+}
+
+// Launch shape of zone_run: rail pairs per wavefront, workgroups, threads.  At
+// most one workgroup per compute unit, so that all are resident; small lattices
+// take four wavefronts per workgroup (one per SIMD) and one pair each, larger
+// ones sixteen and as few pairs as fit.  Beyond 16 pairs per wavefront the ions'
+// registers would spill: no pairs, and zone_step runs step by step (its 33 us
+// per step at 128,000 rails are memory passes that grow with the lattice).
+struct ZoneShape {
+    int pairs;
+    unsigned grid, block;
+};
+ZoneShape zone_shape(const kmc_zone_ctx *c) {
+    const int64_t pairs = ((int64_t)c->p.rails + 1) / 2;
+    if (c->cus < 1) return {0, 0, 0};
+    if (pairs <= 4 * (int64_t)c->cus) return {1, (unsigned)((pairs + 3) / 4), 256};
+    for (int per = 1; per <= kZoneRunMaxPairs; per *= 2) {
+        const int64_t grid = (pairs + 16 * per - 1) / (16 * per);
+        if (grid <= c->cus) return {per, (unsigned)grid, 1024};
+    }
+    return {0, 0, 0};
+}
+
+// Compute units on which every shape of zone_run is resident with a workgroup
+// each (0 when one does not fit).
+int zone_run_cus(int sites) {
+    int dev = 0;
+    hipDeviceProp_t prop;
+    if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+    const size_t lds = zone_run_lds(sites);
+    if (hipFuncSetAttribute((const void *)zone_rescue, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
+    for (int per = 1; per <= kZoneRunMaxPairs; per *= 2) {
+        int blocks = 0;
+        if (hipFuncSetAttribute(zone_run_fn(per), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, zone_run_fn(per), 1024, lds) != hipSuccess || blocks < 1)
+            return 0;
+    }
+    return prop.multiProcessorCount;
+}
+
+// The caller's occupancy after a run of n_steps.
+kmc_status zone_export_state(kmc_zone_ctx *c, int64_t n_steps) {
+    hipLaunchKernelGGL(zone_export, dim3((unsigned)((c->p.rails + 3) / 4)), dim3(256), 0, c->stream,
+                       c->at<uint16_t>(c->off_X), c->occ_user, c->p.rails, c->p.sites, c->p.ions_per_rail);
+    ZONE_HIP(c, hipGetLastError());
+    c->n += n_steps;
     return KMC_OK;
 }
 
@@ -522,6 +1013,11 @@ kmc_status kmc_zone_init(const kmc_zone_params *params, int8_t *occ_dev, void *w
         return fail_init(s);
     if ((s = zone_hip(c, zone_fill(c->at<int64_t>(c->off_total), 1, 0, c->stream), "clear total")) != KMC_OK)
         return fail_init(s);
+    if ((s = zone_hip(c, zone_fill(c->at<int64_t>(c->off_bad), 2, 0, c->stream), "clear flags")) != KMC_OK) return fail_init(s);
+    if ((s = zone_hip(c, zone_fill(c->at<int64_t>(c->off_acc), 2 * kZoneAcc * kZoneAccStride, 0, c->stream),
+                      "clear accumulators")) != KMC_OK)
+        return fail_init(s);
+    c->cus = zone_run_cus(c->p.sites);
     ZoneKnots k{};
     hipLaunchKernelGGL(zone_set_knots, dim3(1), dim3(64), 0, c->stream, c->at<double>(c->off_knots),
                        c->at<double>(c->off_knots) + kMaxKnots, k);
@@ -586,6 +1082,45 @@ kmc_status kmc_zone_run_steps(kmc_zone_ctx *c, int64_t n_steps, int32_t *net_dev
     a.zone_out = zone_dev;
     a.net_total = c->at<int64_t>(c->off_total);
     const int64_t pairs = ((int64_t)c->p.rails + 1) / 2;
+    const ZoneShape shape = zone_shape(c);
+    if (shape.pairs > 0) {
+        ZoneRunArgs r{};
+        r.X = a.X;
+        r.rails = a.rails;
+        r.ions = a.ions;
+        r.sites = a.sites;
+        r.zones = a.zones;
+        r.p0 = a.p0;
+        r.kT = a.kT;
+        r.hot = a.hot;
+        r.v_factor = a.v_factor;
+        r.dt = a.dt;
+        r.key0 = a.key0;
+        r.key1 = a.key1;
+        r.knot_t = a.knot_t;
+        r.knot_v = a.knot_v;
+        r.n_knots = a.n_knots;
+        r.n_set = a.n_set;
+        r.table = c->at<double>(c->off_table) + c->cur * 2 * kZoneMaxZones;
+        r.pop = c->at<int64_t>(c->off_pop) + c->cur * kZoneMaxZones;
+        r.acc = c->at<unsigned long long>(c->off_acc);
+        r.bad = c->at<int32_t>(c->off_bad) + 2;
+        r.gate = reinterpret_cast<uint32_t *>(c->at<int32_t>(c->off_bad) + 3);
+        r.net_out = net_dev;
+        r.zone_out = zone_dev;
+        r.net_total = a.net_total;
+        r.gate_ticks = c->gate_ticks;
+        const size_t lds = zone_run_lds(c->p.sites);
+        for (int64_t k = 0; k < n_steps; k += kZoneRunSteps) {
+            r.n0 = c->n + k;
+            r.row0 = k;
+            r.n_steps = (int32_t)std::min<int64_t>(kZoneRunSteps, n_steps - k);
+            void *kargs[] = {&r};
+            ZONE_HIP(c, hipLaunchKernel(zone_run_fn(shape.pairs), dim3(shape.grid), dim3(shape.block), kargs, lds, c->stream));
+            ZONE_HIP(c, hipLaunchKernel((const void *)zone_rescue, dim3(1), dim3(1024), kargs, lds, c->stream));
+        }
+        return zone_export_state(c, n_steps);
+    }
     const int64_t per_wg = (int64_t)(kZoneBlock / 64) * kZonePairsPerIter;
     const unsigned grid = (unsigned)std::min<int64_t>((pairs + per_wg - 1) / per_wg, kZoneMaxGrid);
     int64_t *pop = c->at<int64_t>(c->off_pop);
@@ -600,11 +1135,7 @@ kmc_status kmc_zone_run_steps(kmc_zone_ctx *c, int64_t n_steps, int32_t *net_dev
         ZONE_HIP(c, hipGetLastError());
         c->cur = 1 - c->cur;
     }
-    hipLaunchKernelGGL(zone_export, dim3((unsigned)((c->p.rails + 3) / 4)), dim3(256), 0, c->stream,
-                       c->at<uint16_t>(c->off_X), c->occ_user, c->p.rails, c->p.sites, c->p.ions_per_rail);
-    ZONE_HIP(c, hipGetLastError());
-    c->n += n_steps;
-    return KMC_OK;
+    return zone_export_state(c, n_steps);
 }
 
 kmc_status kmc_zone_read_positions(kmc_zone_ctx *c, int32_t *X_host, size_t count) {
@@ -613,13 +1144,27 @@ kmc_status kmc_zone_read_positions(kmc_zone_ctx *c, int32_t *X_host, size_t coun
     if (!X_host) return record_error(KMC_EINVAL, "X_host is NULL");
     const size_t n = (size_t)c->p.rails * (size_t)c->p.ions_per_rail;
     if (count < n) return record_error(KMC_ETOOSMALL, "X_host holds fewer than rails * ions_per_rail entries");
+    int32_t timed_out = 0;
+    ZONE_HIP(c, hipMemcpyAsync(&timed_out, c->at<int32_t>(c->off_bad) + 2, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
     std::vector<uint16_t> tmp(n);
     if (n > 0) {
         ZONE_HIP(c, hipMemcpyAsync(tmp.data(), c->at<uint16_t>(c->off_X), sizeof(uint16_t) * n, hipMemcpyDeviceToHost,
                                    c->stream));
     }
     ZONE_HIP(c, hipStreamSynchronize(c->stream));
+    if (timed_out) {
+        c->poisoned = true;
+        return record_error(KMC_EHIP, "zone kernel: a wait between workgroups timed out; state is invalid");
+    }
     for (size_t i = 0; i < n; ++i) X_host[i] = tmp[i];
+    return KMC_OK;
+}
+
+kmc_status kmc_zone_set_gate_limit(kmc_zone_ctx *c, int32_t microseconds) {
+    kmc_status s = zone_usable(c);
+    if (s != KMC_OK) return s;
+    if (microseconds < 0 || microseconds > 10000000) return record_error(KMC_EINVAL, "microseconds must be in [0, 10^7]");
+    c->gate_ticks = microseconds * 100;
     return KMC_OK;
 }
 
