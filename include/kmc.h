@@ -345,8 +345,9 @@ kmc_status kmc_fit_decay(const double *t, const double *m, int64_t n, double t0,
  *     half-steps that changed them.  Needs every device's rails to fit 64
  *     lanes (at least max(rail_range, 1) rails per tile unless the device is
  *     one tile) and every single device's tiling co-resident.
- *   KMC_LAUNCH_AUTO (default): WAVE when it fits, else PERSISTENT when it
- *     fits, else HALF_STEP.
+ *   KMC_LAUNCH_AUTO (default): WAVE when it fits (for rails of more than 2048
+ *     padded sites with 64 sites per lane, which only AUTO chooses), else
+ *     PERSISTENT when it fits, else HALF_STEP.
  * All give bit-identical trajectories. */
 typedef enum {
     KMC_LAUNCH_AUTO = 0,

@@ -48,7 +48,7 @@ hipError_t persistent_capacity(int block, size_t lds, bool fp64, int *blocks_per
 hipError_t launch_zero_i64(int64_t *p, int64_t n, hipStream_t st);
 hipError_t launch_wave(const PArgs &a, int spl, size_t lds, bool fp64, hipStream_t st);
 hipError_t wave_capacity(int spl, size_t lds, bool fp64, int *blocks_per_cu);
-size_t wave_lds_bytes(int spl, int n_kt, bool fp64);
+size_t wave_lds_bytes(int spl, int rail_range, int cut, bool fp64);
 int wave_band_words(int spl);
 hipError_t launch_copy_bytes(const void *src, void *dst, size_t bytes, hipStream_t st);
 hipError_t launch_replay_ec_full(const PhiArgs &a, bool fp64, hipStream_t st);
@@ -175,8 +175,10 @@ Layout layout_for(const kmc_params *p) {
     L.tiles = take(sizeof(Tile) * (size_t)rails);
     L.knot_t = take(sizeof(double) * kMaxKnots * D);
     L.knot_v = take(sizeof(double) * kMaxKnots * D);
-    L.ktab64 = take(sizeof(double) * (m + 1) * (L.cut + 1));
-    L.ktab32 = take(sizeof(float) * (m + 1) * (L.cut + 1));
+    // the kernel tables, each followed by its bond differences (wave kernel)
+    const size_t n_kt = (size_t)(m + 1) * (L.cut + 1 + kernel_diff_width(L.cut));
+    L.ktab64 = take(sizeof(double) * n_kt);
+    L.ktab32 = take(sizeof(float) * n_kt);
     L.tally_net = take(sizeof(int32_t) * kTallySteps * D);
     L.tally_dec = take(sizeof(int32_t) * kTallySteps * D * kDeciles);
     L.dec_run = take(sizeof(int64_t) * D * kDeciles);
@@ -207,7 +209,8 @@ Layout layout_for(const kmc_params *p) {
     // edge-rail snapshots; tiles of one launch bounded by kMaxWaveTiles
     {
         int64_t tiles = 0, slot = 1;
-        for (int spl : {16, 32}) {
+        for (int spl : {16, 32, 64}) {
+            if (spl == 64 && tiles > 0) break;  // only rails that 32 sites per lane do not hold
             int64_t t = 0;
             for (int d = 0; d < D; ++d) {
                 const int pitch = (p->sites[d] + kChunkSites - 1) / kChunkSites * kChunkSites;
@@ -477,8 +480,12 @@ void make_ptiles(kmc_ctx *c) {
 // Wave tiling: every device cut into n_t >= 1 tiles of consecutive rails that
 // fit one wavefront (rails x lanes per rail <= 64), sizes within one rail of
 // each other and at least max(rail_range, 1) rails unless the device is a
-// single tile.  Sites per lane: 16 when that tiling exists, else 32;
-// tile_sites 1024 or 2048 asks for 16 or 32.  False if the tiling with spl
+// single tile.  Sites per lane: 16 when that tiling exists, else 32, else 64
+// (rails of more than 2048 padded sites: at half the wavefronts per CU, since
+// eight Philox blocks per lane take twice the registers, but still one
+// wavefront per rail without barriers; 512 x 3001 with per-site barriers:
+// 15.0 us per step in half-step launches, 4.2 here); tile_sites 1024 or
+// 2048 asks for 16 or 32.  False if the tiling with spl
 // sites per lane does not exist.
 bool wave_tiles_for(kmc_ctx *c, int spl) {
     c->wtiles.clear();
@@ -518,21 +525,24 @@ void make_wtiles(kmc_ctx *c) {
         spl = 16;
     } else if (wave_tiles_for(c, 32)) {
         spl = 32;
+    } else if (wave_tiles_for(c, 64)) {
+        spl = 64;
     } else {
         return;
     }
     c->w_spl = spl;
-    const size_t n_kt = (size_t)(c->p.rail_range + 1) * (c->lay.cut + 1);
     int per_cu = 0, dev = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return;
     // Every workgroup asks for a quarter of the CU's LDS, so that a CU holds
-    // at most four (one wavefront per SIMD each).  A launch of exactly four
+    // at most four (one wavefront per SIMD each; a half and two with 64 sites
+    // per lane).  A launch of exactly four
     // workgroups per CU then gives every SIMD the same four tiles; with the
     // occupancy the registers allow (five), the dispatcher stacks five
     // workgroups on some CUs and three on others, and the tiles of the fuller
     // SIMDs set the launch's time.
-    c->w_lds = std::max(wave_lds_bytes(spl, (int)n_kt, c->fp64), (size_t)prop.maxSharedMemoryPerMultiProcessor / 4);
+    c->w_lds = std::max(wave_lds_bytes(spl, c->p.rail_range, c->lay.cut, c->fp64),
+                        (size_t)prop.maxSharedMemoryPerMultiProcessor / (spl == 64 ? 2 : 4));
     if (wave_capacity(spl, c->w_lds, c->fp64, &per_cu) != hipSuccess) return;
     // groups of whole devices, each co-resident (and within the publication memory)
     int64_t cap = std::min<int64_t>((int64_t)per_cu * prop.multiProcessorCount * kWaveTilesPerWG, c->lay.max_wtiles);
@@ -938,6 +948,20 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
             k32[(size_t)dr * (cut + 1) + ds] = (float)k64[(size_t)dr * (cut + 1) + ds];
         }
 
+    // behind each table, its differences K(dist, |x - cut - 1|) - K(dist, |x - cut|),
+    // x from 0 to 2 cut + 1: what an ion x - cut sites above a bond's lower end
+    // adds to a hop up that bond
+    std::vector<double> tab64 = k64;
+    std::vector<float> tab32 = k32;
+    if (kernel_diff_width(cut) > 0)
+        for (int dr = 0; dr <= m; ++dr)
+            for (int x = 0; x < kernel_diff_width(cut); ++x) {
+                const int up = std::abs(x - cut - 1), down = std::abs(x - cut);
+                const size_t row = (size_t)dr * (cut + 1);
+                tab64.push_back((up > cut ? 0.0 : k64[row + up]) - (down > cut ? 0.0 : k64[row + down]));
+                tab32.push_back((up > cut ? 0.0f : k32[row + up]) - (down > cut ? 0.0f : k32[row + down]));
+            }
+
     // Dense potential (KMC_BF16X2): the distinct 32 x 32 blocks of
     // T[(dist, j)][s] = K(s - j, dist), as MFMA B fragments, each value split
     // into BF16 hi = RN(K) and lo = RN(K - hi).  Block (dist, delta) holds
@@ -1049,8 +1073,8 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
     chk(h2d(lay.ptiles, c->ptiles.data(), sizeof(PTile) * c->ptiles.size()), "copy persistent tiles");
     if (!c->wtiles.empty())
         chk(h2d(lay.wtiles, c->wtiles.data(), sizeof(PTile) * c->wtiles.size()), "copy wave tiles");
-    chk(h2d(lay.ktab64, k64.data(), sizeof(double) * k64.size()), "copy kernel table");
-    chk(h2d(lay.ktab32, k32.data(), sizeof(float) * k32.size()), "copy kernel table");
+    chk(h2d(lay.ktab64, tab64.data(), sizeof(double) * tab64.size()), "copy kernel table");
+    chk(h2d(lay.ktab32, tab32.data(), sizeof(float) * tab32.size()), "copy kernel table");
     if (c->dense) {
         chk(h2d(lay.ktiles, kt_host.data(), sizeof(uint16_t) * kt_host.size()), "copy kernel blocks");
         chk(h2d(lay.dtiles, c->dtiles.data(), sizeof(Tile) * c->dtiles.size()), "copy dense tiles");
@@ -1230,7 +1254,8 @@ kmc_status kmc_set_launch_mode(kmc_ctx *c, int32_t mode) {
     if (mode < KMC_LAUNCH_AUTO || mode > KMC_LAUNCH_WAVE) return fail(KMC_EINVAL, "unknown launch mode");
     if (mode == KMC_LAUNCH_PERSISTENT && !c->p_ok)
         return fail(KMC_EUNSUPPORTED, "the persistent tiling does not fit co-resident on this GPU");
-    if (mode == KMC_LAUNCH_WAVE && !c->w_ok)
+    // (64 sites per lane are the automatic strategy's own choice)
+    if (mode == KMC_LAUNCH_WAVE && (!c->w_ok || c->w_spl == 64))
         return fail(KMC_EUNSUPPORTED, "the wave tiling does not fit co-resident on this GPU");
     c->mode = mode;
     return KMC_OK;
@@ -1350,6 +1375,7 @@ kmc_status kmc_autotune(kmc_ctx *c, int32_t trial_steps, int32_t *tile_sites, in
     std::vector<Cand> cands;
     if (!c->dense && !c->phifix) {
         for (int t : {1024, 2048}) cands.push_back({KMC_LAUNCH_WAVE, t});
+        cands.push_back({KMC_LAUNCH_AUTO, 0});  // tried below only where it is wave tiles of 64 sites per lane
         for (int t : {0, 4096, 8192, 12288, 16384}) cands.push_back({KMC_LAUNCH_PERSISTENT, t});
     }
     for (int t : {0, 1024, 2048, 8192}) cands.push_back({KMC_LAUNCH_HALF_STEP, t});
@@ -1364,6 +1390,7 @@ kmc_status kmc_autotune(kmc_ctx *c, int32_t trial_steps, int32_t *tile_sites, in
         if (s != KMC_OK) break;
         if (cd.mode == KMC_LAUNCH_PERSISTENT && !c->p_ok) continue;
         if (cd.mode == KMC_LAUNCH_WAVE && !c->w_ok) continue;
+        if (cd.mode == KMC_LAUNCH_AUTO && !(c->w_ok && c->w_spl == 64)) continue;
         c->mode = cd.mode;
         float ms = 0.0f;
         bool ok = true;

@@ -19,6 +19,10 @@ constexpr int kDeciles = 10;
 constexpr int kClasses = 128;            // barrier classes in bits 1..7 of a state byte
 constexpr int kLdsTableMax = 2048;       // kernel-table entries kept in LDS
 
+// Entries per rail distance of the bond-difference table behind a kernel
+// table: a bond's window of 2 cut + 2 sites, where a wavefront holds it.
+__host__ __device__ constexpr int kernel_diff_width(int cut) { return 2 * cut + 2 <= 64 ? 2 * cut + 2 : 0; }
+
 // Per-device description, resident in the workspace.
 struct DevInfo {
     int32_t rails, sites, pitch;         // pitch = sites rounded up to 16
@@ -100,7 +104,7 @@ struct HopArgs {
     const double *knot_t;      // [D][kMaxKnots]
     const double *knot_v;
     const void *ea;            // null or per-site barrier (float or double)
-    const double *ktab64;      // [(m+1)][(c+1)] kernel table, binary64
+    const double *ktab64;      // [(m+1)][(c+1)] kernel table, binary64, then its bond differences
     const float *ktab32;       // same, rounded once to binary32
     int32_t cutoff, rail_range;
     double ea_scalar, beta, c0, alpha, dt;

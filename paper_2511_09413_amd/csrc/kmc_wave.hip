@@ -1,7 +1,7 @@
 // Persistent hop-step kernel with one wavefront per tile.
 //
 // A tile is whole rails of one device that fit one wavefront: each lane owns
-// SPL (16 or 32) consecutive sites of a rail for the whole launch and keeps
+// SPL (16, 32 or 64) consecutive sites of a rail for the whole launch and keeps
 // their occupancy as bits in a register, with the next lane's first bit (the
 // far end of its last bond) beside them, refreshed by a cross-lane move only
 // after half-steps that moved ions.  A half-step therefore needs neither an
@@ -29,9 +29,22 @@
 // the status flag, all tiles leave their loops and the host reports the error.
 //
 // Per bond the work is that of hop_half_step: Philox4x32-10 draw, candidate
-// test, exact two-stage prefilter, survivor energy (wavefront-cooperative
-// window sum in the same order as the other kernels), Arrhenius probability
-// and accept test.
+// test, exact two-stage prefilter, survivor energy (window sum in the same
+// order as the other kernels), Arrhenius probability and accept test.
+//
+// What bounds it: with every SIMD full (4096 x 1024) the VALU issue of the
+// common path, 1.51 -> 1.45 us per step when everything rare was nested in its
+// one branch (no value of a rare path merged or spilled on the common one: 87
+// and 82 -> 81 and 76 VALU per half-step); in small lattices that common path's
+// latency (64 x 128 in binary64 0.95 -> 0.82 us per step); at barriers where a
+// tile has survivors every half-step, their latency chain: neighbours'
+// state, neighbours' snapshot, window, barrier, decision.  Survivors are
+// therefore decided kSurvivorsAtOnce at a time, each by a group of lanes, from
+// rail windows held as 64-bit masks and a table of kernel differences, with
+// the barrier loaded ahead of the window (128 x 1024 at 0.15 eV, about four
+// survivors per tile and half-step: 20.4 us per step one at a time over the
+// wavefront, 13.6 in twos, 11.8 in fours, 12.3 in eights; eights also slow the
+// rare survivors of 4096 x 1024, 1.48 us per step against 1.45).
 #include <type_traits>
 
 #include "kmc_device.h"
@@ -42,6 +55,7 @@ namespace kmc {
 namespace {
 
 constexpr int kWaveWin = 64;         // per-step table entries: one per lane
+constexpr int kSurvivorsAtOnce = 4;  // survivors decided together, sixteen lanes each
 
 // Values of a tile that only the rare paths need.  They live in LDS and are
 // read again where needed, so that they do not hold scalar registers across
@@ -58,23 +72,53 @@ struct WaveGeo {
 };
 static_assert(sizeof(WaveGeo) % 16 == 0, "LDS tiles stay 16-byte aligned");
 
+// A lane's occupancy bits.
+template <int SPL>
+using LaneBits = typename std::conditional<SPL == 64, uint64_t, uint32_t>::type;
+
+// A prefilter survivor of a half-step, listed for its group of lanes.
+struct Survivor {
+    uint32_t at;     // row << 16 | (1 << 15 when the ion moves down) | site of the bond
+    uint32_t word;   // its Philox word
+};
+
 // A tile's LDS: its rare-path values, per-device and per-step tables and the
 // rare-path buffers.
-template <int SPL>
+template <typename Real, int SPL>
 struct WaveLds {
     static constexpr int kBand = 4 * SPL + 16;  // 32-bit words of neighbour rails
+    static constexpr int kSnap = SPL == 64 ? 128 : 64;
     WaveGeo geo;
     double cls_a[kClasses];              // exp(-beta (ea_min + q ea_step)) of the tile's device
     double step_v[kWaveWin];             // bias of the steps of the current window
     double step_g[kWaveWin];             // exp(beta (|alpha V| / L + coul_bound) / 2)
-    uint32_t snap[64];                   // each lane's bits at the start of a survivor half-step
+    Survivor list[64];             // survivors of a round: at most one per lane
+    uint32_t snap[kSnap];                // the tile's rails at the start of a survivor half-step, W32 words each
     uint32_t band[kBand];                // neighbour rails: prev tile's last m, next tile's first m
+    uint32_t band_idx[64];               // entry i of band (i < 64): idx << 16 | q of fetch_bands
+    unsigned char row_of[64];            // each lane's rail in the tile
     int16_t snap_state[kSnapSlots];      // launch-relative state of each ring slot's snapshot
     unsigned char cls[64 * SPL];         // barrier class of every site, rows at the device pitch
 };
-static_assert(sizeof(WaveLds<16>) % 16 == 0 && sizeof(WaveLds<32>) % 16 == 0, "LDS tiles stay 16-byte aligned");
-static_assert(offsetof(WaveLds<16>, cls) % 16 == 0 && offsetof(WaveLds<32>, cls) % 16 == 0,
-              "class rows are written as 16-byte vectors");
+template <typename Real, int SPL>
+constexpr bool wave_lds_aligned() {
+    // tiles stay 16-byte aligned, class rows are written as 16-byte vectors
+    using Lds = WaveLds<Real, SPL>;
+    return sizeof(Lds) % 16 == 0 && offsetof(Lds, cls) % 16 == 0;
+}
+static_assert(wave_lds_aligned<float, 16>() && wave_lds_aligned<float, 32>() && wave_lds_aligned<float, 64>() &&
+              wave_lds_aligned<double, 16>() && wave_lds_aligned<double, 32>() && wave_lds_aligned<double, 64>(), "LDS layout");
+
+// The workgroup's table before its tiles: the bond differences where there
+// are such (kernel_diff_width), else the kernel K(dist, ds) when it fits.
+__host__ __device__ inline int wave_table_entries(int rail_range, int cut) {
+    if (kernel_diff_width(cut) > 0) return (rail_range + 1) * kernel_diff_width(cut);
+    const int n_kt = (rail_range + 1) * (cut + 1);
+    return n_kt <= kLdsTableMax ? n_kt : 0;
+}
+__host__ __device__ inline size_t wave_table_bytes(int rail_range, int cut, size_t real) {
+    return ((size_t)wave_table_entries(rail_range, cut) * real + 15) & ~(size_t)15;
+}
 
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -241,12 +285,13 @@ __device__ __forceinline__ uint32_t pick_word(const uint32_t (&wd)[N], int i) {
 }  // namespace
 
 template <typename Real, int SPL>
-__global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
+__global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_wave(PArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int kW = SPL / 2;          // Philox words per lane and half-step (SPL / 8 blocks):
                                          // word b / 2 belongs to the bond at site s0 + b
     constexpr int kNB = SPL / 8;         // Philox blocks per lane and half-step
-    constexpr uint32_t kAll = SPL == 32 ? 0xFFFFFFFFu : 0xFFFFu;
+    using Bits = LaneBits<SPL>;
+    constexpr Bits kAll = SPL == 16 ? (Bits)0xFFFFu : ~(Bits)0;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: tile data in scalar registers
 
@@ -257,29 +302,27 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
     const PTile tile = a.tiles[ti < a.n_tiles ? ti : 0];
     const DevInfo dvc = a.devs[tile.d];
     const int nr_prev = a.tiles[tile.prev].nr, nr_next = a.tiles[tile.next].nr;
-    // the kernel table K(dist, ds), shared by the workgroup's tiles
+    // the table shared by the workgroup's tiles
     {
-        const int n_kt = (a.rail_range + 1) * (a.cutoff + 1);
-        if (n_kt <= kLdsTableMax) {
-            const Real *kt_glob = std::is_same<Real, double>::value ? reinterpret_cast<const Real *>(a.ktab64)
-                                                                    : reinterpret_cast<const Real *>(a.ktab32);
-            for (int i = threadIdx.x; i < n_kt; i += blockDim.x) reinterpret_cast<Real *>(smem)[i] = kt_glob[i];
-        }
+        const Real *tab = std::is_same<Real, double>::value ? reinterpret_cast<const Real *>(a.ktab64)
+                                                            : reinterpret_cast<const Real *>(a.ktab32);
+        if (kernel_diff_width(a.cutoff) > 0) tab += (a.rail_range + 1) * (a.cutoff + 1);
+        const int n = wave_table_entries(a.rail_range, a.cutoff);
+        for (int i = threadIdx.x; i < n; i += blockDim.x) reinterpret_cast<Real *>(smem)[i] = tab[i];
     }
     __syncthreads();
     // the tile's LDS (after the kernel table when that is in LDS)
-    auto lds_of = [&](KArgs ka) -> WaveLds<SPL> & {
-        const int n_kt = (ka->rail_range + 1) * (ka->cutoff + 1);
-        const size_t kt_bytes = n_kt <= kLdsTableMax ? (((size_t)n_kt * sizeof(Real) + 15) & ~(size_t)15) : 0;
-        return reinterpret_cast<WaveLds<SPL> *>(smem + kt_bytes)[wave];
+    auto lds_of = [&](KArgs ka) -> WaveLds<Real, SPL> & {
+        return reinterpret_cast<WaveLds<Real, SPL> *>(smem + wave_table_bytes(ka->rail_range, ka->cutoff, sizeof(Real)))[wave];
     };
-    WaveLds<SPL> &w = lds_of(kargs());
+    WaveLds<Real, SPL> &w = lds_of(kargs());
 
     if (ti >= a.n_tiles) return;  // no barrier follows
 
     // ------------------------------------------------------------ set-up
     // Values the loop itself needs stay in registers; the rest goes to w.geo.
-    uint32_t bits = 0, valid = 0, rail = 0, r_lane = 0, nbit = 0;
+    Bits bits = 0, valid = 0;
+    uint32_t rail = 0, r_lane = 0, nbit = 0;
     uint32_t bx = 0;  // 16 sites per lane: bits | nbit << 16
     int s0 = 0, cls_base = 0, d = 0;
     bool isolated = true;
@@ -333,7 +376,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
         cls_base = row * P;
         rail = (uint32_t)(tile.r0 + row);
         const int last = L - 2 - s0;  // the bond at s0 + b lies inside the rail iff b <= last
-        valid = (!has || last < 0) ? 0u : (last >= SPL - 1 ? kAll : ((2u << last) - 1u));
+        valid = (!has || last < 0) ? (Bits)0 : (last >= SPL - 1 ? kAll : (Bits)(((Bits)2 << last) - 1u));
 
         // load the tile: occupancy bits to registers, barrier classes to LDS
         const int8_t *gstate = a.occ + dv.off_pad + (int64_t)tile.r0 * P;
@@ -342,7 +385,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
             for (int c = 0; c < SPL / 16; ++c) {
                 if (c == 0 || s0 + 16 * c < P) {
                     const uint4 v = *reinterpret_cast<const uint4 *>(gstate + row * P + s0 + 16 * c);
-                    bits |= occ_bits(v) << (16 * c);
+                    bits |= (Bits)occ_bits(v) << (16 * c);
                     *reinterpret_cast<uint4 *>(w.cls + row * P + s0 + 16 * c) =
                         make_uint4((v.x >> 1) & 0x7F7F7F7Fu, (v.y >> 1) & 0x7F7F7F7Fu, (v.z >> 1) & 0x7F7F7F7Fu,
                                    (v.w >> 1) & 0x7F7F7F7Fu);
@@ -350,11 +393,16 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
             }
         }
         for (int q = lane; q < kClasses; q += 64) w.cls_a[q] = exp(-a.beta * (dv.ea_min + (double)q * dv.ea_step));
+        w.row_of[lane] = (unsigned char)row;
+        {
+            const int w32 = (P + 31) / 32, idx = lane / w32;
+            w.band_idx[lane] = (uint32_t)idx << 16 | (uint32_t)(lane - idx * w32);
+        }
         wave_sync();
         // the next lane's first site (the far end of the lane's last bond);
         // refreshed only after half-steps that moved ions
-        nbit = __shfl_down(bits, 1, 64) & 1u;
-        bx = bits | (nbit << 16);
+        nbit = __shfl_down((uint32_t)bits, 1, 64) & 1u;
+        bx = (uint32_t)bits | (nbit << 16);
 
         // Stage-0 scale of the lane: every origin of its bonds (sites s0 ..
         // s0 + SPL) has a class >= q_lo, so every exact threshold is at most
@@ -376,7 +424,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
     PhLane<kNB> phl;
     ph_lane_init<0>(phl, (uint32_t)(s0 >> 3), (uint32_t)d << 4, a.key0, a.key1);
     // the candidate bonds of each parity that lie inside the rail
-    const uint32_t valid_e = valid & 0x55555555u, valid_o = valid & 0xAAAAAAAAu;
+    const Bits valid_e = valid & (Bits)0x5555555555555555ull, valid_o = valid & (Bits)0xAAAAAAAAAAAAAAAAull;
     // the tile's publication words are written by one lane: keeping their base
     // in a vector register frees two scalar registers for the whole loop
     asm volatile("" : "+v"(own));
@@ -388,7 +436,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
     uint32_t t_add = 8600u;  // the stage-0 margin of the window (uniform, kept in a vector register)
     auto refresh = [&](int kb) {
         const KArgs ka = kargs();
-        WaveLds<SPL> &wr = *lds_opaque(&w);
+        WaveLds<Real, SPL> &wr = *lds_opaque(&w);
         const WaveGeo &g = wr.geo;
         const int dd = rfl(g.d);
         const int64_t k = rfl(g.n_base) - rfl(g.n_set) + kb + lane;
@@ -406,9 +454,14 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
     // 32 bits [32 q, 32 q + 32) of tile row r, gathered from the owning lanes;
     // every lane takes part in the cross-lane reads
     auto row_word = [&](int lpr, int r, int q) -> uint32_t {
-        if (SPL == 32) return __shfl(bits, r * lpr + q, 64);
-        const uint32_t lo = __shfl(bits, r * lpr + 2 * q, 64);
-        const uint32_t hi = __shfl(bits, r * lpr + (2 * q + 1 < lpr ? 2 * q + 1 : 2 * q), 64);
+        if constexpr (SPL == 64) {
+            const uint32_t even = __shfl((uint32_t)bits, r * lpr + q / 2, 64);
+            const uint32_t odd = __shfl((uint32_t)(bits >> 32), r * lpr + q / 2, 64);
+            return q & 1 ? odd : even;
+        }
+        if (SPL == 32) return __shfl((uint32_t)bits, r * lpr + q, 64);
+        const uint32_t lo = __shfl((uint32_t)bits, r * lpr + 2 * q, 64);
+        const uint32_t hi = __shfl((uint32_t)bits, r * lpr + (2 * q + 1 < lpr ? 2 * q + 1 : 2 * q), 64);
         return lo | (2 * q + 1 < lpr ? hi << 16 : 0u);
     };
     // snapshot of the edge rails as state jrel into ring slot `slot`
@@ -430,7 +483,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
     // wait for the owning tile's state, then the word of its snapshot), so
     // that the round trips to the other tiles' publications overlap.  Uniform
     // result.
-    auto fetch_bands = [&](KArgs ka, WaveLds<SPL> &wr, int64_t jrel) -> bool {
+    auto fetch_bands = [&](KArgs ka, WaveLds<Real, SPL> &wr, int64_t jrel) -> bool {
         const WaveGeo &g = wr.geo;
         const int w32 = rfl(g.W32), mm = rfl(g.m), prev = rfl(g.prev), next = rfl(g.next);
         const int nr_p = rfl(g.nr_prev), nr_n = rfl(g.nr_next);
@@ -440,7 +493,15 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
         const int limit = ka->spin_limit;
         bool ok = true;
         for (int i = lane; i < 2 * mm * w32; i += 64) {
-            const int idx = i / w32, q = i - idx * w32;
+            int idx, q;
+            if (i < 64) {
+                const uint32_t at = wr.band_idx[i];
+                idx = (int)(at >> 16);
+                q = (int)(at & 0xFFFFu);
+            } else {
+                idx = i / w32;
+                q = i - idx * w32;
+            }
             const int T = idx < mm ? prev : next;
             const int nrT = idx < mm ? nr_p : nr_n;
             const int eT = nrT < 2 * mm ? nrT : 2 * mm;
@@ -480,99 +541,200 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
     uint32_t tag_j = tag_hi;
     asm volatile("" : "+v"(tag_j), "+v"(snap_count));
 
-    // One half-step of parity h (a compile-time constant): state js = 2 kstep
-    // + h to js + 1 (the first state of a launch is even).  False when a wait
-    // for a neighbour failed.
-    auto half_step = [&](auto h_c, const int kstep, const PhStep<kNB> &ps) -> bool {
+    // The survivors of a half-step (rare): bonds whose words passed the class
+    // test, in the bits sv of the lanes any, and each lane's lowest one's word.  Flips the accepted hops' sites and,
+    // when an edge rail changed, writes the new state's snapshot.  False when a
+    // wait for a neighbour failed.
+    auto survivors = [&](auto h_c, const int kstep, Bits sv, const uint32_t w_low, const uint64_t any) __attribute__((always_inline)) -> bool {
         constexpr int h = decltype(h_c)::value;
-        // the state index, needed only on rare paths: derived there from an
-        // opaque copy of the step, so that no register holds it across the step
+        // the state index: derived from an opaque copy of the step, so that no
+        // register holds it across the step
         auto js_now = [&]() -> int {
             int k = kstep;
             asm volatile("" : "+s"(k));
             return 2 * k + h;
         };
         const int kw = kstep & (kWaveWin - 1);
-
-        // candidates: bonds of parity h whose two sites differ
-        // (the site after bond b: bit b + 1, or the next lane's first site)
-        const uint32_t after = SPL == 32 ? __builtin_amdgcn_alignbit(nbit, bits, 1) : bx >> 1;
-        const uint32_t cand = (bits ^ after) & (h ? valid_o : valid_e);
-
-        // Philox words (the key is read from the kernel arguments each
-        // half-step, a scalar load, rather than held in scalar registers)
-        uint32_t wd[kW];
-        {
-            const KArgs ka = kargs();
-            ph_words<h>(wd, phl, ps, ka->key0, ka->key1);
+        bool edge_changed = false;
+        const KArgs ka = kargs();
+        WaveLds<Real, SPL> &wr = *lds_opaque(&w);
+        const WaveGeo &g = wr.geo;
+        const int cut = rfl(g.cutoff), Lq = rfl(g.L), lprq = rfl(g.lpr), nrq = rfl(g.nr), mq = rfl(g.m);
+        const int w32 = rfl(g.W32), Rq = rfl(g.R), n_nbr = rfl(g.n_nbr), r0 = rfl(g.r0), dd = rfl(g.d);
+        const bool single = rfl(g.single) != 0;
+        const int64_t n = rfl(g.n_base) + kstep;
+        // the tile's rails, packed: each lane's bits follow the previous lane's
+        if (s0 < 32 * w32 && lane < nrq * lprq) {
+            const int row = wr.row_of[lane];
+            unsigned char *at = reinterpret_cast<unsigned char *>(wr.snap) + 4 * row * w32 + s0 / 8;
+            if constexpr (SPL == 16) *reinterpret_cast<uint16_t *>(at) = (uint16_t)bits;
+            else if constexpr (SPL == 32) *reinterpret_cast<uint32_t *>(at) = (uint32_t)bits;
+            else {
+                reinterpret_cast<uint32_t *>(at)[0] = (uint32_t)bits;
+                if (s0 / 32 + 1 < w32) reinterpret_cast<uint32_t *>(at)[1] = (uint32_t)(bits >> 32);
+            }
         }
-        // stage 0: the smallest word against the bound of the lane's lowest
-        // class; stage 1 (rare): each candidate's word against its origin's
-        // exact class threshold
-        const uint32_t thr0 = (uint32_t)__builtin_amdgcn_readlane((int)thr_lane, kw);
-        const uint32_t t_lane = __builtin_elementwise_add_sat(__umulhi(thr0, r_lane), t_add);
-        const uint32_t mn = min_word<0>(wd);
-        // the common path decides with one wavefront vote that no lane has a
-        // stage-0 word; only then are the survivor bits and their vote formed
-        const bool stage1 = mn <= t_lane && cand != 0u;
-        uint32_t sv = 0;
-        uint64_t any = 0;
-        if (__ballot(stage1)) {
-            if (stage1) {
-                const double c0 = kargs()->c0;
-                WaveLds<SPL> &wr = *lds_opaque(&w);
-                const double g_step = wr.step_g[kw];
-                uint32_t c = cand;
-                while (c) {
-                    const int b = __builtin_ctz(c);
-                    c &= c - 1;
-                    const uint32_t x = pick_word<0>(wd, b >> 1);
-                    if (x <= t_lane) {
-                        const int o = s0 + (((bits >> b) & 1u) ? b : b + 1);
-                        if (x <= threshold_of(c0, wr.cls_a[wr.cls[cls_base + o]], g_step)) sv |= 1u << b;
-                    }
+        bool ok = true;
+        if (!isolated) ok = fetch_bands(ka, wr, js_now());
+        wave_sync();
+        if (!ok) return false;
+        // rail rho of the tile's neighbourhood (r0 + rho in the device)
+        auto rail_words = [&](int rho) -> const uint32_t * {
+            if (single) {
+                while (rho < 0) rho += Rq;
+                while (rho >= Rq) rho -= Rq;
+            } else if (rho < 0) {
+                return wr.band + (rho + mq) * w32;
+            } else if (rho >= nrq) {
+                return wr.band + (mq + rho - nrq) * w32;
+            }
+            return wr.snap + rho * w32;
+        };
+        // the decision on bond (s, s + 1) of tile row `row`, with its Coulomb part
+        auto decide = [&](Real part, Real ea, uint32_t word, int row, int s, int o, int t) -> bool {
+            const Real alpha_r = (Real)ka->alpha, beta_r = (Real)ka->beta, c0_r = (Real)ka->c0;
+            const Real e_app = ((alpha_r * (Real)wr.step_v[kw]) * (Real)(t - o)) / (Real)Lq;
+            const int srail = r0 + row;
+            HopArgs::LogBuf log;
+            log.count = ka->log.count;
+            log.entries = ka->log.entries;
+            log.cap = ka->log.cap;
+            const bool acc = decide_hop<Real>(e_app + part, ea, word, beta_r, c0_r, log, dd, h, n, srail, s);
+            if (acc) {
+                HopRecord rec;
+                rec.buf = ka->record.buf;
+                rec.count = ka->record.count;
+                rec.cap = ka->record.cap;
+                rec.n0 = ka->record.n0;
+                rec.n_hs = ka->record.n_hs;
+                record_hop(rec, dd, h, n, srail, s, o == s ? 0 : 1);
+                const int64_t base = (n - rfl(g.tally_base)) * ka->n_devices + dd;
+                atomicAdd(&ka->tally_net[base], t < o ? 1 : -1);
+                const int qo = (10 * o) / Lq, qt = (10 * t) / Lq;
+                if (qo != qt) {
+                    atomicAdd(&ka->tally_dec[base * kDeciles + qo], -1);
+                    atomicAdd(&ka->tally_dec[base * kDeciles + qt], 1);
                 }
             }
-            any = __ballot(sv != 0u);
-        }
-
-        // survivors (rare): one at a time over the whole wavefront
-        bool edge_changed = false;
-        if (any) {
-            const KArgs ka = kargs();
-            WaveLds<SPL> &wr = *lds_opaque(&w);
-            const WaveGeo &g = wr.geo;
-            const int cut = rfl(g.cutoff), Lq = rfl(g.L), lprq = rfl(g.lpr), nrq = rfl(g.nr), mq = rfl(g.m);
-            const int w32 = rfl(g.W32), Rq = rfl(g.R), n_nbr = rfl(g.n_nbr), r0 = rfl(g.r0), dd = rfl(g.d);
-            const bool single = rfl(g.single) != 0;
-            const int64_t n = rfl(g.n_base) + kstep;
-            const int n_kt = (ka->rail_range + 1) * (cut + 1);
+            return acc;
+        };
+        // the word of a bond, drawn again (the half-step's words are not held
+        // in registers over this path)
+        auto word_at = [&](int s, uint32_t r) -> uint32_t {
+            const uint4 blk = philox4x32_10((uint32_t)s >> 3, r, (uint32_t)n, (uint32_t)dd << 4 | (uint32_t)h, ka->key0, ka->key1);
+            return word_of(blk, (s >> 1) & 3);
+        };
+        auto barrier_of = [&](int row, int o) -> Real {
+            return ka->ea ? reinterpret_cast<const Real *>(ka->ea)[rfl(g.dv_off) + (int64_t)(r0 + row) * Lq + o]
+                          : (Real)ka->ea_scalar;
+        };
+        Bits fl = 0;
+        auto flip = [&](int row, int s) {
+            if (lane == row * lprq + s / SPL) fl ^= (Bits)1 << (s % SPL);
+            if (lane == row * lprq + (s + 1) / SPL) fl ^= (Bits)1 << ((s + 1) % SPL);
+            if (row < mq || row >= nrq - mq) edge_changed = true;
+        };
+        if (2 * cut + 2 <= 64) {
+            // kGroup lanes per survivor.  A lane of a group holds the terms
+            // of the window's sites g, g + kGroup, ... in accumulators of
+            // their own and combines them in the order in which a whole
+            // wavefront with a site per lane would (halves 32 apart, then 16,
+            // ...), so that the sum is the same to the last bit.
+            constexpr int kGroup = 64 / kSurvivorsAtOnce, kAcc = 64 / kGroup;
+            const int grp = lane / kGroup, gl = lane % kGroup;
+            const Real *diff = reinterpret_cast<const Real *>(smem);
+            uint64_t lanes = any;
+            bool first_round = true;
+            while (lanes) {
+                // a round: every lane lists its lowest survivor
+                if (sv) {
+                    const int b = SPL == 64 ? __builtin_ctzll(sv) : __builtin_ctz((uint32_t)sv);
+                    sv &= sv - 1;
+                    const int row = wr.row_of[lane];
+                    const bool down = ((bits >> b) & 1u) == 0u;
+                    Survivor e;
+                    e.at = (uint32_t)row << 16 | (down ? 0x8000u : 0u) | (uint32_t)(s0 + b);
+                    e.word = first_round ? w_low : word_at(s0 + b, rail);
+                    wr.list[__builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0u))] = e;
+                }
+                first_round = false;
+                const int count = __popcll(lanes);
+                lanes = __ballot(sv != 0u);
+                wave_sync();
+                for (int first = 0; first < count; first += kSurvivorsAtOnce) {
+                    const bool have = first + grp < count;
+                    const Survivor e = wr.list[have ? first + grp : 0];
+                    const int row = (int)(e.at >> 16), s = (int)(e.at & 0x7FFFu);
+                    const bool down = (e.at & 0x8000u) != 0u;
+                    Real ea = (Real)0;  // loaded ahead of the window
+                    if (have && gl == 0) ea = barrier_of(row, down ? s + 1 : s);
+                    int lo = s - cut, hi = s + 1 + cut;
+                    const int x0 = lo < 0 ? -lo : 0;
+                    lo = lo < 0 ? 0 : lo;
+                    hi = hi > Lq - 1 ? Lq - 1 : hi;
+                    const uint64_t window = ~0ull >> (63 - (hi - lo));
+                    const int wi = lo >> 5, sh = lo & 31;
+                    Real p[kAcc];
+#pragma unroll
+                    for (int i = 0; i < kAcc; ++i) p[i] = (Real)0;
+                    for (int k = 0; k < n_nbr; ++k) {
+                        const int off = rfl((int)g.nbr_off[k]);
+                        const Real *dk = diff + rfl((int)g.nbr_dist[k]) * (2 * cut + 2) + x0 + gl;
+                        const uint32_t *words = rail_words(row + off) + wi;
+                        const uint64_t w01 = (uint64_t)words[0] | ((uint64_t)words[1] << 32);
+                        uint64_t bitsw = (w01 >> sh) | (((uint64_t)words[2] << 32) << (32 - sh));
+                        bitsw &= window;
+                        if (off == 0) bitsw &= ~(3ull << (s - lo));
+                        bitsw >>= gl;
+#pragma unroll
+                        for (int i = 0; i < kAcc; ++i)
+                            if (kGroup * i < 2 * cut + 2) p[i] += (bitsw >> (kGroup * i)) & 1u ? dk[kGroup * i] : (Real)0;
+                    }
+#pragma unroll
+                    for (int i = kAcc / 2; i >= 1; i /= 2)
+#pragma unroll
+                        for (int j = 0; j < i; ++j) p[j] += p[j + i];
+                    Real part = p[0];
+#pragma unroll
+                    for (int sh_ = kGroup / 2; sh_ >= 1; sh_ >>= 1) part += __shfl_xor(part, sh_, 64);
+                    // (used by every lane, so that no wait for it is left to
+                    // the half-steps that follow)
+                    asm volatile("" : "+v"(ea));
+                    bool acc = false;
+                    if (have && gl == 0)
+                        acc = decide(down ? -part : part, ea, e.word, row, s, down ? s + 1 : s, down ? s : s + 1);
+                    uint64_t hops = __ballot(acc);
+                    while (hops) {
+                        const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)e.at, __builtin_ctzll(hops));
+                        hops &= hops - 1;
+                        flip((int)(at >> 16), (int)(at & 0x7FFFu));
+                    }
+                }
+                wave_sync();
+            }
+        } else {
+            // windows wider than a wavefront: one survivor at a time
+            const int n_kt = (mq + 1) * (cut + 1);
             const Real *kt = n_kt <= kLdsTableMax ? reinterpret_cast<const Real *>(smem)
                                                   : (std::is_same<Real, double>::value
                                                          ? reinterpret_cast<const Real *>(ka->ktab64)
                                                          : reinterpret_cast<const Real *>(ka->ktab32));
-            auto bit_at = [&](int r, int site) -> uint32_t {
-                return (wr.snap[r * lprq + site / SPL] >> (site % SPL)) & 1u;
-            };
-            wr.snap[lane] = bits;
-            bool ok = true;
-            if (!isolated) ok = fetch_bands(ka, wr, js_now());
-            wave_sync();
-            if (!ok) return false;
-            uint32_t fl = 0;
             uint64_t rest = any;
             while (rest) {
                 const int l = __builtin_ctzll(rest);
                 rest &= rest - 1;
-                uint32_t svl = (uint32_t)__builtin_amdgcn_readlane((int)sv, l);
+                Bits svl = (Bits)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)sv, l);
+                if constexpr (SPL == 64) svl |= (Bits)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(sv >> 32), l) << 32;
                 const int ls0 = __builtin_amdgcn_readlane(s0, l);
-                const int lrow = __builtin_amdgcn_readlane(cls_base, l) / rfl(g.P);
+                const int lrow = wr.row_of[l];
                 while (svl) {
-                    const int b = __builtin_ctz(svl);
+                    const int b = SPL == 64 ? __builtin_ctzll(svl) : __builtin_ctz((uint32_t)svl);
                     svl &= svl - 1;
                     const int s = ls0 + b;
-                    const uint32_t word = (uint32_t)__builtin_amdgcn_readlane((int)pick_word<0>(wd, b >> 1), l);
-                    const int o = bit_at(lrow, s) ? s : s + 1;
+                    const uint32_t word = word_at(s, (uint32_t)(r0 + lrow));
+                    const uint32_t *own_row = wr.snap + lrow * w32;
+                    const int o = (own_row[s >> 5] >> (s & 31)) & 1u ? s : s + 1;
                     const int t = (o == s) ? s + 1 : s;
                     int lo = s - cut, hi = s + 1 + cut;
                     lo = lo < 0 ? 0 : lo;
@@ -581,17 +743,9 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
                     for (int k = 0; k < n_nbr; ++k) {
                         const int off = rfl((int)g.nbr_off[k]);
                         const Real *ktr = kt + rfl((int)g.nbr_dist[k]) * (cut + 1);
-                        int rho = lrow + off, band = -1;
-                        if (single) {
-                            while (rho < 0) rho += Rq;
-                            while (rho >= Rq) rho -= Rq;
-                        } else if (rho < 0) {
-                            band = rho + mq;
-                        } else if (rho >= nrq) {
-                            band = mq + rho - nrq;
-                        }
+                        const uint32_t *words = rail_words(lrow + off);
                         for (int jj = lo + lane; jj <= hi; jj += 64) {
-                            uint32_t bit = band < 0 ? bit_at(rho, jj) : (wr.band[band * w32 + (jj >> 5)] >> (jj & 31)) & 1u;
+                            uint32_t bit = (words[jj >> 5] >> (jj & 31)) & 1u;
                             if (off == 0 && (jj == o || jj == t)) bit = 0;
                             const int dt_ = t - jj < 0 ? jj - t : t - jj;
                             const int do_ = o - jj < 0 ? jj - o : o - jj;
@@ -603,54 +757,17 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
 #pragma unroll
                     for (int sh_ = 32; sh_ >= 1; sh_ >>= 1) part += __shfl_xor(part, sh_, 64);
                     int acc = 0;
-                    if (lane == 0) {
-                        const Real alpha_r = (Real)ka->alpha, beta_r = (Real)ka->beta, c0_r = (Real)ka->c0;
-                        const Real e_app = ((alpha_r * (Real)wr.step_v[kw]) * (Real)(t - o)) / (Real)Lq;
-                        const int srail = r0 + lrow;
-                        const Real ea = ka->ea ? reinterpret_cast<const Real *>(ka->ea)[rfl(g.dv_off) + (int64_t)srail * Lq + o]
-                                               : (Real)ka->ea_scalar;
-                        HopArgs::LogBuf log;
-                        log.count = ka->log.count;
-                        log.entries = ka->log.entries;
-                        log.cap = ka->log.cap;
-                        acc = decide_hop<Real>(e_app + part, ea, word, beta_r, c0_r, log, dd, h, n, srail, s);
-                        if (acc) {
-                            HopRecord rec;
-                            rec.buf = ka->record.buf;
-                            rec.count = ka->record.count;
-                            rec.cap = ka->record.cap;
-                            rec.n0 = ka->record.n0;
-                            rec.n_hs = ka->record.n_hs;
-                            record_hop(rec, dd, h, n, srail, s, o == s ? 0 : 1);
-                            const int64_t base = (n - rfl(g.tally_base)) * ka->n_devices + dd;
-                            atomicAdd(&ka->tally_net[base], t < o ? 1 : -1);
-                            const int qo = (10 * o) / Lq, qt = (10 * t) / Lq;
-                            if (qo != qt) {
-                                atomicAdd(&ka->tally_dec[base * kDeciles + qo], -1);
-                                atomicAdd(&ka->tally_dec[base * kDeciles + qt], 1);
-                            }
-                        }
-                    }
+                    if (lane == 0) acc = decide(part, barrier_of(lrow, o), word, lrow, s, o, t);
                     acc = __builtin_amdgcn_readfirstlane(acc);
-                    if (acc) {
-                        if (lane == lrow * lprq + s / SPL) fl ^= 1u << (s % SPL);
-                        if (lane == lrow * lprq + (s + 1) / SPL) fl ^= 1u << ((s + 1) % SPL);
-                        if (lrow < mq || lrow >= nrq - mq) edge_changed = true;
-                    }
+                    if (acc) flip(lrow, s);
                 }
             }
-            bits ^= fl;
-            nbit = __shfl_down(bits, 1, 64) & 1u;
-            bx = bits | (nbit << 16);
         }
-
-        // publish the new state js + 1
-        ++pub_at;
-        ++tag_j;
+        bits ^= fl;
+        nbit = __shfl_down((uint32_t)bits, 1, 64) & 1u;
+        bx = (uint32_t)bits | (nbit << 16);
         if (edge_changed && !isolated) {
             const uint32_t jn = (uint32_t)js_now() + 1u;
-            const KArgs ka = kargs();
-            WaveLds<SPL> &wr = *lds_opaque(&w);
             const int sc = rfl(snap_count) + 1;
             snap_count = sc;
             const int slot = sc % kSnapSlots;
@@ -669,6 +786,69 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
             if (lane == 0) wr.snap_state[slot] = (int16_t)jn;
             snap_word = ((uint32_t)slot << 12) | jn;
         }
+        return true;
+    };
+
+    // One half-step of parity h (a compile-time constant): state js = 2 kstep
+    // + h to js + 1 (the first state of a launch is even).  False when a wait
+    // for a neighbour failed.
+    auto half_step = [&](auto h_c, const int kstep, const PhStep<kNB> &ps) __attribute__((always_inline)) -> bool {
+        constexpr int h = decltype(h_c)::value;
+        const int kw = kstep & (kWaveWin - 1);
+
+        // candidates: bonds of parity h whose two sites differ
+        // (the site after bond b: bit b + 1, or the next lane's first site)
+        const Bits after = SPL == 64   ? (bits >> 1) | ((Bits)nbit << (SPL - 1))
+                           : SPL == 32 ? (Bits)__builtin_amdgcn_alignbit(nbit, (uint32_t)bits, 1)
+                                       : (Bits)(bx >> 1);
+        const Bits cand = (bits ^ after) & (h ? valid_o : valid_e);
+
+        // Philox words (the key is read from the kernel arguments each
+        // half-step, a scalar load, rather than held in scalar registers)
+        uint32_t wd[kW];
+        {
+            const KArgs ka = kargs();
+            ph_words<h>(wd, phl, ps, ka->key0, ka->key1);
+        }
+        // stage 0: the smallest word against the bound of the lane's lowest
+        // class; stage 1 (rare): each candidate's word against its origin's
+        // exact class threshold
+        const uint32_t thr0 = (uint32_t)__builtin_amdgcn_readlane((int)thr_lane, kw);
+        const uint32_t t_lane = __builtin_elementwise_add_sat(__umulhi(thr0, r_lane), t_add);
+        const uint32_t mn = min_word<0>(wd);
+        // the common path decides with one wavefront vote that no lane has a
+        // stage-0 word; everything rare is nested in that one branch, so that no
+        // value of it (the survivors' vote, the changed edge) is merged, spilled
+        // or tested on the common path
+        const bool stage1 = mn <= t_lane && cand != 0u;
+        if (__builtin_expect(__ballot(stage1) != 0, 0)) {
+            Bits sv = 0;
+            uint32_t w_low = 0;  // the word of the lane's lowest survivor
+            if (stage1) {
+                const double c0 = kargs()->c0;
+                WaveLds<Real, SPL> &wr = *lds_opaque(&w);
+                const double g_step = wr.step_g[kw];
+                Bits c = cand;
+                while (c) {
+                    const int b = SPL == 64 ? __builtin_ctzll(c) : __builtin_ctz((uint32_t)c);
+                    c &= c - 1;
+                    const uint32_t x = pick_word<0>(wd, b >> 1);
+                    if (x <= t_lane) {
+                        const int o = s0 + (((bits >> b) & 1u) ? b : b + 1);
+                        if (x <= threshold_of(c0, wr.cls_a[wr.cls[cls_base + o]], g_step)) {
+                            w_low = sv ? w_low : x;
+                            sv |= (Bits)1 << b;
+                        }
+                    }
+                }
+            }
+            const uint64_t any = __ballot(sv != 0u);
+            if (any && !survivors(h_c, kstep, sv, w_low, any)) return false;
+        }
+
+        // publish the new state js + 1
+        ++pub_at;
+        ++tag_j;
         if (lane == 0)
             __hip_atomic_store(pub_at, ((uint64_t)tag_j << 32) | snap_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return true;
@@ -722,7 +902,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
 #pragma unroll
             for (int c = 0; c < SPL / 16; ++c) {
                 if (c == 0 || s0 + 16 * c < P) {
-                    const uint32_t b16 = (bits >> (16 * c)) & 0xFFFFu;
+                    const uint32_t b16 = (uint32_t)(bits >> (16 * c)) & 0xFFFFu;
                     const uint4 cv = *reinterpret_cast<const uint4 *>(w.cls + cls_base + s0 + 16 * c);
                     uint4 o;
                     o.x = ((b16 >> 0) & 0xFu) * 0x00204081u & 0x01010101u;
@@ -785,17 +965,24 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG) void hop_wave(PArgs a) {
 
 namespace {
 const void *wave_fn(int spl, bool fp64) {
+    if (spl == 64) return fp64 ? (const void *)hop_wave<double, 64> : (const void *)hop_wave<float, 64>;
     if (spl == 32) return fp64 ? (const void *)hop_wave<double, 32> : (const void *)hop_wave<float, 32>;
     return fp64 ? (const void *)hop_wave<double, 16> : (const void *)hop_wave<float, 16>;
 }
+template <typename Real>
+size_t wave_tile_lds(int spl) {
+    return spl == 64 ? sizeof(WaveLds<Real, 64>) : (spl == 32 ? sizeof(WaveLds<Real, 32>) : sizeof(WaveLds<Real, 16>));
+}
 }  // namespace
 
-size_t wave_lds_bytes(int spl, int n_kt, bool fp64) {
-    const size_t kt = n_kt <= kLdsTableMax ? ((size_t)n_kt * (fp64 ? sizeof(double) : sizeof(float)) + 15) & ~(size_t)15 : 0;
-    return kt + kWaveTilesPerWG * (spl == 32 ? sizeof(WaveLds<32>) : sizeof(WaveLds<16>));
+size_t wave_lds_bytes(int spl, int rail_range, int cut, bool fp64) {
+    const size_t real = fp64 ? sizeof(double) : sizeof(float);
+    return wave_table_bytes(rail_range, cut, real) + kWaveTilesPerWG * (fp64 ? wave_tile_lds<double>(spl) : wave_tile_lds<float>(spl));
 }
 
-int wave_band_words(int spl) { return spl == 32 ? WaveLds<32>::kBand : WaveLds<16>::kBand; }
+int wave_band_words(int spl) {
+    return spl == 64 ? WaveLds<float, 64>::kBand : (spl == 32 ? WaveLds<float, 32>::kBand : WaveLds<float, 16>::kBand);
+}
 
 hipError_t launch_wave(const PArgs &a, int spl, size_t lds, bool fp64, hipStream_t st) {
     PArgs args = a;
