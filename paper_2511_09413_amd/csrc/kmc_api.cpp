@@ -15,6 +15,7 @@
 #include <string>
 #include <vector>
 
+#include "kmc_draws.h"
 #include "kmc_internal.h"
 #include "kmc_electrode.h"
 #include "kmc_phifix.h"
@@ -82,6 +83,7 @@ struct Layout {
     size_t occ_a, occ_b, devs, tiles, knot_t, knot_v, ktab64, ktab32, ctl, tally_net, tally_dec, dec_run,
         net_total, log_count, log_entries, scratch, rail_dev, rail_idx, n_ions, ptiles, pub, status,
         rp_a, rp_b, score_log, rec, hops, hop_ctl, phi, ktiles, dtiles, ctiles, ticket, phifix, kfix, electrodes, rtiles, total;
+    size_t dr_lists, dr_hops, dr_cnt, dr_thr, dr_volt, dr_ktiles, phifix_b;  // half-steps by low draws
     int64_t max_ptiles, pub_stride;  // persistent kernel: tiles per launch (ring slots), words per ring
     int64_t max_wtiles, wpub_stride;  // wave kernel: tiles per launch, publication words per tile
     size_t wtiles;                    // wave tiling (PTile array)
@@ -89,6 +91,8 @@ struct Layout {
     int64_t total_sites, total_pad, rails_total;
     int cut;     // interaction table cutoff actually stored
     int64_t hop_cap;  // score replay: entries of the accepted-hop list
+    int64_t dr_hop_cap;  // low draws: accepted hops per half-step
+    int dr_steps;     // steps of one threshold table
     int dense_nb;  // dense potential: 32-site blocks per rail (0 when not used)
 };
 
@@ -267,6 +271,20 @@ Layout layout_for(const kmc_params *p) {
         L.kfix = take(sizeof(int64_t) * (m + 1) * (L.cut + 1));
         L.ctiles = take(sizeof(Tile) * (size_t)rails);
     }
+    if (p->precision == KMC_BF16X2 || p->precision == KMC_PHI_FIXED) {
+        // half-steps driven by low draws: thresholds and biases of a run of
+        // steps, accepted hops of four half-steps, draws of two
+        const bool dense = p->precision == KMC_BF16X2;
+        L.dr_steps = (int)std::min<int64_t>(std::max<int64_t>(kDrawTableEntries / D, 1), kDrawMaxSteps);
+        L.dr_hop_cap = std::max<int64_t>(L.total_sites / 64, 4096);
+        L.dr_thr = take(sizeof(uint32_t) * (size_t)(L.dr_steps + 1) * D);
+        L.dr_volt = take(sizeof(double) * (size_t)(L.dr_steps + 1) * D);
+        L.dr_hops = take(sizeof(uint4) * 4 * (size_t)L.dr_hop_cap);
+        L.dr_cnt = take(sizeof(uint32_t) * 4);
+        L.dr_lists = take(sizeof(uint4) * 2 * kDrawMaxGrid * kDrawSlots);
+        if (dense) L.dr_ktiles = take((size_t)16 * 256 * (m + 1) * (2 * L.dense_nb - 1));
+        else L.phifix_b = take(sizeof(int64_t) * (size_t)pad);
+    }
     L.total = off;
     return L;
 }
@@ -324,6 +342,14 @@ struct kmc_ctx {
     int64_t k10fix = 0;                // K(1, 0) in those units
     std::vector<Electrode> el;         // reservoirs per device (host copy of the workspace's)
     std::vector<Tile> rtiles;          // runs of rails of the streaming replay (empty: the tile replay)
+    // half-steps of the long-range paths driven by low draws
+    bool dr_ok = false;                // they can be used on this GPU
+    std::vector<double> vmax;          // largest |bias| of each device's protocol
+    int dr_rows = 0, dr_grid = 0;      // dense: survivors per product; workgroups per launch
+    size_t dr_lds = 0;
+    bool dr_stale = true, dr_fit = false;  // plan_draws is to run; its answer
+    int dr_per_bin = 1;                // resolving workgroups per column block
+    bool planes_equal = false;         // both state (and potential) planes hold the current state
     bool any_open = false;             // some device has open electrodes: half-step launches only
     // recording of accepted hops for the score replay (kmc_record_hops), in
     // the caller's buffer: per half-step counts, then a flag for the replay's
@@ -376,6 +402,15 @@ void neighbour_offsets(int R, int m, DevInfo &dv) {
         ++cnt;
     }
     dv.n_nbr = cnt;
+}
+
+// Compute units of the current GPU and LDS bytes of one (attributes: the whole
+// property structure costs a millisecond to fill).
+bool gpu_limits(int *cus, int *lds_per_cu) {
+    int dev = 0;
+    return hipGetDevice(&dev) == hipSuccess &&
+           hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+           hipDeviceGetAttribute(lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) == hipSuccess;
 }
 
 // Tiles of whole rails, about kTileSites padded sites each.
@@ -444,14 +479,13 @@ void make_ptiles(kmc_ctx *c) {
     c->pgroups.clear();
     // one lane per 16-site chunk: a tile holds at most kPMaxBlock chunks
     if (max_chunks > kPMaxBlock || lds > 160 * 1024) return;
-    int per_cu = 0, dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return;
+    int per_cu = 0, cus = 0, lds_per_cu = 0;
+    if (!gpu_limits(&cus, &lds_per_cu)) return;
     if (persistent_capacity(c->p_block, lds, c->fp64, &per_cu) != hipSuccess) return;
     // Devices are independent: a lattice larger than what is co-resident runs
     // as a sequence of launches over groups of whole devices, each group small
     // enough to be co-resident (and within the ring slots).
-    int64_t cap = std::min<int64_t>((int64_t)per_cu * prop.multiProcessorCount, c->lay.max_ptiles);
+    int64_t cap = std::min<int64_t>((int64_t)per_cu * cus, c->lay.max_ptiles);
     if (c->group_limit > 0) cap = std::min<int64_t>(cap, c->group_limit);
     if (cap < 1) return;
     int first = 0, count = 0;
@@ -531,9 +565,8 @@ void make_wtiles(kmc_ctx *c) {
         return;
     }
     c->w_spl = spl;
-    int per_cu = 0, dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return;
+    int per_cu = 0, cus = 0, lds_per_cu = 0;
+    if (!gpu_limits(&cus, &lds_per_cu)) return;
     // Every workgroup asks for a quarter of the CU's LDS, so that a CU holds
     // at most four (one wavefront per SIMD each; a half and two with 64 sites
     // per lane).  A launch of exactly four
@@ -542,10 +575,10 @@ void make_wtiles(kmc_ctx *c) {
     // workgroups on some CUs and three on others, and the tiles of the fuller
     // SIMDs set the launch's time.
     c->w_lds = std::max(wave_lds_bytes(spl, c->p.rail_range, c->lay.cut, c->fp64),
-                        (size_t)prop.maxSharedMemoryPerMultiProcessor / (spl == 64 ? 2 : 4));
+                        (size_t)lds_per_cu / (spl == 64 ? 2 : 4));
     if (wave_capacity(spl, c->w_lds, c->fp64, &per_cu) != hipSuccess) return;
     // groups of whole devices, each co-resident (and within the publication memory)
-    int64_t cap = std::min<int64_t>((int64_t)per_cu * prop.multiProcessorCount * kWaveTilesPerWG, c->lay.max_wtiles);
+    int64_t cap = std::min<int64_t>((int64_t)per_cu * cus * kWaveTilesPerWG, c->lay.max_wtiles);
     if (c->group_limit > 0) cap = std::min<int64_t>(cap, c->group_limit);
     if (cap < 1) return;
     int first = 0, count = 0;
@@ -704,6 +737,139 @@ bool wave_finishes(int d0, int d1, int steps) {
     return series <= 64 && (int64_t)series * steps <= 4096;
 }
 
+// Whether the half-steps of a long-range context go by low draws, and with
+// how many resolving workgroups per column block: when few words are expected
+// to pass stage 0, from every device's bound at its largest bias.  Such a
+// half-step costs 10 us (fixed) to 20 us (dense) while its draws fit half the
+// GPU's workgroups, and then grows with draws x accepted hops; the other forms
+// cost 8.2 us (dense) and 0.8 us (fixed) per 10^6 sites and two launches: at
+// 3.4e7 sites and 0.3 eV (1900 draws) 22 us per half-step against 280 (dense)
+// and 16 against 26 (fixed).  The lists hold
+// 511 draws per generating and 256 per resolving workgroup, and are used up to
+// means of 256 and 128; a list that is too short all the same raises the
+// status flag.
+void plan_draws(kmc_ctx *c) {
+    c->dr_stale = false;
+    c->dr_fit = false;
+    if (!c->dr_ok) return;
+    const double beta = 1.0 / c->p.kT_ev, c0 = c->p.nu0_hz * c->p.dt_s;
+    std::vector<double> rail_mean(c->p.n_devices);  // draws of one rail
+    double mean = 0.0;
+    for (int d = 0; d < c->p.n_devices; ++d) {
+        const DevInfo &dv = c->devs[d];
+        const double field = std::fabs(c->p.field_coupling) * c->vmax[d] / (double)dv.sites;
+        const double pb = c0 * std::exp(-beta * (dv.ea_min - 0.5 * (field + dv.coul_bound))) * (1.0 + 1e-3) + 2e-6;
+        rail_mean[d] = std::min(pb, 1.0) * 0.5 * (double)dv.sites;
+        mean += rail_mean[d] * (double)dv.rails;
+    }
+    if (!(mean <= std::min(kDrawMaxMean, (double)c->lay.total_sites / 128.0))) return;
+    // resolving workgroups: about 48 draws each (20 survivors), half the grid at most
+    const int bins = c->dense ? c->lay.dense_nb : 1;
+    c->dr_per_bin = std::max(1, std::min((int)std::ceil(mean / (48.0 * bins)), c->dr_grid / 2 / bins));
+    const int resolvers = bins * c->dr_per_bin, gens = c->dr_grid - resolvers;
+    std::vector<double> list(gens, 0.0), take(c->dr_per_bin, 0.0);
+    for (int i = 0, d = 0; i < gens; ++i) {
+        const int64_t from = draw_share(c->lay.rails_total, i, gens), to = draw_share(c->lay.rails_total, i + 1, gens);
+        for (; d < c->p.n_devices; ++d) {
+            const int64_t lo = std::max(from, c->devs[d].row0), hi = std::min<int64_t>(to, c->devs[d].row0 + c->devs[d].rails);
+            if (hi > lo) list[i] += rail_mean[d] * (double)(hi - lo);
+            if (c->devs[d].row0 + c->devs[d].rails > to) break;
+        }
+        if (list[i] > 256.0) return;
+        take[(resolvers + i) % c->dr_per_bin] += list[i] / bins;
+    }
+    for (double x : take)
+        if (x > 128.0) return;
+    c->dr_fit = true;
+}
+
+// The chunk's half-steps by low draws; done steps of the call's n_steps are
+// enqueued already.
+kmc_status enqueue_draws(kmc_ctx *c, const HopArgs &h, const Ctl &ctl, int64_t done, int64_t n_steps, int chunk) {
+    const Layout &L = c->lay;
+    DrawArgs a{};
+    a.devs = h.devs;
+    a.rail_dev = c->at<int32_t>(L.rail_dev);
+    a.rails_total = L.rails_total;
+    a.n_devices = c->p.n_devices;
+    a.thr = c->at<uint32_t>(L.dr_thr);
+    a.volt = c->at<double>(L.dr_volt);
+    a.beta = h.beta;
+    a.c0 = h.c0;
+    a.alpha = h.alpha;
+    a.ea_scalar = h.ea_scalar;
+    a.ea = h.ea;
+    a.key0 = h.key0;
+    a.key1 = h.key1;
+    a.cutoff = h.cutoff;
+    a.rail_range = h.rail_range;
+    a.draws = c->at<uint4>(L.dr_lists);
+    a.hops = c->at<uint4>(L.dr_hops);
+    a.hop_cap = L.dr_hop_cap;
+    a.n_hops = c->at<uint32_t>(L.dr_cnt);
+    a.n_bins = c->dense ? L.dense_nb : 1;
+    a.per_bin = c->dr_per_bin;
+    a.status = c->at<int32_t>(L.status);
+    a.tally_net = h.tally_net;
+    a.tally_dec = h.tally_dec;
+    a.log = h.log;
+    a.nb = L.dense_nb;
+    a.rows = c->dr_rows;
+    a.pitch = c->devs[0].pitch;
+    a.sites = c->sites[0];
+    a.k10 = c->k10;
+    a.kfix = c->phifix ? c->at<int64_t>(L.kfix) : nullptr;
+    a.k10fix = c->k10fix;
+    a.frac_bits = c->frac_bits;
+    int8_t *planes[2] = {c->cur, c->nxt};
+    int64_t *phis[2] = {nullptr, nullptr};
+    if (c->phifix) {
+        phis[0] = c->at<int64_t>(L.phifix);
+        phis[1] = c->at<int64_t>(L.phifix_b);
+    }
+    auto table = [&](int64_t n, bool clear) {
+        return launch_draw_table(c->at<uint32_t>(L.dr_thr), c->at<double>(L.dr_volt), h.devs, c->p.n_devices, h.knot_t,
+                                 h.knot_v, n, L.dr_steps + 1, h.dt, h.beta, h.c0, h.alpha,
+                                 clear ? a.n_hops : nullptr, c->stream);
+    };
+    if (done == 0) {
+        if (!c->planes_equal) {
+            KMC_HIP(c, launch_copy_bytes(planes[0], planes[1], (size_t)L.total_pad, c->stream));
+            if (c->phifix) KMC_HIP(c, launch_copy_bytes(phis[0], phis[1], sizeof(int64_t) * (size_t)L.total_pad, c->stream));
+        }
+        c->planes_equal = false;  // until the call's last hops have settled
+        // the first half-step's draws
+        KMC_HIP(c, table(ctl.n_base, true));
+        a.generate = 1;
+        a.n = ctl.n_base;
+        KMC_HIP(c, launch_draws(a, c->dense, 1, c->dr_grid, c->dr_lds, c->stream));
+    }
+    a.resolve = 1;
+    for (int k = 0; k < chunk; ++k) {
+        const int64_t step = done + k;
+        a.k = (int32_t)(step % L.dr_steps);
+        if (a.k == 0 && step > 0) KMC_HIP(c, table(ctl.n_base + k, false));
+        a.n = ctl.n_base + k;
+        a.tally_row = k;
+        for (int hh = 0; hh < 2; ++hh) {
+            a.launch = 2 * step + hh;
+            a.generate = step + 1 < n_steps || hh == 0 ? 1 : 0;
+            a.plane = planes[a.launch & 1];
+            a.other = planes[(a.launch & 1) ^ 1];
+            a.phi = phis[a.launch & 1];
+            a.phi_other = phis[(a.launch & 1) ^ 1];
+            a.ktiles = c->dense ? c->ws + (hh ? L.dr_ktiles : L.ktiles) : nullptr;
+            KMC_HIP(c, launch_draws(a, c->dense, hh, c->dr_grid, c->dr_lds, c->stream));
+        }
+    }
+    if (done + chunk == n_steps) {
+        a.launch = 2 * n_steps;
+        KMC_HIP(c, launch_draw_settle(a, c->dense, c->stream));
+        c->planes_equal = true;
+    }
+    return KMC_OK;
+}
+
 // Enqueue n_steps steps.  Returns in *exported whether the launches already
 // wrote the caller's occupancy (the wave kernel does).
 kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t *dec_out, bool *exported) {
@@ -759,9 +925,12 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
         a.record = r;
         pa.record = r;
     }
+    if (c->dr_stale) plan_draws(c);
+    const bool draws = c->dr_fit;
+    kmc_status s = KMC_OK;
     // the fixed-point path's hop counts start at zero (a score replay in
     // between leaves its own there)
-    if (c->phifix) KMC_HIP(c, launch_zero_i64(c->at<int64_t>(c->lay.hop_ctl), 2, c->stream));
+    if (c->phifix && !draws) KMC_HIP(c, launch_zero_i64(c->at<int64_t>(c->lay.hop_ctl), 2, c->stream));
     int64_t done = 0;
     while (done < n_steps) {
         const int chunk = (int)std::min<int64_t>(kTallySteps, n_steps - done);
@@ -806,7 +975,12 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
                 }
             }
         }
-        for (int k = 0; k < chunk && !persistent; ++k) {
+        if (draws) {
+            s = enqueue_draws(c, a, ctl, done, n_steps, chunk);
+            if (s != KMC_OK) return s;
+        }
+        for (int k = 0; k < chunk && !persistent && !draws; ++k) {
+            c->planes_equal = false;
             for (int h = 0; h < 2; ++h) {
                 a.occ_in = c->cur;
                 a.occ_out = c->nxt;
@@ -853,13 +1027,15 @@ kmc_status check_status(kmc_ctx *c) {
     KMC_HIP(c, hipStreamSynchronize(c->stream));
     if (st != 0) {
         c->poisoned = true;
-        return fail(KMC_EHIP, "persistent hop kernel: a neighbour wait timed out; state is invalid");
+        return fail(KMC_EHIP, st == 2 ? "low-draw half-steps: a list overflowed; state is invalid"
+                                      : "persistent hop kernel: a neighbour wait timed out; state is invalid");
     }
     return KMC_OK;
 }
 
 kmc_status after_state_change(kmc_ctx *c) {
     c->rec_on = false;  // a recording describes the trajectory from its own start state
+    c->planes_equal = false;
     if (c->phifix) KMC_HIP(c, launch_phifix_update(phifix_args(c, c->cur, true, 0), c->stream));
     KMC_HIP(c, launch_count_deciles(c->cur, c->at<DevInfo>(c->lay.devs), c->p.n_devices,
                                     c->at<int64_t>(c->lay.dec_run), c->stream));
@@ -931,6 +1107,17 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
         double bound = std::fabs(kernel64(params, 1, 0));
         for (int k = 0; k < dv.n_nbr; ++k)
             if (dv.nbr_dist[k] > 0) bound += std::fabs(kernel64(params, 0, dv.nbr_dist[k]));
+        if (params->precision == KMC_BF16X2) {
+            // the dense potential's own error at either site (its kernel split
+            // and its binary32 sums, of at most n products bounded by the sum of
+            // |K| over the whole window), and the binary32 roundings of dE
+            const int reach = std::min(lay.cut, dv.sites - 1);
+            double sum = 0.0;
+            for (int k = 0; k < dv.n_nbr; ++k)
+                for (int ds = -reach; ds <= reach; ++ds) sum += std::fabs(kernel64(params, ds, dv.nbr_dist[k]));
+            const double n = 2.0 * (params->rail_range + 1) * (32.0 * lay.dense_nb);
+            bound += 2.0 * (std::ldexp(1.0, -16) + n * std::ldexp(1.0, -24)) * sum + std::ldexp(sum + bound, -20);
+        }
         dv.coul_bound = bound;
         off += (int64_t)dv.rails * dv.sites;
         off_pad += (int64_t)dv.rails * dv.pitch;
@@ -1013,7 +1200,7 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
                 c->rtiles.push_back(Tile{d, r0, std::min(run, c->rails[d] - r0), 0});
         }
     }
-    std::vector<uint16_t> kt_host;
+    std::vector<uint16_t> kt_host, kt_shifted;
     if (c->dense) {
         auto bf16_rne = [](float f) {
             uint32_t u;
@@ -1028,27 +1215,57 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
             return (double)f;
         };
         const int nb = lay.dense_nb, nd = 2 * nb - 1;
-        kt_host.assign((size_t)(m + 1) * nd * 256 * 8, 0);
+        // column blocks starting at multiples of 32, and (low draws of the odd
+        // parity) one site later.  K is split once per distance, in the order of
+        // decreasing ds, so that a lane's eight values are consecutive
+        const int reach = 32 * nb + 1;
+        std::vector<uint16_t> hi((size_t)(m + 1) * (2 * reach + 1)), lo(hi.size());
         for (int dd = 0; dd <= m; ++dd)
-            for (int di = 0; di < nd; ++di)
-                for (int q = 0; q < 2; ++q)
-                    for (int l = 0; l < 64; ++l)
-                        for (int e = 0; e < 8; ++e) {
+            for (int x = 0; x <= reach; ++x) {
+                const double k = kernel64(params, x, dd);
+                const size_t mid = (size_t)dd * (2 * reach + 1) + reach;
+                hi[mid - x] = hi[mid + x] = bf16_rne((float)k);
+                lo[mid - x] = lo[mid + x] = bf16_rne((float)(k - bf16_val(hi[mid + x])));
+            }
+        for (int shift = 0; shift < 2; ++shift) {
+            std::vector<uint16_t> &kt = shift ? kt_shifted : kt_host;
+            kt.assign((size_t)(m + 1) * nd * 256 * 8, 0);
+            for (int dd = 0; dd <= m; ++dd)
+                for (int di = 0; di < nd; ++di)
+                    for (int q = 0; q < 2; ++q)
+                        for (int l = 0; l < 64; ++l) {
                             const int delta = di - (nb - 1);
-                            const int ds = -32 * delta + (l % 32) - 16 * q - 8 * (l / 32) - e;
-                            const double k = kernel64(params, ds, dd);
-                            const uint16_t hi = bf16_rne((float)k);
-                            const uint16_t lo = bf16_rne((float)(k - bf16_val(hi)));
+                            const int ds = -32 * delta + shift + (l % 32) - 16 * q - 8 * (l / 32);  // of e = 0
+                            const size_t from = (size_t)dd * (2 * reach + 1) + reach - ds;
                             const size_t base = ((size_t)(dd * nd + di) * 2) * 2;
-                            kt_host[(((base + 0 * 2 + q) * 64) + l) * 8 + e] = hi;
-                            kt_host[(((base + 1 * 2 + q) * 64) + l) * 8 + e] = lo;
+                            std::memcpy(&kt[(((base + 0 * 2 + q) * 64) + l) * 8], &hi[from], 16);
+                            std::memcpy(&kt[(((base + 1 * 2 + q) * 64) + l) * 8], &lo[from], 16);
                         }
+        }
         const int per_wg = 256 / (c->devs[0].pitch / 8);  // rails of one decision workgroup
         for (int d = 0; d < D; ++d) {
             for (int r0 = 0; r0 < c->rails[d]; r0 += kDenseRails)
                 c->dtiles.push_back(Tile{d, r0, std::min(kDenseRails, c->rails[d] - r0), 0});
             for (int r0 = 0; r0 < c->rails[d]; r0 += per_wg)
                 c->ctiles.push_back(Tile{d, r0, std::min(per_wg, c->rails[d] - r0), 0});
+        }
+    }
+
+    // Half-steps by low draws (long-range paths): the launch shape (a workgroup
+    // per CU)
+    c->vmax.assign(D, 0.0);
+    if ((c->dense || c->phifix) && lay.rails_total < ((int64_t)1 << 28)) {
+        int cus = 0, lds = 0;
+        if (gpu_limits(&cus, &lds)) {
+            c->dr_grid = std::min(cus, kDrawMaxGrid);
+            c->dr_rows = 32;
+            c->dr_lds = draws_lds_bytes(c->dense, m, lay.dense_nb, c->dr_rows, cut);
+            if (c->dense && c->dr_lds > 100 * 1024) {
+                c->dr_rows = 16;
+                c->dr_lds = draws_lds_bytes(true, m, lay.dense_nb, c->dr_rows, cut);
+            }
+            // the kernels' own static LDS is below 40 KiB
+            c->dr_ok = c->dr_lds <= 120 * 1024 && c->dr_grid >= 2 * std::max(lay.dense_nb, 32);
         }
     }
 
@@ -1081,6 +1298,8 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
         chk(h2d(lay.ctiles, c->ctiles.data(), sizeof(Tile) * c->ctiles.size()), "copy decision tiles");
         chk(set_dense_lds_limit((size_t)(kDenseRails + 2 * m) * (lay.dense_nb * 32 + 8)), "LDS limit of the dense kernel");
     }
+    if (c->dense) chk(h2d(lay.dr_ktiles, kt_shifted.data(), sizeof(uint16_t) * kt_shifted.size()), "copy kernel blocks");
+    if (c->dr_ok) chk(set_draws_lds_limit(c->dense, c->dr_lds), "LDS limit of the low-draw kernels");
     if (!c->rtiles.empty()) chk(h2d(lay.rtiles, c->rtiles.data(), sizeof(Tile) * c->rtiles.size()), "copy replay runs");
     if (c->phifix) {
         chk(h2d(lay.kfix, kfix_host.data(), sizeof(int64_t) * kfix_host.size()), "copy fixed-point kernel table");
@@ -1111,6 +1330,13 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
         chk(launch_barrier_range(ea_dev, c->fp64, c->at<DevInfo>(lay.devs), D,
                                  c->at<unsigned long long>(lay.scratch), st),
             "barrier range");
+    if (ea_dev && c->dr_ok) {
+        // the lowest barriers, for the choice of low-draw half-steps
+        std::vector<DevInfo> back(D);
+        chk(hipMemcpyAsync(back.data(), c->ws + lay.devs, sizeof(DevInfo) * D, hipMemcpyDeviceToHost, st), "read barrier ranges");
+        chk(hipStreamSynchronize(st), "read barrier ranges");
+        for (int d = 0; d < D; ++d) c->devs[d].ea_min = back[d].ea_min;
+    }
     chk(launch_import(occ_dev, c->cur, c->at<DevInfo>(lay.devs), D, lay.total_pad, ea_dev, c->fp64, st),
         "import occupancy");
     if (ok == KMC_OK) ok = after_state_change(c);
@@ -1164,6 +1390,10 @@ kmc_status kmc_set_bias_protocol(kmc_ctx *c, int32_t device, const double *t_s, 
     }
     const int d0 = device < 0 ? 0 : device, d1 = device < 0 ? c->p.n_devices : device + 1;
     c->rec_on = false;  // the replay evaluates every step under the installed protocols
+    double peak = 0.0;
+    for (int i = 0; i < n_knots; ++i) peak = std::max(peak, std::fabs(v_volt[i]));
+    for (int d = d0; d < d1; ++d) c->vmax[d] = peak;
+    c->dr_stale = true;
     KMC_HIP(c, launch_set_protocol(c->at<double>(c->lay.knot_t), c->at<double>(c->lay.knot_v),
                                    c->at<DevInfo>(c->lay.devs), d0, d1, n_knots, c->n, t_s, v_volt, c->stream));
     return KMC_OK;
@@ -1340,6 +1570,7 @@ kmc_status save_state(kmc_ctx *c, Saved &sv) {
 kmc_status restore_state(kmc_ctx *c, const Saved &sv) {
     const int D = c->p.n_devices;
     c->rec_on = false;  // the trial steps were recorded too
+    c->planes_equal = false;
     KMC_HIP(c, hipMemcpyAsync(c->cur, c->ws + c->lay.rp_a, (size_t)c->lay.total_pad, hipMemcpyDeviceToDevice,
                               c->stream));
     KMC_HIP(c, hipMemcpyAsync(c->ws + c->lay.net_total, sv.net_total.data(), sizeof(int64_t) * D,

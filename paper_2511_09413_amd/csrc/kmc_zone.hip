@@ -34,6 +34,7 @@
 
 #include "kmc_device.h"
 #include "kmc_internal.h"
+#include "kmc_philox.h"
 
 namespace kmc {
 kmc_status record_error(kmc_status s, const std::string &msg);
@@ -44,6 +45,11 @@ namespace {
 using kmc::record_error;
 using kmc::kMaxKnots;
 using kmc::philox4x32_10;
+using kmc::philox_lane;
+using kmc::philox_step;
+using kmc::philox_words;
+using kmc::PhiloxLane;
+using kmc::PhiloxStep;
 using kmc::protocol_voltage;
 
 constexpr int kZoneMaxZones = 64;
@@ -369,51 +375,6 @@ struct ZoneLds {
     int32_t go;
 };
 
-struct ZoneStepConst {  // of one step: Philox values that do not depend on the rail
-    uint32_t s_y0;       // hi(M1 n) ^ k0
-    uint32_t lo2, hi2;   // round 2: M0 x0
-};
-struct ZoneLaneConst {  // of one lane
-    uint32_t r1_lo_k;    // lo(M1 x2) of round 0's output ^ k0 + 2 W0
-    uint32_t r1_hi_k;    // hi(M1 x2) ^ k0 + W0
-    uint32_t y3_k;       // lo(M0 l) ^ k1 + W1
-};
-constexpr uint32_t kZM0 = 0xD2511F53u, kZM1 = 0xCD9E8D57u, kZW0 = 0x9E3779B9u, kZW1 = 0xBB67AE85u;
-
-__device__ __forceinline__ ZoneLaneConst zone_lane_const(uint32_t l, uint32_t k0, uint32_t k1) {
-    const uint64_t m0 = (uint64_t)kZM0 * l;
-    const uint64_t m1 = (uint64_t)kZM1 * ((uint32_t)(m0 >> 32) ^ (2u << 1) ^ k1);
-    return {(uint32_t)m1 ^ (k0 + 2u * kZW0), (uint32_t)(m1 >> 32) ^ (k0 + kZW0), (uint32_t)m0 ^ (k1 + kZW1)};
-}
-__device__ __forceinline__ ZoneStepConst zone_step_const(const ZoneLaneConst &c, uint32_t n, uint32_t k0, uint32_t k1) {
-    const uint64_t m1 = (uint64_t)kZM1 * n;
-    const uint64_t a2 = (uint64_t)kZM0 * (c.r1_hi_k ^ (uint32_t)m1);
-    return {(uint32_t)(m1 >> 32) ^ k0, (uint32_t)a2, (uint32_t)(a2 >> 32) ^ (k1 + 2u * kZW1)};
-}
-// The words of philox4x32_10(l, rail, n, 2 << 1, k0, k1).
-__device__ __forceinline__ uint4 zone_words(const ZoneLaneConst &c, const ZoneStepConst &s, uint32_t rail, uint32_t k0,
-                                            uint32_t k1) {
-    const uint64_t a1 = (uint64_t)kZM0 * (s.s_y0 ^ rail);
-    const uint64_t b2 = (uint64_t)kZM1 * ((uint32_t)(a1 >> 32) ^ c.y3_k);
-    uint32_t x0 = (uint32_t)(b2 >> 32) ^ c.r1_lo_k, x1 = (uint32_t)b2;
-    uint32_t x2 = s.hi2 ^ (uint32_t)a1, x3 = s.lo2;
-    uint32_t kr0 = k0 + 2u * kZW0, kr1 = k1 + 2u * kZW1;
-#pragma unroll
-    for (int round = 3; round < 10; ++round) {
-        kr0 += kZW0;
-        kr1 += kZW1;
-        const uint64_t m0 = (uint64_t)kZM0 * x0;
-        const uint64_t m1 = (uint64_t)kZM1 * x2;
-        const uint32_t y0 = kmc::xor3((uint32_t)(m1 >> 32), x1, kr0);
-        const uint32_t y2 = kmc::xor3((uint32_t)(m0 >> 32), x3, kr1);
-        x1 = (uint32_t)m1;
-        x3 = (uint32_t)m0;
-        x0 = y0;
-        x2 = y2;
-    }
-    return make_uint4(x0, x1, x2, x3);
-}
-
 constexpr uint64_t kFirstLanes = 0x0000000100000001ull, kLastLanes = 0x8000000080000000ull;
 
 // One step of a rail pair: lane l of each half holds ions 2l and 2l + 1 of its
@@ -585,7 +546,7 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
     const uint32_t rail0 = (uint32_t)(2 * pair0 + half);
     const int mine = (int)(pairs - pair0 < P ? (pairs - pair0 > 0 ? pairs - pair0 : 0) : P);  // pairs of this wavefront
     const int odd_at = (a.rails & 1) ? (int)(pairs - 1 - pair0 < P ? pairs - 1 - pair0 : P) : P;  // the pair without a second rail
-    const ZoneLaneConst lc = zone_lane_const((uint32_t)l, a.key0, a.key1);
+    const PhiloxLane lc = philox_lane((uint32_t)l, 2u << 1, a.key0, a.key1);
     for (int i = tid; i < 2 * kZoneAcc * (kZoneMaxZones + 1); i += blockDim.x) (&s.before[0][0])[i] = 0;  // each its own reader
     for (int k = 0; k < a.n_steps; ++k) {
         const int par = k & 1;
@@ -594,12 +555,12 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
         int mine_k = __builtin_amdgcn_readfirstlane(mine), odd_k = __builtin_amdgcn_readfirstlane(odd_at);
         asm volatile("" : "+v"(rail_k), "+s"(mine_k), "+s"(odd_k));
         const uint32_t key0 = zone_kargs()->key0, key1 = zone_kargs()->key1;
-        const ZoneStepConst sc = zone_step_const(lc, (uint32_t)zone_kargs()->n0 + (uint32_t)k, key0, key1);
+        const PhiloxStep sc = philox_step(lc, (uint32_t)zone_kargs()->n0 + (uint32_t)k, key0, key1);
         int net = 0;
 #pragma unroll
         for (int q = 0; q < P; ++q) {
             if (q < mine_k) {
-                const uint4 w = zone_words(lc, sc, rail_k + 2u * (uint32_t)q, key0, key1);
+                const uint4 w = philox_words(lc, sc, rail_k + 2u * (uint32_t)q, key0, key1);
                 const uint64_t v = q == odd_k ? 0xFFFFFFFFull : ~0ull;
                 net += zone_pair(x0[q], x1[q], z0[q], z1[q], w, has0 & v, has1 & v, wall, last_lane, &s.thr[0][0],
                                  s.dpop[par], zone_at);
@@ -674,10 +635,10 @@ __global__ __launch_bounds__(1024) void zone_rescue(ZoneRunArgs a) {
         zone_setup(a, s, zone_at);
         const int64_t pairs = ((int64_t)a.rails + 1) / 2;
         const uint32_t wall = (uint32_t)a.sites + 1u;
-        const ZoneLaneConst lc = zone_lane_const((uint32_t)l, a.key0, a.key1);
+        const PhiloxLane lc = philox_lane((uint32_t)l, 2u << 1, a.key0, a.key1);
             for (int k = 0; k < a.n_steps; ++k) {
             const int par = k & 1;
-            const ZoneStepConst sc = zone_step_const(lc, (uint32_t)(a.n0 + k), a.key0, a.key1);
+            const PhiloxStep sc = philox_step(lc, (uint32_t)(a.n0 + k), a.key0, a.key1);
             int net = 0;
             for (int64_t pr = wave; pr < pairs; pr += blockDim.x >> 6) {
                 const int64_t rail = 2 * pr + half;
@@ -685,7 +646,7 @@ __global__ __launch_bounds__(1024) void zone_rescue(ZoneRunArgs a) {
                 uint16_t *row = a.X + rail * a.ions;
                 uint32_t x0 = h0 ? row[j0] : wall, x1 = h1 ? row[j1] : wall;
                 uint32_t z0 = zone_at[x0], z1 = zone_at[x1];
-                const uint4 w = zone_words(lc, sc, (uint32_t)rail, a.key0, a.key1);
+                const uint4 w = philox_words(lc, sc, (uint32_t)rail, a.key0, a.key1);
                 net += zone_pair(x0, x1, z0, z1, w, __ballot(h0), __ballot(h1), wall, l == 31, &s.thr[0][0], s.dpop[par],
                                  zone_at);
                 if (h0) row[j0] = (uint16_t)x0;
@@ -922,9 +883,10 @@ ZoneShape zone_shape(const kmc_zone_ctx *c) {
 // Compute units on which every shape of zone_run is resident with a workgroup
 // each (0 when one does not fit).
 int zone_run_cus(int sites) {
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
     const size_t lds = zone_run_lds(sites);
     if (hipFuncSetAttribute((const void *)zone_rescue, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
     for (int per = 1; per <= kZoneRunMaxPairs; per *= 2) {
@@ -933,7 +895,7 @@ int zone_run_cus(int sites) {
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, zone_run_fn(per), 1024, lds) != hipSuccess || blocks < 1)
             return 0;
     }
-    return prop.multiProcessorCount;
+    return cus;
 }
 
 // The caller's occupancy after a run of n_steps.
