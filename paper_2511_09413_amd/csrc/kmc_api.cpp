@@ -35,7 +35,8 @@ hipError_t launch_import(const int8_t *src, int8_t *dst, const DevInfo *devs, in
 hipError_t launch_export(const int8_t *src, int8_t *dst, const DevInfo *devs, int n_dev, int64_t total,
                          hipStream_t st);
 hipError_t launch_place(int8_t *occ_pad, const DevInfo *devs, const int32_t *rail_dev, const int32_t *rail_idx,
-                        const int32_t *n_ions, int n_rails_total, uint32_t key0, uint32_t key1, hipStream_t st);
+                        const int32_t *n_ions, int n_rails_total, int max_sites, uint32_t key0, uint32_t key1,
+                        hipStream_t st);
 hipError_t launch_barrier_range(const void *ea, bool fp64, DevInfo *devs, int n_dev,
                                 unsigned long long *scratch, hipStream_t st);
 hipError_t launch_count_deciles(const int8_t *occ_pad, const DevInfo *devs, int n_dev, int64_t *dec_run,
@@ -52,7 +53,7 @@ hipError_t wave_capacity(int spl, size_t lds, bool fp64, int *blocks_per_cu);
 size_t wave_lds_bytes(int spl, int rail_range, int cut, bool fp64);
 int wave_band_words(int spl);
 hipError_t launch_copy_bytes(const void *src, void *dst, size_t bytes, hipStream_t st);
-hipError_t launch_replay_ec_full(const PhiArgs &a, bool fp64, hipStream_t st);
+hipError_t launch_replay_ec_full(const PhiArgs &a, int max_pitch, bool fp64, hipStream_t st);
 hipError_t launch_replay_ec_update(const PhiArgs &a, bool fp64, hipStream_t st, int64_t hops_known = -1);
 hipError_t launch_dense_phi(const DenseArgs &a, hipStream_t st);
 hipError_t launch_dense_decide(const HopArgs &a, int pitch, hipStream_t st);
@@ -1363,7 +1364,7 @@ kmc_status kmc_fill_random(kmc_ctx *c, const double *filling) {
                               c->stream));
     KMC_HIP(c, launch_place(c->cur, c->at<DevInfo>(c->lay.devs), c->at<int32_t>(c->lay.rail_dev),
                             c->at<int32_t>(c->lay.rail_idx), c->at<int32_t>(c->lay.n_ions),
-                            (int)c->lay.rails_total, (uint32_t)(c->p.seed & 0xffffffffu),
+                            (int)c->lay.rails_total, c->lay.max_pitch, (uint32_t)(c->p.seed & 0xffffffffu),
                             (uint32_t)(c->p.seed >> 32), c->stream));
     KMC_HIP(c, hipStreamSynchronize(c->stream));  // n_ions staging buffer is local
     return after_state_change(c);
@@ -1759,7 +1760,7 @@ kmc_status enqueue_replay(kmc_ctx *c, const int8_t *occ0_dev, int64_t step0, int
     pa.hops = b.hops;
     pa.hop_cap = c->lay.hop_cap;
     KMC_HIP(c, launch_zero_i64(b.hop_ctl, 2, c->stream));
-    KMC_HIP(c, launch_replay_ec_full(pa, c->fp64, c->stream));
+    KMC_HIP(c, launch_replay_ec_full(pa, c->lay.max_pitch, c->fp64, c->stream));
     // The recorded half-steps keep the state as one bit per site in the plane
     // not holding it (packed when they begin, unpacked into the byte plane,
     // whose barrier classes are unchanged, before a half-step drawn again).
