@@ -1,13 +1,14 @@
 """Set-up kernels at the sizes where they can go wrong (needs an MI355X): the
 random placement (the last ion's word found bit by bit) against the oracle's
-ranking, and the replay's starting Coulomb parts (table sums over window bits)
-through the replay against the oracle's."""
+ranking, the replay's starting Coulomb parts (table sums over window bits)
+through the replay against the oracle's, and protocols installed device by
+device."""
 import numpy as np
 import pytest
 
 import oracle
 from parity_util import gpu_available
-from workloads import FP32, FP64, Physics, constant
+from workloads import FP32, FP64, Physics, constant, step_then_relax
 
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
@@ -50,4 +51,33 @@ def test_replay_from_the_start_state(rails, sites, m, cut):
     ref = oracle.score_replay(oracle.OracleParams(ph, rails, sites), protos, occ0, 0, w)
     g, mag = ref["grad"], ref["mag"]
     assert np.all(np.abs(grad - g) <= 1e-9 * mag + 1e-300), (grad, g)
+    sim.close()
+
+
+def test_protocols_set_device_by_device():
+    """Runs of equal and different protocols, set in and out of order and again
+    after steps, give the trajectories of devices that each had theirs alone."""
+    from paper_2511_09413_amd import Simulator
+    rails, sites = [6] * 7, [48] * 7
+    ph = Physics(precision=FP64, seed=4, ea_ev=0.12)
+    p_or = oracle.OracleParams(ph, rails, sites)
+    a, b, c = constant(1.5), step_then_relax(-2.0, 15e-12), constant(-0.7)
+    sim = Simulator(ph, rails, sites)
+    occ = oracle.fill(p_or, [0.35] * 7)
+    sim.load_occupancy(occ)
+    first = [a, a, a, b, b, a, c]
+    for d in (0, 1, 2, 3, 4, 6, 5):
+        sim.set_bias_protocol(*first[d], device=d)
+    net = sim.run_steps(20, tallies=True)[0].cpu().numpy()
+    out = oracle.run(p_or, first, occ, 0, 20)
+    assert out["n_log"] > 0 or np.array_equal(net, out["net"])
+    for d in (2, 3):                                  # an incomplete run, then the steps
+        sim.set_bias_protocol(*b, device=d)
+    second, n_set = list(first), [0] * 7
+    second[2] = second[3] = b
+    n_set[2] = n_set[3] = 20
+    net = sim.run_steps(20, tallies=True)[0].cpu().numpy()
+    out = oracle.run(p_or, second, occ, 20, 20, n_set=n_set)
+    assert out["n_log"] > 0 or np.array_equal(net, out["net"])
+    assert np.array_equal(sim.read_occupancy(), occ)
     sim.close()
