@@ -287,8 +287,10 @@ kmc_status kmc_dense_potential(kmc_ctx *ctx, float *phi_dev);
  * Transfers count in the net tallies and the current like hops (toward site
  * 0's side positive), and in the deciles; the ion count is then free.  Draws:
  * Philox4x32-10 at counter (0, r, n, 16 d + 6 + h), word 0 (grounded side) or
- * 1 (biased side).  While any device has open electrodes every run uses the
- * half-step strategy, and kmc_score_replay returns KMC_EUNSUPPORTED.
+ * 1 (biased side).  While any device has open electrodes the launch strategy
+ * reads HALF_STEP (under AUTO and WAVE the library still runs a chunk of steps
+ * per launch where every device's tiles fit one workgroup, with the same
+ * results), and kmc_score_replay returns KMC_EUNSUPPORTED.
  *   ea_*, mu_*: eV, finite.  open: 0 (blocking, the default) or 1.
  * KMC_EUNSUPPORTED for KMC_BF16X2 and KMC_PHI_FIXED contexts.  Synchronises. */
 kmc_status kmc_set_electrodes(kmc_ctx *ctx, int32_t device, int32_t open, double ea_ground, double mu_ground,
@@ -360,7 +362,8 @@ typedef enum {
  * fit. */
 kmc_status kmc_set_launch_mode(kmc_ctx *ctx, int32_t mode);
 
-/* The strategy kmc_run_steps will use now (HALF_STEP, PERSISTENT or WAVE). */
+/* The strategy kmc_run_steps will use now (HALF_STEP, PERSISTENT or WAVE);
+ * HALF_STEP whenever a device has open electrodes (see kmc_set_electrodes). */
 kmc_status kmc_get_launch_mode(kmc_ctx *ctx, int32_t *mode);
 
 /* Number of launches per 1024-step chunk of the strategy in use (PERSISTENT

@@ -48,9 +48,9 @@ hipError_t launch_zero_i32(int32_t *p, int64_t n, hipStream_t st);
 hipError_t launch_persistent(const PArgs &a, int block, size_t lds, bool fp64, hipStream_t st);
 hipError_t persistent_capacity(int block, size_t lds, bool fp64, int *blocks_per_cu);
 hipError_t launch_zero_i64(int64_t *p, int64_t n, hipStream_t st);
-hipError_t launch_wave(const PArgs &a, int spl, size_t lds, bool fp64, hipStream_t st);
-hipError_t wave_capacity(int spl, size_t lds, bool fp64, int *blocks_per_cu);
-size_t wave_lds_bytes(int spl, int rail_range, int cut, bool fp64);
+hipError_t launch_wave(const PArgs &a, int spl, size_t lds, bool fp64, int open_tiles, hipStream_t st);
+hipError_t wave_capacity(int spl, size_t lds, bool fp64, int open_tiles, int *blocks_per_cu);
+size_t wave_lds_bytes(int spl, int rail_range, int cut, bool fp64, int open_tiles);
 int wave_band_words(int spl);
 hipError_t launch_copy_bytes(const void *src, void *dst, size_t bytes, hipStream_t st);
 hipError_t launch_replay_ec_full(const PhiArgs &a, int max_pitch, bool fp64, hipStream_t st);
@@ -334,6 +334,8 @@ struct kmc_ctx {
     int w_spl = 0;                     // sites per lane of the wave tiling
     size_t w_lds = 0;
     bool w_ok = false;                 // wave tiling fits co-resident on this GPU
+    int w_open_tiles = 0;              // tiles of every device when open electrodes run in wave tiles, else 0
+    size_t w_lds_open = 0;
     int mode = 0;                      // KMC_LAUNCH_AUTO / _HALF_STEP / _PERSISTENT
     uint64_t epoch = 0;
     float k10 = 0.0f;                  // K(1, 0) rounded to binary32
@@ -356,7 +358,7 @@ struct kmc_ctx {
     bool dr_stale = true, dr_fit = false;  // plan_draws is to run; its answer
     int dr_per_bin = 1;                // resolving workgroups per column block
     bool planes_equal = false;         // both state (and potential) planes hold the current state
-    bool any_open = false;             // some device has open electrodes: half-step launches only
+    bool any_open = false;             // some device has open electrodes: half-step launches or wave tiles (open_by_wave)
     // recording of accepted hops for the score replay (kmc_record_hops), in
     // the caller's buffer: per half-step counts, then a flag for the replay's
     // check of its start state; the state at the recording's first step; the
@@ -556,6 +558,7 @@ void make_wtiles(kmc_ctx *c) {
     c->wtiles.clear();
     c->wgroups.clear();
     c->w_ok = false;
+    c->w_open_tiles = 0;
     if (c->dense) return;
     int spl = 0;
     if (c->tile_sites == 1024 || c->tile_sites == 2048) {
@@ -580,9 +583,9 @@ void make_wtiles(kmc_ctx *c) {
     // occupancy the registers allow (five), the dispatcher stacks five
     // workgroups on some CUs and three on others, and the tiles of the fuller
     // SIMDs set the launch's time.
-    c->w_lds = std::max(wave_lds_bytes(spl, c->p.rail_range, c->lay.cut, c->fp64),
-                        (size_t)lds_per_cu / (spl == 64 ? 2 : 4));
-    if (wave_capacity(spl, c->w_lds, c->fp64, &per_cu) != hipSuccess) return;
+    const size_t share = (size_t)lds_per_cu / (spl == 64 ? 2 : 4);
+    c->w_lds = std::max(wave_lds_bytes(spl, c->p.rail_range, c->lay.cut, c->fp64, 0), share);
+    if (wave_capacity(spl, c->w_lds, c->fp64, 0, &per_cu) != hipSuccess) return;
     // groups of whole devices, each co-resident (and within the publication memory)
     int64_t cap = std::min<int64_t>((int64_t)per_cu * cus * kWaveTilesPerWG, c->lay.max_wtiles);
     if (c->group_limit > 0) cap = std::min<int64_t>(cap, c->group_limit);
@@ -608,6 +611,19 @@ void make_wtiles(kmc_ctx *c) {
             c->wtiles[i].next -= g.first;
         }
     c->w_ok = true;
+    // Open electrodes: wave tiles where every device's tiles are the same
+    // number and fit one workgroup, so that no tile ever waits for another
+    // workgroup's and the launch is as independent of what else runs on the
+    // GPU as half-step launches are.
+    const int n_open = (int)(c->wtiles.size() / (size_t)c->p.n_devices);
+    if (c->phifix || spl > 32 || n_open > kWaveOpenTiles) return;
+    for (size_t i = 0; i < c->wtiles.size(); ++i)
+        if (c->wtiles[i].d != (int)(i / (size_t)n_open)) return;
+    c->w_lds_open = wave_lds_bytes(spl, c->p.rail_range, c->lay.cut, c->fp64, n_open);
+    if (c->w_lds_open > (size_t)lds_per_cu) return;
+    int open_per_cu = 0;
+    if (wave_capacity(spl, c->w_lds_open, c->fp64, n_open, &open_per_cu) == hipSuccess && open_per_cu >= 1)
+        c->w_open_tiles = n_open;
 }
 
 // The strategy a run uses: KMC_LAUNCH_WAVE, _PERSISTENT or _HALF_STEP.
@@ -630,6 +646,16 @@ kmc_status bias_flush(kmc_ctx *c) {
                                    c->at<DevInfo>(c->lay.devs), d0, d1, c->bias_n, c->bias_set, c->bias_t, c->bias_v,
                                    c->stream));
     return KMC_OK;
+}
+
+// Whether a run with open electrodes goes by wave tiles: where a device's
+// tiles fit one workgroup (make_wtiles), unless another strategy was asked
+// for.  (kmc_get_launch_mode reports HALF_STEP for every context with open
+// electrodes.)  4 x 64 x 200 in binary64 at 0.15 eV: 42.1 us per step in
+// half-step launches with a launch for the boundary bonds each, 14.5 in wave
+// tiles.
+bool open_by_wave(const kmc_ctx *c) {
+    return c->any_open && c->w_open_tiles > 0 && (c->mode == KMC_LAUNCH_AUTO || c->mode == KMC_LAUNCH_WAVE);
 }
 
 HopArgs hop_args(kmc_ctx *c) {
@@ -895,7 +921,8 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
     if (s != KMC_OK) return s;
     HopArgs a = hop_args(c);
     const int kind = launch_kind(c);
-    const bool wave = kind == KMC_LAUNCH_WAVE;
+    const bool open_wave = open_by_wave(c);
+    const bool wave = kind == KMC_LAUNCH_WAVE || open_wave;
     const bool persistent = wave || kind == KMC_LAUNCH_PERSISTENT;
     Ctl ctl{};
     ctl.call_base = c->n;
@@ -938,6 +965,7 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
         pa.status = c->at<int32_t>(c->lay.status);
         pa.spin_limit = c->spin_limit;
         pa.occ_user = c->occ_user;
+        pa.el = c->at<Electrode>(c->lay.electrodes);
     }
     if (c->rec_on) {
         HopRecord r{c->rec_buf, c->rec_count, c->rec_cap, c->rec_n0, c->rec_n_hs};
@@ -980,7 +1008,8 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
                 pa.ticket = nullptr;
                 if (wave && wave_finishes(pa.fin.d0, pa.fin.d1, chunk)) pa.ticket = c->at<uint32_t>(c->lay.ticket);
                 else all_finished = false;
-                if (wave) KMC_HIP(c, launch_wave(pa, c->w_spl, c->w_lds, c->fp64, c->stream));
+                if (wave) KMC_HIP(c, launch_wave(pa, c->w_spl, open_wave ? c->w_lds_open : c->w_lds, c->fp64,
+                                                open_wave ? c->w_open_tiles : 0, c->stream));
                 else KMC_HIP(c, launch_persistent(pa, c->p_block, c->p_lds, c->fp64, c->stream));
             }
             if (wave && !all_finished) {
@@ -1987,6 +2016,14 @@ kmc_status kmc_set_electrodes(kmc_ctx *c, int32_t device, int32_t open, double e
         e.mu_ground = mu_ground;
         e.ea_bias = ea_bias;
         e.mu_bias = mu_bias;
+        // bounds of a boundary site's potential: its window lies on one side
+        e.phi_pos = e.phi_neg = 0.0;
+        const DevInfo &dv = c->devs[d];
+        for (int k = 0; k < dv.n_nbr; ++k)
+            for (int ds = 0; ds <= std::min(c->lay.cut, dv.sites - 1); ++ds) {
+                const double K = kernel64(&c->p, ds, dv.nbr_dist[k]);
+                (K > 0.0 ? e.phi_pos : e.phi_neg) += std::fabs(K);
+            }
     }
     c->any_open = false;
     for (const Electrode &e : c->el) c->any_open = c->any_open || e.open;

@@ -6,6 +6,11 @@
 
 #include <hip/hip_runtime.h>
 
+#if defined(__HIPCC__)
+#include <type_traits>
+
+#include "kmc_device.h"
+#endif
 #include "kmc_internal.h"
 
 namespace kmc {
@@ -16,6 +21,7 @@ struct Electrode {
     int32_t open, pad_;
     double ea_ground, mu_ground;   // eV
     double ea_bias, mu_bias;       // eV
+    double phi_pos, phi_neg;       // -phi_neg <= phi <= phi_pos at a boundary site, whatever the state
 };
 
 // One half-step of boundary bonds, after the interior bonds of the same
@@ -41,6 +47,22 @@ struct ElectrodeArgs {
     int32_t n_devices;
     HopArgs::LogBuf log;
 };
+
+#if defined(__HIPCC__)
+// Inclusive threshold of a boundary bond's Philox word: every configuration
+// has p below it.  dE = (+-field + s phi) - s mu with |field| and phi bounded,
+// s = +1 injection, -1 extraction; the slack covers the rounding of the
+// path's own sums (`terms` window terms) in Real, threshold_of the rest.
+template <typename Real>
+__device__ inline uint32_t boundary_threshold(double ea, double mu, double phi_pos, double phi_neg, bool inject,
+                                              double field, int terms, double beta, double c0) {
+    const double eps = std::is_same<Real, double>::value ? 1.2e-16 : 6e-8;
+    const double low = inject ? field + phi_neg + mu : field + phi_pos - mu;  // -dE at most
+    const double slack = eps * (double)(terms + 8) * (fabs(ea) + fabs(mu) + field + phi_pos + phi_neg);
+    const double A = exp(-beta * (ea - 0.5 * low - slack));
+    return A < 1e37 ? threshold_of(c0, A, 1.0) : 0xFFFFFFFFu;
+}
+#endif
 
 hipError_t launch_electrodes(const ElectrodeArgs &a, bool fp64, hipStream_t st);
 

@@ -55,6 +55,7 @@ struct PTile {
 
 constexpr int kPubSlots = 2 * kTallySteps + 1;  // publication slots per tile: one per state of a launch
 constexpr int kPMaxBlock = 1024;         // threads per workgroup, persistent kernel
+constexpr int kWaveOpenTiles = 16;       // the same with open electrodes: at most, all of one device
 constexpr int kWaveTilesPerWG = 4;       // wave kernel: tiles (one wavefront each) per workgroup
 constexpr int kSnapSlots = 64;           // wave kernel: edge-row snapshots per tile in a ring
 constexpr int kTicketBuckets = 64;       // wave kernel: end-of-launch counters (one 128-byte line each)
@@ -174,6 +175,8 @@ struct DenseArgs {
 
 // Arguments of the persistent kernel (several steps per launch, each
 // workgroup keeps its tile in LDS and talks to its two neighbours only).
+struct Electrode;  // kmc_electrode.h
+
 struct PArgs {
     int8_t *occ;               // padded state: read at launch start, written at the end
     const DevInfo *devs;
@@ -207,6 +210,7 @@ struct PArgs {
     // tally finish for the launch's devices [fin.d0, fin.d1) and clears the
     // counters.
     int8_t *occ_user;
+    const Electrode *el;       // [D], read by the tiles of an open-electrode launch
     uint32_t *ticket;
     FinishArgs fin;
 };

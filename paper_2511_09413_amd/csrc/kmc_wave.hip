@@ -12,7 +12,7 @@
 // the tile's bits (the Jacobi snapshot) and, when a survivor's Coulomb window
 // may cross the tile edge, fetch the neighbouring tiles' edge rails.  The
 // workgroup is only a container for kWaveTilesPerWG independent tiles; its one
-// barrier precedes the loop.
+// barrier precedes the loop (except with open electrodes, below).
 //
 // Cross-tile data.  After every half-step a tile stores one 64-bit word for
 // the new state into its per-state array: a tag naming the state (launch
@@ -45,9 +45,25 @@
 // survivors per tile and half-step: 20.4 us per step one at a time over the
 // wavefront, 13.6 in twos, 11.8 in fours, 12.3 in eights; eights also slow the
 // rare survivors of 4096 x 1024, 1.48 us per step against 1.45).
+//
+// Open electrodes (the Open instantiations; boundary bonds as kmc_electrode.hip
+// defines them).  The tiles of a device are one workgroup, so they exchange
+// through LDS: every half-step each lane stores its sites into the next of two
+// planes of the device's packed rails, one barrier follows, and survivors read
+// any rail of the current plane; nothing is published and no tile waits for
+// another workgroup's.  A boundary bond belongs to the lane that holds the
+// site: its word is drawn every half-step of its parity and tested against a
+// threshold per step, side and direction, and a word that passes is decided
+// exactly by that lane.  What bounds it: VALU issue and latency of the
+// survivors, sixteen tiles on one CU (4 x 64 x 200 in binary64 at 0.15 eV,
+// 14.5 us per step; with the publications of the closed kernel in place of the
+// planes 15.4; the boundary potential walks the set bits, in pairs, where a
+// test of every site of the window took 4.4 us more per step; survivors in
+// eights or sixteens 15.4 and 17.6).  Half-step launches: 42.1 us.
 #include <type_traits>
 
 #include "kmc_device.h"
+#include "kmc_electrode.h"
 #include "kmc_internal.h"
 
 namespace kmc {
@@ -82,10 +98,19 @@ struct Survivor {
     uint32_t word;   // its Philox word
 };
 
+// Stage-0 thresholds of the boundary bonds of a tile with open electrodes, per
+// step of the window: [side][0 injection, 1 extraction].
+template <bool Open>
+struct WaveOpenLds {};
+template <>
+struct WaveOpenLds<true> {
+    uint32_t step_el[2][2][kWaveWin];
+};
+
 // A tile's LDS: its rare-path values, per-device and per-step tables and the
 // rare-path buffers.
-template <typename Real, int SPL>
-struct WaveLds {
+template <typename Real, int SPL, bool Open>
+struct WaveLds : WaveOpenLds<Open> {
     static constexpr int kBand = 4 * SPL + 16;  // 32-bit words of neighbour rails
     static constexpr int kSnap = SPL == 64 ? 128 : 64;
     WaveGeo geo;
@@ -98,26 +123,25 @@ struct WaveLds {
     uint32_t band_idx[64];               // entry i of band (i < 64): idx << 16 | q of fetch_bands
     unsigned char row_of[64];            // each lane's rail in the tile
     int16_t snap_state[kSnapSlots];      // launch-relative state of each ring slot's snapshot
-    unsigned char cls[64 * SPL];         // barrier class of every site, rows at the device pitch
+    alignas(16) unsigned char cls[64 * SPL];  // barrier class of every site, rows at the device pitch
 };
-template <typename Real, int SPL>
-constexpr bool wave_lds_aligned() {
-    // tiles stay 16-byte aligned, class rows are written as 16-byte vectors
-    using Lds = WaveLds<Real, SPL>;
-    return sizeof(Lds) % 16 == 0 && offsetof(Lds, cls) % 16 == 0;
-}
-static_assert(wave_lds_aligned<float, 16>() && wave_lds_aligned<float, 32>() && wave_lds_aligned<float, 64>() &&
-              wave_lds_aligned<double, 16>() && wave_lds_aligned<double, 32>() && wave_lds_aligned<double, 64>(), "LDS layout");
+// Open electrodes: the device's rails, packed, of the current and the next
+// state (words per state: 64 per tile at most, one for the idle lanes' stores
+// and two that window reads may touch).
+constexpr int kPlaneWords = 64 * kWaveOpenTiles + 4;
+constexpr size_t kPlaneBytes = 2 * kPlaneWords * sizeof(uint32_t);
+static_assert(kPlaneBytes % 16 == 0, "LDS tiles stay 16-byte aligned");
 
 // The workgroup's table before its tiles: the bond differences where there
-// are such (kernel_diff_width), else the kernel K(dist, ds) when it fits.
-__host__ __device__ inline int wave_table_entries(int rail_range, int cut) {
-    if (kernel_diff_width(cut) > 0) return (rail_range + 1) * kernel_diff_width(cut);
-    const int n_kt = (rail_range + 1) * (cut + 1);
+// are such (kernel_diff_width; with open electrodes the kernel K(dist, ds)
+// before them), else the kernel when it fits.
+__host__ __device__ inline int wave_table_entries(int rail_range, int cut, bool open) {
+    const int n_kt = (rail_range + 1) * (cut + 1), n_diff = (rail_range + 1) * kernel_diff_width(cut);
+    if (n_diff > 0) return n_diff + (open ? n_kt : 0);
     return n_kt <= kLdsTableMax ? n_kt : 0;
 }
-__host__ __device__ inline size_t wave_table_bytes(int rail_range, int cut, size_t real) {
-    return ((size_t)wave_table_entries(rail_range, cut) * real + 15) & ~(size_t)15;
+__host__ __device__ inline size_t wave_table_bytes(int rail_range, int cut, size_t real, bool open) {
+    return ((size_t)wave_table_entries(rail_range, cut, open) * real + 15) & ~(size_t)15;
 }
 
 __device__ __forceinline__ void wave_sync() {
@@ -284,8 +308,8 @@ __device__ __forceinline__ uint32_t pick_word(const uint32_t (&wd)[N], int i) {
 
 }  // namespace
 
-template <typename Real, int SPL>
-__global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_wave(PArgs a) {
+template <typename Real, int SPL, bool Open>
+__global__ __launch_bounds__(64 * (Open ? kWaveOpenTiles : kWaveTilesPerWG), SPL == 64 ? 2 : 4) void hop_wave(PArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int kW = SPL / 2;          // Philox words per lane and half-step (SPL / 8 blocks):
                                          // word b / 2 belongs to the bond at site s0 + b
@@ -295,8 +319,10 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: tile data in scalar registers
 
-    const int n_groups = (a.n_tiles + kWaveTilesPerWG - 1) / kWaveTilesPerWG;
-    const int ti = tile_of_block(blockIdx.x, n_groups) * kWaveTilesPerWG + wave;
+    // (open electrodes: one device's tiles to the workgroup)
+    const int per_wg = Open ? (int)blockDim.x >> 6 : kWaveTilesPerWG;
+    const int n_groups = (a.n_tiles + per_wg - 1) / per_wg;
+    const int ti = tile_of_block(blockIdx.x, n_groups) * per_wg + wave;
     // the tile and its device, loaded before the barrier that the kernel table
     // needs, so that their latencies overlap the table's
     const PTile tile = a.tiles[ti < a.n_tiles ? ti : 0];
@@ -306,16 +332,17 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
     {
         const Real *tab = std::is_same<Real, double>::value ? reinterpret_cast<const Real *>(a.ktab64)
                                                             : reinterpret_cast<const Real *>(a.ktab32);
-        if (kernel_diff_width(a.cutoff) > 0) tab += (a.rail_range + 1) * (a.cutoff + 1);
-        const int n = wave_table_entries(a.rail_range, a.cutoff);
+        if (!Open && kernel_diff_width(a.cutoff) > 0) tab += (a.rail_range + 1) * (a.cutoff + 1);
+        const int n = wave_table_entries(a.rail_range, a.cutoff, Open);
         for (int i = threadIdx.x; i < n; i += blockDim.x) reinterpret_cast<Real *>(smem)[i] = tab[i];
     }
     __syncthreads();
     // the tile's LDS (after the kernel table when that is in LDS)
-    auto lds_of = [&](KArgs ka) -> WaveLds<Real, SPL> & {
-        return reinterpret_cast<WaveLds<Real, SPL> *>(smem + wave_table_bytes(ka->rail_range, ka->cutoff, sizeof(Real)))[wave];
+    auto lds_of = [&](KArgs ka) -> WaveLds<Real, SPL, Open> & {
+        return reinterpret_cast<WaveLds<Real, SPL, Open> *>(smem + wave_table_bytes(ka->rail_range, ka->cutoff, sizeof(Real), Open) +
+                                                            (Open ? kPlaneBytes : 0))[wave];
     };
-    WaveLds<Real, SPL> &w = lds_of(kargs());
+    WaveLds<Real, SPL, Open> &w = lds_of(kargs());
 
     if (ti >= a.n_tiles) return;  // no barrier follows
 
@@ -421,6 +448,32 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
             r_lane = q_lo == 0 ? 0xFFFFFFFFu : (uint32_t)fmin(ceil(rho * 4294967296.0), 4294967295.0);
         }
     }
+    // Open: the rail ends the lane owns (bit 0: site 0, bit 1: site L - 1), the
+    // parity of the bond behind site L - 1, and the byte of the lane's sites in
+    // the device's plane (rail by rail, W32 words each).
+    uint32_t ends = 0, plane_at = 4 * (kPlaneWords - 3);
+    int far_parity = 0;
+    auto plane_of = [&](KArgs ka) -> unsigned char * {
+        return smem + wave_table_bytes(ka->rail_range, ka->cutoff, sizeof(Real), true);
+    };
+    auto plane_put = [&](int state) {
+        unsigned char *at = plane_of(kargs()) + (state & 1) * (4 * kPlaneWords) + plane_at;
+        if constexpr (SPL == 16) *reinterpret_cast<uint16_t *>(at) = (uint16_t)bits;
+        else *reinterpret_cast<uint32_t *>(at) = (uint32_t)bits;
+    };
+    if constexpr (Open) {
+        const int x = dvc.sites - 1, lpr = (dvc.pitch + SPL - 1) / SPL;
+        far_parity = x & 1;
+        if (lane < tile.nr * lpr) {
+            if (a.el[d].open) ends = (s0 == 0 ? 1u : 0u) | (x >= s0 && x < s0 + SPL ? 2u : 0u);
+            plane_at = 4 * rail * (uint32_t)((dvc.pitch + 31) / 32) + s0 / 8;
+        }
+        for (int i = threadIdx.x; i < 2 * kPlaneWords; i += blockDim.x)
+            reinterpret_cast<uint32_t *>(plane_of(kargs()))[i] = 0u;
+        __syncthreads();
+        plane_put(0);
+        __syncthreads();
+    }
     PhLane<kNB> phl;
     ph_lane_init<0>(phl, (uint32_t)(s0 >> 3), (uint32_t)d << 4, a.key0, a.key1);
     // the candidate bonds of each parity that lie inside the rail
@@ -436,7 +489,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
     uint32_t t_add = 8600u;  // the stage-0 margin of the window (uniform, kept in a vector register)
     auto refresh = [&](int kb) {
         const KArgs ka = kargs();
-        WaveLds<Real, SPL> &wr = *lds_opaque(&w);
+        WaveLds<Real, SPL, Open> &wr = *lds_opaque(&w);
         const WaveGeo &g = wr.geo;
         const int dd = rfl(g.d);
         const int64_t k = rfl(g.n_base) - rfl(g.n_set) + kb + lane;
@@ -448,6 +501,16 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
         thr_lane = threshold_of(ka->c0, wr.cls_a[0], gg);
         t_add = __ballot(thr_lane == 0xFFFFFFFFu) != 0 ? 0xFFFFFFFFu : 8600u;
         asm volatile("" : "+v"(t_add));
+        if constexpr (Open) {
+            const Electrode &el = ka->el[dd];
+            const double field = fabs(ka->alpha * V) / (double)rfl(g.L);
+            const int terms = rfl(g.n_nbr) * (rfl(g.cutoff) + 1);
+#pragma unroll 1
+            for (int i = 0; i < 4; ++i)
+                wr.step_el[i >> 1][i & 1][lane] = boundary_threshold<Real>(
+                    i & 2 ? el.ea_bias : el.ea_ground, i & 2 ? el.mu_bias : el.mu_ground, el.phi_pos, el.phi_neg,
+                    (i & 1) == 0, field, terms, ka->beta, ka->c0);
+        }
         wave_sync();
     };
 
@@ -483,7 +546,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
     // wait for the owning tile's state, then the word of its snapshot), so
     // that the round trips to the other tiles' publications overlap.  Uniform
     // result.
-    auto fetch_bands = [&](KArgs ka, WaveLds<Real, SPL> &wr, int64_t jrel) -> bool {
+    auto fetch_bands = [&](KArgs ka, WaveLds<Real, SPL, Open> &wr, int64_t jrel) -> bool {
         const WaveGeo &g = wr.geo;
         const int w32 = rfl(g.W32), mm = rfl(g.m), prev = rfl(g.prev), next = rfl(g.next);
         const int nr_p = rfl(g.nr_prev), nr_n = rfl(g.nr_next);
@@ -523,7 +586,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
 
     int snap_count = 0;
     uint32_t snap_word = 0;  // ring slot << 12 | launch-relative state of the latest snapshot
-    if (!isolated) {
+    if (!Open && !isolated) {
         write_snapshot(w.geo, 0, 0);
         if (lane == 0) {
             w.snap_state[0] = 0;
@@ -545,7 +608,8 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
     // test, in the bits sv of the lanes any, and each lane's lowest one's word.  Flips the accepted hops' sites and,
     // when an edge rail changed, writes the new state's snapshot.  False when a
     // wait for a neighbour failed.
-    auto survivors = [&](auto h_c, const int kstep, Bits sv, const uint32_t w_low, const uint64_t any) __attribute__((always_inline)) -> bool {
+    auto survivors = [&](auto h_c, const int kstep, Bits sv, const uint32_t w_low, const uint64_t any,
+                         const uint32_t el_hit) __attribute__((always_inline)) -> bool {
         constexpr int h = decltype(h_c)::value;
         // the state index: derived from an opaque copy of the step, so that no
         // register holds it across the step
@@ -557,14 +621,14 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
         const int kw = kstep & (kWaveWin - 1);
         bool edge_changed = false;
         const KArgs ka = kargs();
-        WaveLds<Real, SPL> &wr = *lds_opaque(&w);
+        WaveLds<Real, SPL, Open> &wr = *lds_opaque(&w);
         const WaveGeo &g = wr.geo;
         const int cut = rfl(g.cutoff), Lq = rfl(g.L), lprq = rfl(g.lpr), nrq = rfl(g.nr), mq = rfl(g.m);
         const int w32 = rfl(g.W32), Rq = rfl(g.R), n_nbr = rfl(g.n_nbr), r0 = rfl(g.r0), dd = rfl(g.d);
         const bool single = rfl(g.single) != 0;
         const int64_t n = rfl(g.n_base) + kstep;
         // the tile's rails, packed: each lane's bits follow the previous lane's
-        if (s0 < 32 * w32 && lane < nrq * lprq) {
+        if (!Open && s0 < 32 * w32 && lane < nrq * lprq) {
             const int row = wr.row_of[lane];
             unsigned char *at = reinterpret_cast<unsigned char *>(wr.snap) + 4 * row * w32 + s0 / 8;
             if constexpr (SPL == 16) *reinterpret_cast<uint16_t *>(at) = (uint16_t)bits;
@@ -575,11 +639,17 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
             }
         }
         bool ok = true;
-        if (!isolated) ok = fetch_bands(ka, wr, js_now());
+        if (!Open && !isolated) ok = fetch_bands(ka, wr, js_now());
         wave_sync();
         if (!ok) return false;
         // rail rho of the tile's neighbourhood (r0 + rho in the device)
         auto rail_words = [&](int rho) -> const uint32_t * {
+            if constexpr (Open) {
+                int r = r0 + rho;
+                while (r < 0) r += Rq;
+                while (r >= Rq) r -= Rq;
+                return reinterpret_cast<const uint32_t *>(plane_of(ka)) + h * kPlaneWords + r * w32;
+            }
             if (single) {
                 while (rho < 0) rho += Rq;
                 while (rho >= Rq) rho -= Rq;
@@ -642,7 +712,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
             // ...), so that the sum is the same to the last bit.
             constexpr int kGroup = 64 / kSurvivorsAtOnce, kAcc = 64 / kGroup;
             const int grp = lane / kGroup, gl = lane % kGroup;
-            const Real *diff = reinterpret_cast<const Real *>(smem);
+            const Real *diff = reinterpret_cast<const Real *>(smem) + (Open ? (mq + 1) * (cut + 1) : 0);
             uint64_t lanes = any;
             bool first_round = true;
             while (lanes) {
@@ -733,7 +803,7 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
                     svl &= svl - 1;
                     const int s = ls0 + b;
                     const uint32_t word = word_at(s, (uint32_t)(r0 + lrow));
-                    const uint32_t *own_row = wr.snap + lrow * w32;
+                    const uint32_t *own_row = Open ? rail_words(lrow) : wr.snap + lrow * w32;
                     const int o = (own_row[s >> 5] >> (s & 31)) & 1u ? s : s + 1;
                     const int t = (o == s) ? s + 1 : s;
                     int lo = s - cut, hi = s + 1 + cut;
@@ -763,10 +833,80 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
                 }
             }
         }
+        if constexpr (Open) {
+            // Boundary bonds whose words passed their stage 0 (see
+            // kmc_electrode.hip): each its own lane's, the potential of the
+            // boundary site summed rail by rail in the neighbour order, sites in
+            // increasing order.
+            const int n_kt = (mq + 1) * (cut + 1);
+            const bool kt_lds = kernel_diff_width(cut) > 0 || n_kt <= kLdsTableMax;
+            uint32_t hit = el_hit;
+            while (__ballot(hit != 0u)) {
+                if (hit) {
+                    const int side = hit & 1u ? 0 : 1;
+                    hit &= hit - 1;
+                    const int row = wr.row_of[lane];
+                    const int x = side ? Lq - 1 : 0, res = side ? Lq : -1;
+                    const Electrode &el = ka->el[dd];
+                    const bool inject = ((bits >> (x - s0)) & 1u) == 0u;
+                    const int o = inject ? res : x, t = inject ? x : res;
+                    const int lo = x - cut < 0 ? 0 : x - cut, hi = x + cut > Lq - 1 ? Lq - 1 : x + cut;
+                    Real phi = (Real)0;
+                    auto window = [&](const Real *kt) {
+                        for (int k = 0; k < n_nbr; ++k) {
+                            const int off = rfl((int)g.nbr_off[k]);
+                            const Real *ktr = kt + rfl((int)g.nbr_dist[k]) * (cut + 1);
+                            const uint32_t *words = rail_words(row + off);
+                            // 32 sites at a time, their ions in pairs (the table
+                            // reads of a pair overlap)
+                            for (int j0 = lo; j0 <= hi; j0 += 32) {
+                                const int q = j0 >> 5;
+                                uint32_t m = (uint32_t)(((uint64_t)words[q] | (uint64_t)words[q + 1] << 32) >> (j0 & 31));
+                                if (hi - j0 < 31) m &= (2u << (hi - j0)) - 1u;
+                                if (off == 0 && x >= j0 && x < j0 + 32) m &= ~(1u << (x - j0));
+                                while (m) {
+                                    const int j = j0 + __builtin_ctz(m);
+                                    m &= m - 1;
+                                    const bool two = m != 0u;
+                                    const int j2 = two ? j0 + __builtin_ctz(m) : j;
+                                    m &= m - 1;
+                                    const Real K = ktr[side ? x - j : j], K2 = ktr[side ? x - j2 : j2];
+                                    phi += K;
+                                    phi += two ? K2 : (Real)0;
+                                }
+                            }
+                        }
+                    };
+                    if (kt_lds) window(reinterpret_cast<const Real *>(smem));
+                    else if constexpr (std::is_same<Real, double>::value) window(reinterpret_cast<const Real *>(ka->ktab64));
+                    else window(reinterpret_cast<const Real *>(ka->ktab32));
+                    const Real alpha_r = (Real)ka->alpha, V_r = (Real)wr.step_v[kw];
+                    const Real e_app = ((alpha_r * V_r) * (Real)(t - o)) / (Real)Lq;
+                    const Real sgn = inject ? (Real)1 : (Real)-1;
+                    const Real mu = (Real)(side == 0 ? el.mu_ground : el.mu_bias);
+                    const Real dE = (e_app + sgn * phi) - sgn * mu;
+                    const Real ea = (Real)(side == 0 ? el.ea_ground : el.ea_bias);
+                    const uint4 blk = philox4x32_10(0u, (uint32_t)(r0 + row), (uint32_t)n,
+                                                    ((uint32_t)dd << 4) | (3u << 1) | (uint32_t)h, ka->key0, ka->key1);
+                    HopArgs::LogBuf log;
+                    log.count = ka->log.count;
+                    log.entries = ka->log.entries;
+                    log.cap = ka->log.cap;
+                    if (decide_hop<Real>(dE, ea, side == 0 ? blk.x : blk.y, (Real)ka->beta, (Real)ka->c0, log, dd, h, n,
+                                         r0 + row, side == 0 ? -1 : Lq - 1)) {
+                        fl ^= (Bits)1 << (x - s0);
+                        const int64_t base = (n - rfl(g.tally_base)) * ka->n_devices + dd;
+                        // toward site 0's side: extraction at the grounded end, injection at the biased end
+                        atomicAdd(&ka->tally_net[base], (side == 0) != inject ? 1 : -1);
+                        atomicAdd(&ka->tally_dec[base * kDeciles + (10 * x) / Lq], inject ? 1 : -1);
+                    }
+                }
+            }
+        }
         bits ^= fl;
         nbit = __shfl_down((uint32_t)bits, 1, 64) & 1u;
         bx = (uint32_t)bits | (nbit << 16);
-        if (edge_changed && !isolated) {
+        if (!Open && edge_changed && !isolated) {
             const uint32_t jn = (uint32_t)js_now() + 1u;
             const int sc = rfl(snap_count) + 1;
             snap_count = sc;
@@ -821,12 +961,26 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
         // value of it (the survivors' vote, the changed edge) is merged, spilled
         // or tested on the common path
         const bool stage1 = mn <= t_lane && cand != 0u;
-        if (__builtin_expect(__ballot(stage1) != 0, 0)) {
+        uint32_t el_hit = 0;  // Open: the lane's boundary bonds of this parity whose words pass stage 0
+        if constexpr (Open) {
+            if (h == 1 || far_parity == 0) {
+                const KArgs ka = kargs();
+                const WaveLds<Real, SPL, Open> &wr = *lds_opaque(&w);
+                const uint4 blk = philox4x32_10(0u, rail, (uint32_t)ka->ctl.n_base + (uint32_t)kstep,
+                                                ((uint32_t)d << 4) | (3u << 1) | (uint32_t)h, ka->key0, ka->key1);
+                if (h == 1 && (ends & 1u) && blk.x <= wr.step_el[0][bits & 1u][kw]) el_hit |= 1u;
+                if (far_parity == h && (ends & 2u)) {
+                    const int x = rfl(wr.geo.L) - 1 - s0;
+                    if (blk.y <= wr.step_el[1][(bits >> x) & 1u][kw]) el_hit |= 2u;
+                }
+            }
+        }
+        if (__builtin_expect(__ballot(stage1 || el_hit != 0u) != 0, 0)) {
             Bits sv = 0;
             uint32_t w_low = 0;  // the word of the lane's lowest survivor
             if (stage1) {
                 const double c0 = kargs()->c0;
-                WaveLds<Real, SPL> &wr = *lds_opaque(&w);
+                WaveLds<Real, SPL, Open> &wr = *lds_opaque(&w);
                 const double g_step = wr.step_g[kw];
                 Bits c = cand;
                 while (c) {
@@ -843,9 +997,20 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
                 }
             }
             const uint64_t any = __ballot(sv != 0u);
-            if (any && !survivors(h_c, kstep, sv, w_low, any)) return false;
+            if ((any || __ballot(el_hit != 0u)) && !survivors(h_c, kstep, sv, w_low, any, el_hit)) return false;
         }
 
+        if constexpr (Open) {
+            // the new state's plane: the other one was last read a half-step
+            // ago, before the previous barrier
+            // (the barrier waits for LDS only: the tallies' atomics and the
+            // log's stores go on)
+            plane_put(h + 1);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            return true;
+        }
         // publish the new state js + 1
         ++pub_at;
         ++tag_j;
@@ -964,40 +1129,51 @@ __global__ __launch_bounds__(64 * kWaveTilesPerWG, SPL == 64 ? 2 : 4) void hop_w
 }
 
 namespace {
-const void *wave_fn(int spl, bool fp64) {
-    if (spl == 64) return fp64 ? (const void *)hop_wave<double, 64> : (const void *)hop_wave<float, 64>;
-    if (spl == 32) return fp64 ? (const void *)hop_wave<double, 32> : (const void *)hop_wave<float, 32>;
-    return fp64 ? (const void *)hop_wave<double, 16> : (const void *)hop_wave<float, 16>;
+// (open electrodes: 16 or 32 sites per lane, the host's rule)
+const void *wave_fn(int spl, bool fp64, bool open) {
+    if (open) {
+        if (spl == 32) return fp64 ? (const void *)hop_wave<double, 32, true> : (const void *)hop_wave<float, 32, true>;
+        return fp64 ? (const void *)hop_wave<double, 16, true> : (const void *)hop_wave<float, 16, true>;
+    }
+    if (spl == 64) return fp64 ? (const void *)hop_wave<double, 64, false> : (const void *)hop_wave<float, 64, false>;
+    if (spl == 32) return fp64 ? (const void *)hop_wave<double, 32, false> : (const void *)hop_wave<float, 32, false>;
+    return fp64 ? (const void *)hop_wave<double, 16, false> : (const void *)hop_wave<float, 16, false>;
 }
-template <typename Real>
+template <typename Real, bool Open>
 size_t wave_tile_lds(int spl) {
-    return spl == 64 ? sizeof(WaveLds<Real, 64>) : (spl == 32 ? sizeof(WaveLds<Real, 32>) : sizeof(WaveLds<Real, 16>));
+    return spl == 64 ? sizeof(WaveLds<Real, 64, Open>) : (spl == 32 ? sizeof(WaveLds<Real, 32, Open>) : sizeof(WaveLds<Real, 16, Open>));
 }
 }  // namespace
 
-size_t wave_lds_bytes(int spl, int rail_range, int cut, bool fp64) {
+size_t wave_lds_bytes(int spl, int rail_range, int cut, bool fp64, int open_tiles) {
+    const bool open = open_tiles > 0;
     const size_t real = fp64 ? sizeof(double) : sizeof(float);
-    return wave_table_bytes(rail_range, cut, real) + kWaveTilesPerWG * (fp64 ? wave_tile_lds<double>(spl) : wave_tile_lds<float>(spl));
+    const size_t tile = fp64 ? (open ? wave_tile_lds<double, true>(spl) : wave_tile_lds<double, false>(spl))
+                             : (open ? wave_tile_lds<float, true>(spl) : wave_tile_lds<float, false>(spl));
+    return wave_table_bytes(rail_range, cut, real, open) + (open ? kPlaneBytes + open_tiles * tile : kWaveTilesPerWG * tile);
 }
 
 int wave_band_words(int spl) {
-    return spl == 64 ? WaveLds<float, 64>::kBand : (spl == 32 ? WaveLds<float, 32>::kBand : WaveLds<float, 16>::kBand);
+    return spl == 64 ? WaveLds<float, 64, false>::kBand : (spl == 32 ? WaveLds<float, 32, false>::kBand : WaveLds<float, 16, false>::kBand);
 }
 
-hipError_t launch_wave(const PArgs &a, int spl, size_t lds, bool fp64, hipStream_t st) {
+hipError_t launch_wave(const PArgs &a, int spl, size_t lds, bool fp64, int open_tiles, hipStream_t st) {
     PArgs args = a;
     void *kargs[] = {&args};
-    const int groups = (a.n_tiles + kWaveTilesPerWG - 1) / kWaveTilesPerWG;
+    const int per_wg = open_tiles > 0 ? open_tiles : kWaveTilesPerWG;
+    const int groups = (a.n_tiles + per_wg - 1) / per_wg;
     // An ordinary launch: the grid never exceeds what is co-resident (checked
-    // by the host), and every neighbour wait is bounded.
-    return hipLaunchKernel(wave_fn(spl, fp64), dim3(groups), dim3(64 * kWaveTilesPerWG), kargs, (size_t)lds, st);
+    // by the host; with open electrodes no tile waits for another workgroup's),
+    // and every neighbour wait is bounded.
+    return hipLaunchKernel(wave_fn(spl, fp64, open_tiles > 0), dim3(groups), dim3(64 * per_wg), kargs, (size_t)lds, st);
 }
 
-hipError_t wave_capacity(int spl, size_t lds, bool fp64, int *blocks_per_cu) {
-    const void *fn = wave_fn(spl, fp64);
+hipError_t wave_capacity(int spl, size_t lds, bool fp64, int open_tiles, int *blocks_per_cu) {
+    const void *fn = wave_fn(spl, fp64, open_tiles > 0);
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, 64 * kWaveTilesPerWG, lds);
+    const int per_wg = open_tiles > 0 ? open_tiles : kWaveTilesPerWG;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, 64 * per_wg, lds);
 }
 
 }  // namespace kmc
