@@ -188,6 +188,24 @@ def set_bias_protocol(ctx: int, device: int, t_s: Sequence[float], v_volt: Seque
                                        v.ctypes.data_as(C.POINTER(C.c_double)), len(t)))
 
 
+def _one_protocol(protocols) -> bool:
+    """Whether every (times, volts) is the first one, or sequences of Python
+    numbers equal to it (arrays are compared by identity only)."""
+    t0, v0 = protocols[0]
+    plain = all(isinstance(x, (list, tuple)) and all(type(y) in (float, int) for y in x) for x in (t0, v0))
+    for t, v in protocols:
+        if t is t0 and v is v0:
+            continue
+        if not plain or type(t) is not type(t0) or type(v) is not type(v0):
+            return False
+        try:
+            if t != t0 or v != v0:
+                return False
+        except ValueError:                     # an array among the numbers
+            return False
+    return True
+
+
 def run_steps(ctx: int, n_steps: int, net_ptr: int = 0, dec_ptr: int = 0) -> None:
     _check(lib().kmc_run_steps(C.c_void_p(ctx), n_steps, C.c_void_p(net_ptr), C.c_void_p(dec_ptr)))
 
@@ -316,6 +334,12 @@ class Simulator:
         set_bias_protocol(self.ctx, device, t_s, v_volt)
 
     def set_protocols(self, protocols) -> None:
+        # replicas under one protocol take one call, not one per device (4 us
+        # each on the host: 2.1 ms of a training step over 512 replicas)
+        protocols = list(protocols)
+        if len(protocols) == self.n_devices > 1 and _one_protocol(protocols):
+            set_bias_protocol(self.ctx, -1, *protocols[0])
+            return
         for d, (t, v) in enumerate(protocols):
             set_bias_protocol(self.ctx, d, t, v)
 
