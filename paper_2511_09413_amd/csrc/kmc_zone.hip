@@ -3,7 +3,9 @@
 // kmc_zone_* calls.
 //
 // State: the ion-position matrix X [rails][ions] (1-based columns, uint16,
-// strictly increasing along a rail).  One kernel launch per step:
+// strictly increasing along a rail).  Up to 4096 steps per launch with every
+// ion in registers (zone_run) for up to 131072 rails; beyond, one launch per
+// step (zone_step).  A step:
 //   * the step's table comes from the zone populations before the step: the
 //     bias V(t_n), the net drop with the implicit space charge
 //     dV_net(z) = V - f (sum_{z'<z} rho_z' - sum_{z'>z} rho_z'),
