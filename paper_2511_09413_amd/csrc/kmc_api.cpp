@@ -651,7 +651,7 @@ kmc_status bias_flush(kmc_ctx *c) {
 // Whether a run with open electrodes goes by wave tiles: where a device's
 // tiles fit one workgroup (make_wtiles), unless another strategy was asked
 // for.  (kmc_get_launch_mode reports HALF_STEP for every context with open
-// electrodes.)  4 x 64 x 200 in binary64 at 0.15 eV: 42.1 us per step in
+// electrodes.)  4 x 64 x 200 in binary64 at 0.15 eV: 34 us per step in
 // half-step launches with a launch for the boundary bonds each, 14.5 in wave
 // tiles.
 bool open_by_wave(const kmc_ctx *c) {
@@ -719,6 +719,7 @@ ElectrodeArgs electrode_args(kmc_ctx *c, const HopArgs &a) {
     e.ktab64 = a.ktab64;
     e.ktab32 = a.ktab32;
     e.cutoff = a.cutoff;
+    e.rail_range = a.rail_range;
     e.beta = a.beta;
     e.c0 = a.c0;
     e.alpha = a.alpha;

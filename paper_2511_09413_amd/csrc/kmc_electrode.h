@@ -37,7 +37,7 @@ struct ElectrodeArgs {
     const double *knot_t, *knot_v;
     const double *ktab64;
     const float *ktab32;
-    int32_t cutoff;
+    int32_t cutoff, rail_range;
     double beta, c0, alpha, dt;
     uint32_t key0, key1;
     int64_t n;                     // step
