@@ -377,13 +377,18 @@ __device__ void resolve(const DrawArgs &a, DrawLds &w, unsigned char *smem, int 
             // the rows of the left operand: for every survivor, the sums of the
             // rails at each distance
             const int Lp = a.nb * 32, rs = Lp + 8, pieces = Lp / 16;
-            if (me_tid < a.rows * pieces) {  // (at most one piece per thread)
-                const int i = me_tid / pieces, c = me_tid - i * pieces;
+            // 16 sites per thread and turn: rails of up to 512 sites take one
+            // turn, longer ones two where more than half a tile has survivors.
+            // (The rows of a tile do not interact: those without a survivor
+            // are neither staged nor looked at.)
+#pragma unroll 1
+            for (int p = me_tid; p < here * pieces; p += kDrawBlock) {
+                const int i = p / pieces, c = p - i * pieces;
                 // (every load is issued before the first is used, so the
                 // rails that are not wanted are read as the survivor's own)
-                const bool have = i < here && c * 16 < a.pitch;
-                const uint4 v = w.surv[i0 + (have ? i : 0)];
-                const int rr = (int)v.w, R = w.surv_rails[i0 + (have ? i : 0)];
+                const bool have = c * 16 < a.pitch;
+                const uint4 v = w.surv[i0 + i];
+                const int rr = (int)v.w, R = w.surv_rails[i0 + i];
                 const int8_t *base = a.plane + (int64_t)(v.x - v.w) * a.pitch + (have ? c * 16 : 0);
                 // (two groups of loads: all nine rails would not fit the
                 // registers)
