@@ -356,7 +356,7 @@ struct kmc_ctx {
     int64_t bias_set = 0;
     double bias_t[kMaxKnots], bias_v[kMaxKnots];
     bool dr_stale = true, dr_fit = false;  // plan_draws is to run; its answer
-    int dr_per_bin = 1;                // resolving workgroups per column block
+    int dr_bins = 1, dr_per_bin = 1;   // column blocks that hold bonds; resolving workgroups of each
     bool planes_equal = false;         // both state (and potential) planes hold the current state
     bool any_open = false;             // some device has open electrodes: half-step launches or wave tiles (open_by_wave)
     // recording of accepted hops for the score replay (kmc_record_hops), in
@@ -807,9 +807,14 @@ void plan_draws(kmc_ctx *c) {
         mean += rail_mean[d] * (double)dv.rails;
     }
     if (!(mean <= std::min(kDrawMaxMean, (double)c->lay.total_sites / 128.0))) return;
-    // resolving workgroups: about 48 draws each (20 survivors), half the grid at most
-    const int bins = c->dense ? c->lay.dense_nb : 1;
-    c->dr_per_bin = std::max(1, std::min((int)std::ceil(mean / (48.0 * bins)), c->dr_grid / 2 / bins));
+    // resolving workgroups: about 48 draws each (20 survivors), half the grid at
+    // most.  Only the column blocks that hold bonds have any, and the first of
+    // them has a full block's share (all draws for rails of up to 33 sites).
+    const int bonds = c->devs[0].sites - 1;
+    const int bins = c->dense ? (bonds + 31) / 32 : 1;
+    const double share = c->dense ? (double)std::min(bonds, 32) / (double)bonds : 1.0;
+    c->dr_bins = bins;
+    c->dr_per_bin = std::max(1, std::min((int)std::ceil(mean * share / 48.0), c->dr_grid / 2 / bins));
     const int resolvers = bins * c->dr_per_bin, gens = c->dr_grid - resolvers;
     std::vector<double> list(gens, 0.0), take(c->dr_per_bin, 0.0);
     for (int i = 0, d = 0; i < gens; ++i) {
@@ -820,7 +825,7 @@ void plan_draws(kmc_ctx *c) {
             if (c->devs[d].row0 + c->devs[d].rails > to) break;
         }
         if (list[i] > 256.0) return;
-        take[(resolvers + i) % c->dr_per_bin] += list[i] / bins;
+        take[(resolvers + i) % c->dr_per_bin] += list[i] * share;
     }
     for (double x : take)
         if (x > 128.0) return;
@@ -851,7 +856,7 @@ kmc_status enqueue_draws(kmc_ctx *c, const HopArgs &h, const Ctl &ctl, int64_t d
     a.hops = c->at<uint4>(L.dr_hops);
     a.hop_cap = L.dr_hop_cap;
     a.n_hops = c->at<uint32_t>(L.dr_cnt);
-    a.n_bins = c->dense ? L.dense_nb : 1;
+    a.n_bins = c->dr_bins;
     a.per_bin = c->dr_per_bin;
     a.status = c->at<int32_t>(L.status);
     a.tally_net = h.tally_net;

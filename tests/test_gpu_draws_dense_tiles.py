@@ -115,3 +115,32 @@ def test_tiles_of_long_rails(L, m, staged):
     assert most > staged, "no tile with more survivors than one turn stages"
     sim.close()
     twin.close()
+
+
+# rails that fill a few of their padded column blocks, many of them, with close
+# to one draw per 128 sites: the first block's resolving workgroups take nearly
+# all draws (33 sites or fewer), half of them, or a third
+@pytest.mark.parametrize("L,devices", [(20, 51), (33, 31), (40, 26), (65, 16), (129, 8), (140, 7)])
+def test_draws_of_short_rails_fit_their_workgroups(L, devices):
+    from paper_2511_09413_amd import Simulator
+    rails = [1024] * devices
+    n_sites = 1024 * devices * L
+    ph = Physics(precision=BF16X2, seed=9 + L, screening_sites=0.0, cutoff_sites=L - 1, rail_range=1)
+    ph = ph.replace(ea_ev=barrier_for(ph, n_sites / 2, L, 0.985 * min(8192, n_sites / 128)))
+    sim, twin = (Simulator(ph, rails, [L] * devices) for _ in range(2))
+    sim.fill_random([0.3] * devices)
+    sim.set_bias_protocol(*constant(VOLT))
+    occ = sim.read_occupancy().copy()
+    for n in range(2):
+        net = np.zeros(devices, dtype=np.int64)
+        for h in (0, 1):
+            twin.load_occupancy(occ)
+            net += dense_half_step(ph, occ, twin.dense_potential().cpu().numpy(), rails, L, n, h)[0]
+        got, _ = sim.run_steps(1, tallies=True)
+        assert np.array_equal(got.cpu().numpy()[0], net), f"step {n}"
+        assert np.array_equal(sim.read_occupancy(), occ), f"step {n}"
+    # (an overfull list is reported by the next read)
+    sim.run_steps(1000)
+    sim.read_occupancy()
+    sim.close()
+    twin.close()
