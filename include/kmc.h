@@ -479,7 +479,12 @@ kmc_status kmc_zone_set_bias_protocol(kmc_zone_ctx *ctx, const double *t_s, cons
  *   net_dev:  NULL or device int32 [n_steps]: moves toward column 1 minus
  *             moves toward column `sites` in each step.
  *   zone_dev: NULL or device int32 [n_steps][zones]: ions in each zone after
- *             each step (with 10 zones, the deciles of SI S3). */
+ *             each step (with 10 zones, the deciles of SI S3).
+ * Workgroups of a multi-step launch wait for one another's sums.  A wait
+ * declared hung (kmc_zone_set_wait_limit) stops the launch and those enqueued
+ * behind it cleanly: the tally rows of those launches read INT32_MIN, the
+ * state is invalid, and the next kmc_zone_read_positions, kmc_zone_check or
+ * kmc_zone_load_occupancy returns KMC_EHIP and poisons the context. */
 kmc_status kmc_zone_run_steps(kmc_zone_ctx *ctx, int64_t n_steps, int32_t *net_dev, int32_t *zone_dev);
 
 /* Copy X to host int32 [rails][ions_per_rail] (count >= rails * ions).
@@ -492,6 +497,17 @@ kmc_status kmc_zone_read_positions(kmc_zone_ctx *ctx, int32_t *X_host, size_t co
  * holds the GPU can make that happen; the results are the same.  In [0, 10^7]
  * microseconds.  Takes effect for launches enqueued after it. */
 kmc_status kmc_zone_set_gate_limit(kmc_zone_ctx *ctx, int32_t microseconds);
+
+/* Polls of a step's sums before the wait is declared hung (default 2^22, some
+ * seconds; 0 makes every such wait fail at once).  For tests of that path and
+ * for callers that prefer a shorter bound.  Takes effect for launches enqueued
+ * after it. */
+kmc_status kmc_zone_set_wait_limit(kmc_zone_ctx *ctx, int32_t polls);
+
+/* KMC_EHIP (and the context is poisoned) when a wait of the steps enqueued so
+ * far was declared hung, else KMC_OK.  Synchronises.  For callers that read
+ * the occupancy or the tallies from their own device buffers. */
+kmc_status kmc_zone_check(kmc_zone_ctx *ctx);
 
 /* Current step counter of a zone-model context. */
 kmc_status kmc_zone_get_step(kmc_zone_ctx *ctx, int64_t *step);

@@ -116,6 +116,8 @@ def lib():
         L.kmc_zone_read_positions.argtypes = [vp, P(C.c_int32), C.c_size_t]
         L.kmc_zone_get_step.argtypes = [vp, P(C.c_int64)]
         L.kmc_zone_set_gate_limit.argtypes = [vp, C.c_int32]
+        L.kmc_zone_set_wait_limit.argtypes = [vp, C.c_int32]
+        L.kmc_zone_check.argtypes = [vp]
         L.kmc_zone_destroy.argtypes = [vp]
         L.kmc_zone_destroy.restype = None
         L.kmc_fit_decay.argtypes = [P(C.c_double), P(C.c_double), C.c_int64, C.c_double, P(C.c_double),
@@ -133,7 +135,7 @@ def lib():
                      "kmc_record_hops", "kmc_zone_workspace_bytes",
                      "kmc_zone_init", "kmc_zone_load_occupancy", "kmc_zone_set_bias_protocol", "kmc_zone_run_steps",
                      "kmc_zone_read_positions", "kmc_zone_set_gate_limit",
-                     "kmc_zone_get_step"):
+                     "kmc_zone_set_wait_limit", "kmc_zone_check", "kmc_zone_get_step"):
             getattr(L, name).restype = C.c_int
         _LIB = L
     return _LIB
@@ -569,7 +571,13 @@ class ZoneSimulator:
                                              out.size))
         return out
 
+    def set_wait_limit(self, polls: int) -> None:
+        """Polls before a wait between a launch's workgroups is declared hung
+        (kmc_zone_set_wait_limit; 0: every wait fails at once)."""
+        _check(lib().kmc_zone_set_wait_limit(C.c_void_p(self.ctx), polls))
+
     def read_occupancy(self) -> np.ndarray:
+        _check(lib().kmc_zone_check(C.c_void_p(self.ctx)))  # (synchronises)
         self.torch.cuda.current_stream(self.device).synchronize()
         return self.occ.cpu().numpy()
 

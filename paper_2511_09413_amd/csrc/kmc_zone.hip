@@ -332,6 +332,7 @@ constexpr int kZoneRunSteps = 4096;       // steps per launch (the biased sums s
 constexpr int kZonePairsMixed = 1;        // rail pairs of a wavefront whose work is interleaved
 constexpr int kZoneRunMaxPairs = 16;      // rail pairs per wavefront
 constexpr uint32_t kZoneAbort = 0x80000000u;
+constexpr int32_t kZoneNoTally = -2147483647 - 1;
 constexpr int64_t kZoneBias = 1 << 20;    // above any workgroup's change in one step
 
 struct ZoneRunArgs {
@@ -348,10 +349,11 @@ struct ZoneRunArgs {
     int64_t *pop;               // [Z] zone populations, replaced likewise
     unsigned long long *acc;    // [2][kZoneAcc][kZoneAccStride], zero on entry
     uint32_t *gate;             // arrivals, and kZoneAbort when the launch left undone; zero on entry
-    int32_t *bad;               // raised when a wait of the loop timed out
+    int32_t *bad;               // raised when a wait of the loop timed out; while it is, launches leave at once
     int32_t *net_out, *zone_out;
     int64_t *net_total;
     int32_t gate_ticks;         // 10 ns ticks a workgroup waits at the gate
+    int32_t wait_limit;         // polls of a step's sums before the wait counts as hung
 };
 
 // The kernel arguments, read again from the argument segment where a step's
@@ -519,7 +521,7 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
             __builtin_amdgcn_s_sleep(1);
             seen = __hip_atomic_load(a.gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        s.go = seen & kZoneAbort ? 0 : 1;
+        s.go = (seen & kZoneAbort) || __hip_atomic_load(a.bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 0 : 1;
     }
     zone_setup(a, s, zone_at);
     if (!s.go) return;
@@ -595,7 +597,7 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
             int spins = 0;
             while (((v = __hip_atomic_load(rows_at + row * kZoneAccStride + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >>
                     40) != want) {
-                if (++spins > (1 << 22)) {
+                if (++spins > ka->wait_limit) {
                     s.go = 0;
                     __hip_atomic_store(ka->bad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     break;
@@ -607,9 +609,9 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
             s.before[par][e] = low;
         }
         kmc::lds_barrier();
+        if (!s.go) return;
         zone_end_step(s, k, V, blockIdx.x == 0);
         kmc::lds_barrier();
-        if (!s.go) return;
     }
 #pragma unroll
     for (int k = 0; k < P; ++k) {
@@ -624,11 +626,18 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
 
 // Behind every zone_run: the same steps in one workgroup when the launch left
 // them undone (the ions in memory), and the accumulators and the gate cleared
-// for the next launch.
+// for the next launch.  After a timed-out wait nothing is run; the tally rows
+// of the launch read kZoneNoTally.
 __global__ __launch_bounds__(1024) void zone_rescue(ZoneRunArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
-    const bool undone = (*a.gate & kZoneAbort) != 0;
+    const bool bad = *a.bad != 0;
+    const bool undone = (*a.gate & kZoneAbort) != 0 && !bad;
+    if (bad) {
+        for (int i = tid; a.net_out && i < a.n_steps; i += blockDim.x) a.net_out[a.row0 + i] = kZoneNoTally;
+        for (int i = tid; a.zone_out && i < a.n_steps * a.zones; i += blockDim.x)
+            a.zone_out[a.row0 * a.zones + i] = kZoneNoTally;
+    }
     if (undone) {
         ZoneLds &s = *reinterpret_cast<ZoneLds *>(smem);
         uint8_t *zone_at = smem + sizeof(ZoneLds);
@@ -767,6 +776,7 @@ struct kmc_zone_ctx {
     // workspace layout
     int cus = 0;                // compute units of the GPU (0: the runs go step by step)
     int32_t gate_ticks = 10000000;  // 0.1 s
+    int32_t wait_limit = 1 << 22;
     size_t off_X, off_pop, off_table, off_bucket, off_ticket, off_knots, off_total, off_bad, off_acc, total;
     template <typename T>
     T *at(size_t off) { return reinterpret_cast<T *>(ws + off); }
@@ -900,6 +910,17 @@ int zone_run_cus(int sites) {
     return cus;
 }
 
+// Whether a wait between workgroups of the runs enqueued so far timed out
+// (synchronises).  The state is then invalid and the context of no use.
+kmc_status zone_check(kmc_zone_ctx *c) {
+    int32_t timed_out = 0;
+    ZONE_HIP(c, hipMemcpyAsync(&timed_out, c->at<int32_t>(c->off_bad) + 2, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+    ZONE_HIP(c, hipStreamSynchronize(c->stream));
+    if (!timed_out) return KMC_OK;
+    c->poisoned = true;
+    return record_error(KMC_EHIP, "zone kernel: a wait between workgroups timed out; state is invalid");
+}
+
 // The caller's occupancy after a run of n_steps.
 kmc_status zone_export_state(kmc_zone_ctx *c, int64_t n_steps) {
     hipLaunchKernelGGL(zone_export, dim3((unsigned)((c->p.rails + 3) / 4)), dim3(256), 0, c->stream,
@@ -994,6 +1015,7 @@ kmc_status kmc_zone_init(const kmc_zone_params *params, int8_t *occ_dev, void *w
 kmc_status kmc_zone_load_occupancy(kmc_zone_ctx *c) {
     kmc_status s = zone_usable(c);
     if (s != KMC_OK) return s;
+    if ((s = zone_check(c)) != KMC_OK) return s;
     return zone_load(c);
 }
 
@@ -1074,6 +1096,7 @@ kmc_status kmc_zone_run_steps(kmc_zone_ctx *c, int64_t n_steps, int32_t *net_dev
         r.zone_out = zone_dev;
         r.net_total = a.net_total;
         r.gate_ticks = c->gate_ticks;
+        r.wait_limit = c->wait_limit;
         const size_t lds = zone_run_lds(c->p.sites);
         for (int64_t k = 0; k < n_steps; k += kZoneRunSteps) {
             r.n0 = c->n + k;
@@ -1108,18 +1131,13 @@ kmc_status kmc_zone_read_positions(kmc_zone_ctx *c, int32_t *X_host, size_t coun
     if (!X_host) return record_error(KMC_EINVAL, "X_host is NULL");
     const size_t n = (size_t)c->p.rails * (size_t)c->p.ions_per_rail;
     if (count < n) return record_error(KMC_ETOOSMALL, "X_host holds fewer than rails * ions_per_rail entries");
-    int32_t timed_out = 0;
-    ZONE_HIP(c, hipMemcpyAsync(&timed_out, c->at<int32_t>(c->off_bad) + 2, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+    if ((s = zone_check(c)) != KMC_OK) return s;
     std::vector<uint16_t> tmp(n);
     if (n > 0) {
         ZONE_HIP(c, hipMemcpyAsync(tmp.data(), c->at<uint16_t>(c->off_X), sizeof(uint16_t) * n, hipMemcpyDeviceToHost,
                                    c->stream));
     }
     ZONE_HIP(c, hipStreamSynchronize(c->stream));
-    if (timed_out) {
-        c->poisoned = true;
-        return record_error(KMC_EHIP, "zone kernel: a wait between workgroups timed out; state is invalid");
-    }
     for (size_t i = 0; i < n; ++i) X_host[i] = tmp[i];
     return KMC_OK;
 }
@@ -1130,6 +1148,19 @@ kmc_status kmc_zone_set_gate_limit(kmc_zone_ctx *c, int32_t microseconds) {
     if (microseconds < 0 || microseconds > 10000000) return record_error(KMC_EINVAL, "microseconds must be in [0, 10^7]");
     c->gate_ticks = microseconds * 100;
     return KMC_OK;
+}
+
+kmc_status kmc_zone_set_wait_limit(kmc_zone_ctx *c, int32_t polls) {
+    kmc_status s = zone_usable(c);
+    if (s != KMC_OK) return s;
+    if (polls < 0) return record_error(KMC_EINVAL, "polls must be >= 0");
+    c->wait_limit = polls;
+    return KMC_OK;
+}
+
+kmc_status kmc_zone_check(kmc_zone_ctx *c) {
+    kmc_status s = zone_usable(c);
+    return s != KMC_OK ? s : zone_check(c);
 }
 
 kmc_status kmc_zone_get_step(kmc_zone_ctx *c, int64_t *step) {
