@@ -491,11 +491,12 @@ kmc_status kmc_zone_run_steps(kmc_zone_ctx *ctx, int64_t n_steps, int32_t *net_d
  * Synchronises. */
 kmc_status kmc_zone_read_positions(kmc_zone_ctx *ctx, int32_t *X_host, size_t count);
 
-/* How long the workgroups of a multi-step launch wait for one another to be
- * resident before they leave the steps to a single workgroup (default 100 ms;
- * 0: a launch of more than one workgroup leaves at once).  Other work that
- * holds the GPU can make that happen; the results are the same.  In [0, 10^7]
- * microseconds.  Takes effect for launches enqueued after it. */
+/* How long at most the workgroups of a multi-step launch wait for one another
+ * to be resident before they leave its steps to a queue of tiles that any free
+ * part of the GPU takes (default 100 ms, and never longer than 10 us per step of
+ * the launch or 160 us; 0: a launch of more than one workgroup leaves at once).
+ * Other work that holds the GPU can make that happen; the results are the same.
+ * In [0, 10^7] microseconds.  Takes effect for launches enqueued after it. */
 kmc_status kmc_zone_set_gate_limit(kmc_zone_ctx *ctx, int32_t microseconds);
 
 /* Polls of a step's sums before the wait is declared hung (default 2^22, some

@@ -561,8 +561,8 @@ class ZoneSimulator:
         return net, zones
 
     def set_gate_limit(self, microseconds: int) -> None:
-        """Wait for a multi-step launch's workgroups to be resident together
-        (kmc_zone_set_gate_limit; 0: leave the steps to one workgroup)."""
+        """Longest wait for a multi-step launch's workgroups to be resident
+        together (kmc_zone_set_gate_limit; 0: leave the steps to the queue)."""
         _check(lib().kmc_zone_set_gate_limit(C.c_void_p(self.ctx), microseconds))
 
     def read_positions(self) -> np.ndarray:

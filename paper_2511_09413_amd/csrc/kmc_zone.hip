@@ -37,6 +37,7 @@
 #include "kmc_device.h"
 #include "kmc_internal.h"
 #include "kmc_philox.h"
+#include "kmc_queue.h"
 
 namespace kmc {
 kmc_status record_error(kmc_status s, const std::string &msg);
@@ -321,17 +322,15 @@ __global__ __launch_bounds__(kZoneBlock) void zone_step(ZoneArgs a) {
 // about 120 instructions per rail pair).
 //
 // The launch needs all its workgroups resident at once.  It is sized for an
-// idle GPU; when other work holds the CUs, the workgroups first meet at a gate,
-// and if they have not all arrived after a bounded time they leave without
-// having changed anything (one atomic word decides, so all leave or none).
-// zone_rescue, launched behind it, then runs the same steps in one workgroup,
-// which needs no other workgroup to make progress.
+// idle GPU; where other work holds CUs its workgroups leave at the gate
+// (kmc_queue.h) and zone_queue, launched behind it, takes the same steps tile by
+// tile with the ions in memory, on whatever part of the GPU is free.
 constexpr int kZoneAcc = 8;               // accumulator rows (workgroup index modulo 8: one XCD each)
 constexpr int kZoneAccStride = 72;        // 64-bit words per row (zones, then net)
 constexpr int kZoneRunSteps = 4096;       // steps per launch (the biased sums stay below 2^40)
 constexpr int kZonePairsMixed = 1;        // rail pairs of a wavefront whose work is interleaved
 constexpr int kZoneRunMaxPairs = 16;      // rail pairs per wavefront
-constexpr uint32_t kZoneAbort = 0x80000000u;
+constexpr int64_t kZoneGateTicks = 1000;  // 10 us per step: what the wait at the gate may cost
 constexpr int32_t kZoneNoTally = -2147483647 - 1;
 constexpr int64_t kZoneBias = 1 << 20;    // above any workgroup's change in one step
 
@@ -348,7 +347,10 @@ struct ZoneRunArgs {
     double *table;              // [2][Z] of the first step; replaced by the one after the last step
     int64_t *pop;               // [Z] zone populations, replaced likewise
     unsigned long long *acc;    // [2][kZoneAcc][kZoneAccStride], zero on entry
-    uint32_t *gate;             // arrivals, and kZoneAbort when the launch left undone; zero on entry
+    kmc::QueueWords *queue;     // zero on entry
+    unsigned long long *acc_next;   // the following launch's, cleared by this one
+    kmc::QueueWords *queue_next;
+    int32_t tile_pairs, n_tiles;    // zone_queue: rail pairs per tile, tiles
     int32_t *bad;               // raised when a wait of the loop timed out; while it is, launches leave at once
     int32_t *net_out, *zone_out;
     int64_t *net_total;
@@ -377,6 +379,7 @@ struct ZoneLds {
     double kt[kMaxKnots], kv[kMaxKnots];
     int64_t net;
     int32_t go;
+    uint32_t ticket, last;             // zone_queue
 };
 
 constexpr uint64_t kFirstLanes = 0x0000000100000001ull, kLastLanes = 0x8000000080000000ull;
@@ -448,7 +451,10 @@ __device__ inline void zone_setup(const ZoneRunArgs &a, ZoneLds &s, uint8_t *zon
 }
 
 // The end of step k in the first wavefront: populations, the output row (one
-// workgroup), the thresholds of step k + 1; V is the bias at that step.
+// workgroup), the thresholds of step k + 1; V is the bias at that step.  kEach:
+// the workgroup ends this step alone, so its populations, table and net hops go
+// to memory now, else after the launch's last step.
+template <bool kEach>
 __device__ inline void zone_end_step(ZoneLds &s, int k, double V, bool writer) {
     const ZoneKArgs ap = zone_kargs();
     const auto &a = *ap;
@@ -482,7 +488,11 @@ __device__ inline void zone_end_step(ZoneLds &s, int k, double V, bool writer) {
         s.thr[1][tid] = word_threshold(pl);
         if (writer) {
             if (a.zone_out) a.zone_out[(a.row0 + k) * Z + tid] = (int32_t)pop;
-            if (k == a.n_steps - 1) {
+            if (kEach) {
+                kmc::queue_store(a.pop + tid, pop);
+                kmc::queue_store(a.table + tid, pl);
+                kmc::queue_store(a.table + Z + tid, pr);
+            } else if (k == a.n_steps - 1) {
                 a.pop[tid] = pop;
                 a.table[tid] = pl;
                 a.table[Z + tid] = pr;
@@ -492,8 +502,15 @@ __device__ inline void zone_end_step(ZoneLds &s, int k, double V, bool writer) {
     if (writer && tid == 0) {
         s.net += net;
         if (a.net_out) a.net_out[a.row0 + k] = net;
-        if (k == a.n_steps - 1) *a.net_total += s.net;
+        if (kEach) atomicAdd(reinterpret_cast<unsigned long long *>(a.net_total), (unsigned long long)(int64_t)net);
+        else if (k == a.n_steps - 1) *a.net_total += s.net;
     }
+}
+
+// The accumulators and queue words of one launch, by one workgroup.
+__device__ inline void zone_clear(unsigned long long *acc, kmc::QueueWords *queue) {
+    for (int i = threadIdx.x; i < 2 * kZoneAcc * kZoneAccStride; i += blockDim.x) acc[i] = 0;
+    for (int i = threadIdx.x; i < kmc::kQueueWords; i += blockDim.x) reinterpret_cast<uint32_t *>(queue)[i] = 0u;
 }
 
 template <int P>
@@ -504,25 +521,11 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int waves = blockDim.x >> 6;
-    // the gate: all workgroups are resident, or none runs
-    if (tid == 0) {
-        uint32_t seen = __hip_atomic_fetch_add(a.gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-        while (!(seen & kZoneAbort) && seen < gridDim.x) {
-            if ((int64_t)(__builtin_amdgcn_s_memrealtime() - t0) >= (int64_t)a.gate_ticks) {
-                // give up, unless the last workgroup arrives first
-                uint32_t expect = seen;
-                if (__hip_atomic_compare_exchange_strong(a.gate, &expect, seen | kZoneAbort, __ATOMIC_RELAXED,
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                    expect = seen | kZoneAbort;
-                seen = expect;
-                continue;
-            }
-            __builtin_amdgcn_s_sleep(1);
-            seen = __hip_atomic_load(a.gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        s.go = (seen & kZoneAbort) || __hip_atomic_load(a.bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 0 : 1;
-    }
+    // all workgroups are resident, or none runs
+    if (tid == 0)
+        s.go = kmc::queue_gate(a.queue->gate, gridDim.x, a.gate_ticks) &&
+               !__hip_atomic_load(a.bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (blockIdx.x == 0) zone_clear(a.acc_next, a.queue_next);
     zone_setup(a, s, zone_at);
     if (!s.go) return;
 
@@ -589,6 +592,9 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
         double V = 0.0;
         if (tid < 64) V = protocol_voltage(s.kt, s.kv, ka->n_knots, (double)(ka->n0 + k + 1 - ka->n_set) * ka->dt);
         const int words = min((int)gridDim.x, kZoneAcc) * (Z + 1);
+        // (after a hung wait the remaining steps run through without waiting,
+        // and nothing of them is used)
+        const int limit = s.go ? ka->wait_limit : 0;
         for (int e = tid; e < words; e += blockDim.x) {
             const int row = e / (Z + 1), q = e - row * (Z + 1);
             const int64_t members = ((int)gridDim.x - row + kZoneAcc - 1) / kZoneAcc;
@@ -597,9 +603,9 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
             int spins = 0;
             while (((v = __hip_atomic_load(rows_at + row * kZoneAccStride + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >>
                     40) != want) {
-                if (++spins > ka->wait_limit) {
+                if (++spins > limit) {
                     s.go = 0;
-                    __hip_atomic_store(ka->bad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(zone_kargs()->bad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
@@ -609,8 +615,7 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
             s.before[par][e] = low;
         }
         kmc::lds_barrier();
-        if (!s.go) return;
-        zone_end_step(s, k, V, blockIdx.x == 0);
+        zone_end_step<false>(s, k, V, blockIdx.x == 0);
         kmc::lds_barrier();
     }
 #pragma unroll
@@ -624,61 +629,96 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
     }
 }
 
-// Behind every zone_run: the same steps in one workgroup when the launch left
-// them undone (the ions in memory), and the accumulators and the gate cleared
-// for the next launch.  After a timed-out wait nothing is run; the tally rows
-// of the launch read kZoneNoTally.
-__global__ __launch_bounds__(1024) void zone_rescue(ZoneRunArgs a) {
+// Behind every zone_run: the same steps when the launch left them undone, from
+// a queue of tiles (kmc_queue.h) with the ions in memory.  The workgroup that
+// completes a step's last tile sums the step's changes, writes its output row
+// and the next step's table, and publishes the step.  After a timed-out wait
+// nothing is run, and the tally rows of the launch read kZoneNoTally.
+__global__ __launch_bounds__(1024) void zone_queue(ZoneRunArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
-    const bool bad = *a.bad != 0;
-    const bool undone = (*a.gate & kZoneAbort) != 0 && !bad;
-    if (bad) {
+    if (*a.bad != 0) {
+        if (blockIdx.x != 0) return;
         for (int i = tid; a.net_out && i < a.n_steps; i += blockDim.x) a.net_out[a.row0 + i] = kZoneNoTally;
         for (int i = tid; a.zone_out && i < a.n_steps * a.zones; i += blockDim.x)
             a.zone_out[a.row0 * a.zones + i] = kZoneNoTally;
+        return;
     }
-    if (undone) {
-        ZoneLds &s = *reinterpret_cast<ZoneLds *>(smem);
-        uint8_t *zone_at = smem + sizeof(ZoneLds);
-        const int lane = tid & 63, half = lane >> 5, l = lane & 31, j0 = 2 * l, j1 = 2 * l + 1, Z = a.zones;
-        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        zone_setup(a, s, zone_at);
-        const int64_t pairs = ((int64_t)a.rails + 1) / 2;
-        const uint32_t wall = (uint32_t)a.sites + 1u;
-        const PhiloxLane lc = philox_lane((uint32_t)l, 2u << 1, a.key0, a.key1);
-            for (int k = 0; k < a.n_steps; ++k) {
-            const int par = k & 1;
-            const PhiloxStep sc = philox_step(lc, (uint32_t)(a.n0 + k), a.key0, a.key1);
-            int net = 0;
-            for (int64_t pr = wave; pr < pairs; pr += blockDim.x >> 6) {
-                const int64_t rail = 2 * pr + half;
-                const bool h0 = rail < a.rails && j0 < a.ions, h1 = rail < a.rails && j1 < a.ions;
-                uint16_t *row = a.X + rail * a.ions;
-                uint32_t x0 = h0 ? row[j0] : wall, x1 = h1 ? row[j1] : wall;
-                uint32_t z0 = zone_at[x0], z1 = zone_at[x1];
-                const uint4 w = philox_words(lc, sc, (uint32_t)rail, a.key0, a.key1);
-                net += zone_pair(x0, x1, z0, z1, w, __ballot(h0), __ballot(h1), wall, l == 31, &s.thr[0][0], s.dpop[par],
-                                 zone_at);
-                if (h0) row[j0] = (uint16_t)x0;
-                if (h1) row[j1] = (uint16_t)x1;
-            }
-            if (lane == 0 && net != 0) atomicAdd(&s.dnet[par], net);
-            __syncthreads();
-            if (tid <= Z) {
-                int32_t *at = tid < Z ? &s.dpop[par][tid] : &s.dnet[par];
-                s.sum[par][tid] = *at;
-                *at = 0;
-            }
-            __syncthreads();
-            const double V = protocol_voltage(s.kt, s.kv, a.n_knots, (double)(a.n0 + k + 1 - a.n_set) * a.dt);
-            zone_end_step(s, k, V, true);
-            __syncthreads();
+    if ((a.queue->gate[0] & kmc::kQueueAbort) == 0) return;
+    ZoneLds &s = *reinterpret_cast<ZoneLds *>(smem);
+    uint8_t *zone_at = smem + sizeof(ZoneLds);
+    const int lane = tid & 63, half = lane >> 5, l = lane & 31, j0 = 2 * l, j1 = 2 * l + 1, Z = a.zones;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    zone_setup(a, s, zone_at);
+    const int pairs = (a.rails + 1) / 2;
+    const uint32_t wall = (uint32_t)a.sites + 1u;
+    const PhiloxLane lc = philox_lane((uint32_t)l, 2u << 1, a.key0, a.key1);
+    unsigned long long *row_of_wg = a.acc + (blockIdx.x % kZoneAcc) * kZoneAccStride;
+    int at_step = -1;  // whose thresholds the LDS holds
+    for (;;) {
+        if (tid == 0) {
+            const uint32_t v = __hip_atomic_fetch_add(a.queue->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s.ticket = v;
+            s.go = v < (uint32_t)a.n_steps * (uint32_t)a.n_tiles &&
+                   kmc::queue_wait(a.queue->ready, v / (uint32_t)a.n_tiles, a.bad, a.wait_limit);
         }
+        __syncthreads();
+        if (!s.go) return;
+        const int k = (int)(s.ticket / (uint32_t)a.n_tiles), tile = (int)(s.ticket - (uint32_t)k * (uint32_t)a.n_tiles);
+        if (k != at_step && tid < Z) {
+            s.thr[0][tid] = word_threshold(kmc::queue_load(a.table + Z + tid));
+            s.thr[1][tid] = word_threshold(kmc::queue_load(a.table + tid));
+        }
+        at_step = k;
+        __syncthreads();
+        const PhiloxStep sc = philox_step(lc, (uint32_t)(a.n0 + k), a.key0, a.key1);
+        int net = 0;
+        const int end = min(pairs, (tile + 1) * a.tile_pairs);
+        for (int pr = tile * a.tile_pairs + wave; pr < end; pr += blockDim.x >> 6) {
+            const int rail = 2 * pr + half;
+            const bool h0 = rail < a.rails && j0 < a.ions, h1 = rail < a.rails && j1 < a.ions;
+            uint16_t *row = a.X + (int64_t)rail * a.ions;
+            uint32_t x0 = h0 ? kmc::queue_load(row + j0) : wall, x1 = h1 ? kmc::queue_load(row + j1) : wall;
+            uint32_t z0 = zone_at[x0], z1 = zone_at[x1];
+            const uint4 w = philox_words(lc, sc, (uint32_t)rail, a.key0, a.key1);
+            net += zone_pair(x0, x1, z0, z1, w, __ballot(h0), __ballot(h1), wall, l == 31, &s.thr[0][0], s.dpop[0], zone_at);
+            if (h0) kmc::queue_store(row + j0, (uint16_t)x0);
+            if (h1) kmc::queue_store(row + j1, (uint16_t)x1);
+        }
+        if (lane == 0 && net != 0) atomicAdd(&s.dnet[0], net);
+        __syncthreads();
+        unsigned long long *sums = a.acc + (k & 1) * kZoneAcc * kZoneAccStride;
+        if (tid <= Z) {
+            int32_t *at = tid < Z ? &s.dpop[0][tid] : &s.dnet[0];
+            const int64_t v = *at;
+            *at = 0;
+            if (v != 0) atomicAdd(row_of_wg + (k & 1) * kZoneAcc * kZoneAccStride + tid, (unsigned long long)v);
+        }
+        kmc::queue_stores_done();
+        if (tid == 0)
+            s.last = __hip_atomic_fetch_add(a.queue->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+                     (uint32_t)(k + 1) * (uint32_t)a.n_tiles;
+        __syncthreads();
+        if (!s.last) continue;
+        // every tile of step k is done
+        if (tid < Z) s.pop[tid] = (int32_t)kmc::queue_load(a.pop + tid);
+        if (tid <= Z) {
+            int64_t sum = 0;
+            for (int r = 0; r < kZoneAcc; ++r) {
+                unsigned long long *p = sums + r * kZoneAccStride + tid;
+                sum += (int64_t)__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(p, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            s.sum[k & 1][tid] = (int32_t)sum;
+        }
+        __syncthreads();
+        const double V = protocol_voltage(s.kt, s.kv, a.n_knots, (double)(a.n0 + k + 1 - a.n_set) * a.dt);
+        zone_end_step<true>(s, k, V, true);
+        kmc::queue_stores_done();
+        if (tid == 0)
+            __hip_atomic_store(a.queue->ready, (uint32_t)(k + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        at_step = k + 1;  // zone_end_step left its thresholds in the LDS
     }
-    for (int i = tid; i < 2 * kZoneAcc * kZoneAccStride; i += blockDim.x) a.acc[i] = 0;
-    __syncthreads();
-    if (tid == 0) *a.gate = 0;
 }
 
 // The table of the step n from the populations pop (one workgroup).
@@ -732,8 +772,12 @@ __global__ __launch_bounds__(256) void zone_import(const int8_t *occ, uint16_t *
 }
 
 // Caller occupancy from the ion-position matrix (one wavefront per rail).
-__global__ __launch_bounds__(256) void zone_export(const uint16_t *X, int8_t *occ, int rails, int sites, int ions) {
+// The first workgroup clears the words of the call's multi-step launches.
+__global__ __launch_bounds__(256) void zone_export(const uint16_t *X, int8_t *occ, int rails, int sites, int ions,
+                                                  unsigned long long *acc, kmc::QueueWords *queue) {
     const int lane = threadIdx.x & 63;
+    if (blockIdx.x == 0)
+        for (int i = 0; i < 2; ++i) zone_clear(acc + i * 2 * kZoneAcc * kZoneAccStride, queue + i);
     const int64_t rail = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (rail >= rails) return;
     int8_t *dst = occ + rail * sites;
@@ -777,7 +821,7 @@ struct kmc_zone_ctx {
     int cus = 0;                // compute units of the GPU (0: the runs go step by step)
     int32_t gate_ticks = 10000000;  // 0.1 s
     int32_t wait_limit = 1 << 22;
-    size_t off_X, off_pop, off_table, off_bucket, off_ticket, off_knots, off_total, off_bad, off_acc, total;
+    size_t off_X, off_pop, off_table, off_bucket, off_ticket, off_knots, off_total, off_bad, off_acc, off_queue, total;
     template <typename T>
     T *at(size_t off) { return reinterpret_cast<T *>(ws + off); }
 };
@@ -817,8 +861,10 @@ void zone_layout(kmc_zone_ctx *c) {
     c->off_ticket = take(sizeof(uint32_t) * (kZoneBuckets + 1) * 32);
     c->off_knots = take(sizeof(double) * 2 * kMaxKnots);
     c->off_total = take(sizeof(int64_t));
-    c->off_bad = take(sizeof(int32_t) * 4);  // rejected occupancy, -, timed-out wait, gate
-    c->off_acc = take(sizeof(uint64_t) * 2 * kZoneAcc * kZoneAccStride);
+    c->off_bad = take(sizeof(int32_t) * 4);  // rejected occupancy, -, timed-out wait, -
+    // (two sets, used in turn by the launches of a call)
+    c->off_acc = take(sizeof(uint64_t) * 2 * 2 * kZoneAcc * kZoneAccStride);
+    c->off_queue = take(sizeof(kmc::QueueWords) * 2);
     c->total = off;
 }
 
@@ -900,7 +946,7 @@ int zone_run_cus(int sites) {
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return 0;
     const size_t lds = zone_run_lds(sites);
-    if (hipFuncSetAttribute((const void *)zone_rescue, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
+    if (hipFuncSetAttribute((const void *)zone_queue, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
     for (int per = 1; per <= kZoneRunMaxPairs; per *= 2) {
         int blocks = 0;
         if (hipFuncSetAttribute(zone_run_fn(per), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
@@ -924,7 +970,8 @@ kmc_status zone_check(kmc_zone_ctx *c) {
 // The caller's occupancy after a run of n_steps.
 kmc_status zone_export_state(kmc_zone_ctx *c, int64_t n_steps) {
     hipLaunchKernelGGL(zone_export, dim3((unsigned)((c->p.rails + 3) / 4)), dim3(256), 0, c->stream,
-                       c->at<uint16_t>(c->off_X), c->occ_user, c->p.rails, c->p.sites, c->p.ions_per_rail);
+                       c->at<uint16_t>(c->off_X), c->occ_user, c->p.rails, c->p.sites, c->p.ions_per_rail,
+                       c->at<unsigned long long>(c->off_acc), c->at<kmc::QueueWords>(c->off_queue));
     ZONE_HIP(c, hipGetLastError());
     c->n += n_steps;
     return KMC_OK;
@@ -999,8 +1046,8 @@ kmc_status kmc_zone_init(const kmc_zone_params *params, int8_t *occ_dev, void *w
     if ((s = zone_hip(c, zone_fill(c->at<int64_t>(c->off_total), 1, 0, c->stream), "clear total")) != KMC_OK)
         return fail_init(s);
     if ((s = zone_hip(c, zone_fill(c->at<int64_t>(c->off_bad), 2, 0, c->stream), "clear flags")) != KMC_OK) return fail_init(s);
-    if ((s = zone_hip(c, zone_fill(c->at<int64_t>(c->off_acc), 2 * kZoneAcc * kZoneAccStride, 0, c->stream),
-                      "clear accumulators")) != KMC_OK)
+    if ((s = zone_hip(c, zone_fill(c->at<int64_t>(c->off_acc), (int64_t)(c->total - c->off_acc) / 8, 0, c->stream),
+                      "clear accumulators and queue words")) != KMC_OK)
         return fail_init(s);
     c->cus = zone_run_cus(c->p.sites);
     ZoneKnots k{};
@@ -1089,22 +1136,30 @@ kmc_status kmc_zone_run_steps(kmc_zone_ctx *c, int64_t n_steps, int32_t *net_dev
         r.n_set = a.n_set;
         r.table = c->at<double>(c->off_table) + c->cur * 2 * kZoneMaxZones;
         r.pop = c->at<int64_t>(c->off_pop) + c->cur * kZoneMaxZones;
-        r.acc = c->at<unsigned long long>(c->off_acc);
         r.bad = c->at<int32_t>(c->off_bad) + 2;
-        r.gate = reinterpret_cast<uint32_t *>(c->at<int32_t>(c->off_bad) + 3);
         r.net_out = net_dev;
         r.zone_out = zone_dev;
         r.net_total = a.net_total;
-        r.gate_ticks = c->gate_ticks;
         r.wait_limit = c->wait_limit;
+        r.tile_pairs = (int32_t)std::max<int64_t>((pairs + shape.grid - 1) / shape.grid, 16);
+        r.n_tiles = (int32_t)((pairs + r.tile_pairs - 1) / r.tile_pairs);
         const size_t lds = zone_run_lds(c->p.sites);
         for (int64_t k = 0; k < n_steps; k += kZoneRunSteps) {
             r.n0 = c->n + k;
             r.row0 = k;
             r.n_steps = (int32_t)std::min<int64_t>(kZoneRunSteps, n_steps - k);
+            r.gate_ticks = (int32_t)std::min<int64_t>(c->gate_ticks, kZoneGateTicks * std::max(r.n_steps, 16));
+            unsigned long long *acc = c->at<unsigned long long>(c->off_acc);
+            kmc::QueueWords *queue = c->at<kmc::QueueWords>(c->off_queue);
+            const int set = (int)(k / kZoneRunSteps) & 1;
+            r.acc = acc + set * 2 * kZoneAcc * kZoneAccStride;
+            r.queue = queue + set;
+            r.acc_next = acc + (1 - set) * 2 * kZoneAcc * kZoneAccStride;
+            r.queue_next = queue + (1 - set);
             void *kargs[] = {&r};
             ZONE_HIP(c, hipLaunchKernel(zone_run_fn(shape.pairs), dim3(shape.grid), dim3(shape.block), kargs, lds, c->stream));
-            ZONE_HIP(c, hipLaunchKernel((const void *)zone_rescue, dim3(1), dim3(1024), kargs, lds, c->stream));
+            ZONE_HIP(c, hipLaunchKernel((const void *)zone_queue, dim3((unsigned)std::min<int64_t>(r.n_tiles, shape.grid)),
+                                        dim3(1024), kargs, lds, c->stream));
         }
         return zone_export_state(c, n_steps);
     }

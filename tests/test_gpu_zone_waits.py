@@ -1,12 +1,17 @@
-"""A zone-model run whose workgroups' wait for one another is declared hung (the
-limit is set to no polls on the host; every kernel ends normally): each reader
-reports it and nothing goes on from the invalid state (needs an MI355X)."""
+"""Zone-model runs whose workgroups cannot wait for one another (needs an MI355X).
+
+* A wait that is declared hung (the limit is set to no polls on the host; every
+  kernel ends normally): each reader reports it and nothing goes on from the
+  invalid state.
+* A launch that leaves at its gate (the limit is set to no time): its steps are
+  taken from the queue of tiles, with the oracle's trajectory."""
 import numpy as np
 import pytest
 
+import oracle
 from parity_util import gpu_available
 from test_gpu_zone import _pair
-from workloads import constant
+from workloads import constant, step_then_relax, triangle
 
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
@@ -33,4 +38,24 @@ def test_a_hung_wait_is_reported(reader):
     with pytest.raises(KmcError) as e:
         sim.run_steps(1)
     assert e.value.status == KMC_ESTATE
+    sim.close()
+
+
+# one tile and two; a tile's last pair without its second rail; a workgroup per
+# compute unit with one and with two rail pairs per wavefront, most rails; more
+# steps than a launch takes; every lane and zone
+@pytest.mark.parametrize("rails,sites,ions,zones,steps", [
+    (33, 24, 9, 5, 40), (35, 24, 9, 5, 40), (601, 50, 21, 10, 4100), (4097, 24, 9, 5, 12), (12345, 70, 64, 64, 12),
+    (131072, 24, 9, 5, 6)])
+def test_steps_from_the_queue(rails, sites, ions, zones, steps):
+    sim, p, X = _pair(rails, sites, ions, zones, 0.8, 1e-5, seed=rails)
+    proto = triangle(4.0, 0.06) if zones > 5 else step_then_relax(4.0, 0.004)
+    sim.set_bias_protocol(*proto)
+    for limit, chunk in ((0, steps), (100000, 3), (0, 2)):
+        sim.set_gate_limit(limit)
+        net, zon = sim.run_steps(chunk, tallies=True)
+        out = oracle.zone_run(p, proto, X, sim.step - chunk, chunk)
+        assert np.array_equal(net.cpu().numpy(), out["net"])
+        assert np.array_equal(zon.cpu().numpy(), out["zones"])
+        assert np.array_equal(sim.read_positions(), X)
     sim.close()
