@@ -62,6 +62,7 @@ constexpr int kZoneBucketStride = 128;  // int64 per bucket row (zones, then net
 constexpr int kZoneBlock = 256;
 constexpr int kZoneMaxGrid = 2048;
 
+constexpr int32_t kZoneNoTally = -2147483647 - 1;  // tally rows of launches after a timed-out wait
 constexpr int kZonePairsPerIter = 4;  // rail pairs a wavefront loads before computing them
 
 struct ZoneArgs {
@@ -82,6 +83,7 @@ struct ZoneArgs {
     int32_t *net_out;           // caller [n_steps] or null
     int32_t *zone_out;          // caller [n_steps][Z] or null
     int64_t *net_total;         // running total of the net hops
+    const int32_t *bad;         // raised by a timed-out wait of an earlier launch: nothing is run
 };
 
 __device__ __forceinline__ int zone_of(int x, int sites, int zones) {
@@ -142,6 +144,11 @@ __global__ __launch_bounds__(kZoneBlock) void zone_step(ZoneArgs a) {
     __shared__ uint32_t s_last;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int Z = a.zones;
+    if (*a.bad != 0) {
+        if (blockIdx.x == 0 && tid == 0 && a.net_out) a.net_out[a.row] = kZoneNoTally;
+        if (blockIdx.x == 0 && tid < Z && a.zone_out) a.zone_out[a.row * Z + tid] = kZoneNoTally;
+        return;
+    }
     if (tid < Z) {
         s_tl[tid] = word_threshold(a.table[tid]);
         s_tr[tid] = word_threshold(a.table[Z + tid]);
@@ -331,7 +338,6 @@ constexpr int kZoneRunSteps = 4096;       // steps per launch (the biased sums s
 constexpr int kZonePairsMixed = 1;        // rail pairs of a wavefront whose work is interleaved
 constexpr int kZoneRunMaxPairs = 16;      // rail pairs per wavefront
 constexpr int64_t kZoneGateTicks = 1000;  // 10 us per step: what the wait at the gate may cost
-constexpr int32_t kZoneNoTally = -2147483647 - 1;
 constexpr int64_t kZoneBias = 1 << 20;    // above any workgroup's change in one step
 
 struct ZoneRunArgs {
@@ -1114,9 +1120,14 @@ kmc_status kmc_zone_run_steps(kmc_zone_ctx *c, int64_t n_steps, int32_t *net_dev
     a.net_out = net_dev;
     a.zone_out = zone_dev;
     a.net_total = c->at<int64_t>(c->off_total);
+    a.bad = c->at<int32_t>(c->off_bad) + 2;
     const int64_t pairs = ((int64_t)c->p.rails + 1) / 2;
     const ZoneShape shape = zone_shape(c);
-    if (shape.pairs > 0) {
+    // One step of a large lattice goes by zone_step: loading the ions to
+    // registers and the launch behind cost more than its passes over memory
+    // (128,000 rails: 77 us for the call against 69; 32,000: 39 and 37; 4000: 27
+    // and 29; two steps 91 and 103, 44 and 53, 30 and 42).
+    if (shape.pairs > 0 && (n_steps > 1 || c->p.rails <= 16384)) {
         ZoneRunArgs r{};
         r.X = a.X;
         r.rails = a.rails;

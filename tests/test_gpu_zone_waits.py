@@ -19,16 +19,18 @@ pytestmark = [pytest.mark.gpu,
 NO_TALLY = -2 ** 31
 
 
-@pytest.mark.parametrize("reader", ["positions", "occupancy", "load"])
-def test_a_hung_wait_is_reported(reader):
+# (a single step of the larger lattice is a launch of its own kind)
+@pytest.mark.parametrize("reader,rails,steps", [("positions", 601, 5), ("occupancy", 601, 1), ("load", 601, 5),
+                                                ("occupancy", 16387, 1)])
+def test_a_hung_wait_is_reported(reader, rails, steps):
     from paper_2511_09413_amd import KMC_EHIP, KMC_ESTATE, KmcError
-    sim, _, X = _pair(601, 50, 21, 10, 0.7, 1e-3, seed=3)
+    sim, _, X = _pair(rails, 50, 21, 10, 0.7, 1e-3, seed=3)
     sim.set_bias_protocol(*constant(2.0))
     before = sim.read_occupancy().copy()
     sim.set_wait_limit(0)
     net, zones = sim.run_steps(12, tallies=True)
     sim.set_wait_limit(1 << 22)
-    later, zones_later = sim.run_steps(5, tallies=True)       # enqueued before anyone looked
+    later, zones_later = sim.run_steps(steps, tallies=True)      # enqueued before anyone looked
     for t in (net, zones, later, zones_later):
         assert bool((t == NO_TALLY).all())
     with pytest.raises(KmcError) as e:
