@@ -350,11 +350,6 @@ struct kmc_ctx {
     std::vector<double> vmax;          // largest |bias| of each device's protocol
     int dr_rows = 0, dr_grid = 0;      // dense: survivors per product; workgroups per launch
     size_t dr_lds = 0;
-    // a protocol set device by device: equal ones of consecutive devices are
-    // installed by one launch (bias_flush; none waiting: bias_d0 == bias_d1)
-    int bias_d0 = 0, bias_d1 = 0, bias_n = 0;
-    int64_t bias_set = 0;
-    double bias_t[kMaxKnots], bias_v[kMaxKnots];
     bool dr_stale = true, dr_fit = false;  // plan_draws is to run; its answer
     int dr_bins = 1, dr_per_bin = 1;   // column blocks that hold bonds; resolving workgroups of each
     bool planes_equal = false;         // both state (and potential) planes hold the current state
@@ -637,17 +632,6 @@ int launch_kind(const kmc_ctx *c) {
 }
 
 
-// Installs the protocol of the devices [bias_d0, bias_d1) that were set last.
-kmc_status bias_flush(kmc_ctx *c) {
-    if (c->bias_d0 == c->bias_d1) return KMC_OK;
-    const int d0 = c->bias_d0, d1 = c->bias_d1;
-    c->bias_d0 = c->bias_d1 = 0;
-    KMC_HIP(c, launch_set_protocol(c->at<double>(c->lay.knot_t), c->at<double>(c->lay.knot_v),
-                                   c->at<DevInfo>(c->lay.devs), d0, d1, c->bias_n, c->bias_set, c->bias_t, c->bias_v,
-                                   c->stream));
-    return KMC_OK;
-}
-
 // Whether a run with open electrodes goes by wave tiles: where a device's
 // tiles fit one workgroup (make_wtiles), unless another strategy was asked
 // for.  (kmc_get_launch_mode reports HALF_STEP for every context with open
@@ -923,8 +907,6 @@ kmc_status enqueue_draws(kmc_ctx *c, const HopArgs &h, const Ctl &ctl, int64_t d
 // wrote the caller's occupancy (the wave kernel does).
 kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t *dec_out, bool *exported) {
     const int D = c->p.n_devices;
-    kmc_status s = bias_flush(c);
-    if (s != KMC_OK) return s;
     HopArgs a = hop_args(c);
     const int kind = launch_kind(c);
     const bool open_wave = open_by_wave(c);
@@ -980,6 +962,7 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
     }
     if (c->dr_stale) plan_draws(c);
     const bool draws = c->dr_fit;
+    kmc_status s = KMC_OK;
     // the fixed-point path's hop counts start at zero (a score replay in
     // between leaves its own there)
     if (c->phifix && !draws) KMC_HIP(c, launch_zero_i64(c->at<int64_t>(c->lay.hop_ctl), 2, c->stream));
@@ -1447,23 +1430,9 @@ kmc_status kmc_set_bias_protocol(kmc_ctx *c, int32_t device, const double *t_s, 
     for (int i = 0; i < n_knots; ++i) peak = std::max(peak, std::fabs(v_volt[i]));
     for (int d = d0; d < d1; ++d) c->vmax[d] = peak;
     c->dr_stale = true;
-    // Programs set replicas one by one (512 launches of 2 us each on the GPU and
-    // 8 on the host): a device that continues the run of devices set before it
-    // with the same knots at the same step joins that run's launch, which goes
-    // out when the run ends, at the last device, or before the next steps.
-    const bool joins = c->bias_d0 < c->bias_d1 && c->bias_d1 == d0 && device >= 0 && c->bias_n == n_knots &&
-                       c->bias_set == c->n && std::memcmp(c->bias_t, t_s, sizeof(double) * n_knots) == 0 &&
-                       std::memcmp(c->bias_v, v_volt, sizeof(double) * n_knots) == 0;
-    if (!joins) {
-        if ((s = bias_flush(c)) != KMC_OK) return s;
-        c->bias_d0 = d0;
-        c->bias_n = n_knots;
-        c->bias_set = c->n;
-        std::copy(t_s, t_s + n_knots, c->bias_t);
-        std::copy(v_volt, v_volt + n_knots, c->bias_v);
-    }
-    c->bias_d1 = d1;
-    return d1 == c->p.n_devices ? bias_flush(c) : KMC_OK;
+    KMC_HIP(c, launch_set_protocol(c->at<double>(c->lay.knot_t), c->at<double>(c->lay.knot_v),
+                                   c->at<DevInfo>(c->lay.devs), d0, d1, n_knots, c->n, t_s, v_volt, c->stream));
+    return KMC_OK;
 }
 
 kmc_status kmc_run_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_hops_dev, int32_t *decile_dev) {
@@ -1779,8 +1748,6 @@ kmc_status check_replay_args(kmc_ctx *c, const int8_t *occ0_dev, int64_t step0, 
 kmc_status enqueue_replay(kmc_ctx *c, const int8_t *occ0_dev, int64_t step0, int64_t n_steps,
                           const double *weight_dev, double *grad_dev, const ReplayBufs &b, bool use_record) {
     const int D = c->p.n_devices;
-    const kmc_status flushed = bias_flush(c);
-    if (flushed != KMC_OK) return flushed;
     KMC_HIP(c, launch_zero_i64(reinterpret_cast<int64_t *>(grad_dev), 4 * (int64_t)D, c->stream));
     if (n_steps == 0) return KMC_OK;
     // A recording serves the replay when it began at step0, its steps up to
