@@ -353,6 +353,7 @@ struct kmc_ctx {
     bool dr_stale = true, dr_fit = false;  // plan_draws is to run; its answer
     int dr_bins = 1, dr_per_bin = 1;   // column blocks that hold bonds; resolving workgroups of each
     bool planes_equal = false;         // both state (and potential) planes hold the current state
+    bool captured = false;             // some of its work is in a graph: replays change the planes unseen
     bool any_open = false;             // some device has open electrodes: half-step launches or wave tiles (open_by_wave)
     // recording of accepted hops for the score replay (kmc_record_hops), in
     // the caller's buffer: per half-step counts, then a flag for the replay's
@@ -765,6 +766,14 @@ bool wave_finishes(int d0, int d1, int steps) {
     return series <= 64 && (int64_t)series * steps <= 4096;
 }
 
+// Whether the context's stream is being captured into a graph.
+bool capturing(const kmc_ctx *c) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Whether the half-steps of a long-range context go by low draws, and with
 // how many resolving workgroups per column block: when few words are expected
 // to pass stage 0, from every device's bound at its largest bias.  Such a
@@ -866,7 +875,8 @@ kmc_status enqueue_draws(kmc_ctx *c, const HopArgs &h, const Ctl &ctl, int64_t d
                                  clear ? a.n_hops : nullptr, c->stream);
     };
     if (done == 0) {
-        if (!c->planes_equal) {
+        // (a graph may be replayed after any change of the state)
+        if (!c->planes_equal || c->captured) {
             KMC_HIP(c, launch_copy_bytes(planes[0], planes[1], (size_t)L.total_pad, c->stream));
             if (c->phifix) KMC_HIP(c, launch_copy_bytes(phis[0], phis[1], sizeof(int64_t) * (size_t)L.total_pad, c->stream));
         }
@@ -961,6 +971,7 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
         pa.record = r;
     }
     if (c->dr_stale) plan_draws(c);
+    if (c->dr_ok && capturing(c)) c->captured = true;
     const bool draws = c->dr_fit;
     kmc_status s = KMC_OK;
     // the fixed-point path's hop counts start at zero (a score replay in
@@ -1072,6 +1083,7 @@ kmc_status check_status(kmc_ctx *c) {
 kmc_status after_state_change(kmc_ctx *c) {
     c->rec_on = false;  // a recording describes the trajectory from its own start state
     c->planes_equal = false;
+    if (c->dr_ok && capturing(c)) c->captured = true;
     if (c->phifix) KMC_HIP(c, launch_phifix_update(phifix_args(c, c->cur, true, 0), c->stream));
     KMC_HIP(c, launch_count_deciles(c->cur, c->at<DevInfo>(c->lay.devs), c->p.n_devices,
                                     c->at<int64_t>(c->lay.dec_run), c->stream));

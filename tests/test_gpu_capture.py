@@ -73,3 +73,66 @@ def test_a_replay_uses_the_protocols_installed_when_it_runs():
         _replay(sim, graph)
         assert np.array_equal(net.cpu().numpy(), expect)
         assert np.array_equal(sim.read_occupancy(), ref.read_occupancy())
+
+
+LONG_RANGE = [(BF16X2, [40, 40], 96), (PHI_FIXED, [40, 40], 96)]
+
+
+def _long_range(precision, sites):
+    return Physics(precision=precision, seed=6, ea_ev=0.2, screening_sites=0.0, cutoff_sites=sites - 1, rail_range=2)
+
+
+@pytest.mark.parametrize("precision,rails,sites", LONG_RANGE)
+def test_a_replay_starts_from_the_state_loaded_before_it(precision, rails, sites):
+    """Captured after a run (when both planes of the low-draw half-steps are
+    alike), replayed after loads and runs."""
+    ph = _long_range(precision, sites)
+    sim, ref = (_sim(ph, rails, [sites] * 2) for _ in range(2))
+    states = [sim.read_occupancy().copy()]
+    for s in (sim, ref):
+        s.set_bias_protocol(*constant(1.0))
+        _eager(s, 10)
+    states.append(sim.read_occupancy().copy())
+    graph, net = _capture(sim, 12)
+    expect = []
+    for occ in states:
+        twin = _sim(ph, rails, [sites] * 2)
+        twin.set_bias_protocol(*constant(1.0))
+        _eager(twin, 10)
+        _load(twin, occ)
+        expect.append((_eager(twin, 12), twin.read_occupancy()))
+        twin.close()
+    for k in (0, 1, 0, 1):
+        _load(sim, states[k])
+        _replay(sim, graph)
+        assert np.array_equal(net.cpu().numpy(), expect[k][0])
+        assert np.array_equal(sim.read_occupancy(), expect[k][1])
+        if k == 1:                       # a replay, then a run from its state
+            step = sim.step
+            got = _eager(sim, 12)
+            twin = _sim(ph, rails, [sites] * 2)
+            twin.set_bias_protocol(*constant(1.0))
+            _eager(twin, step)
+            _load(twin, expect[k][1])
+            assert np.array_equal(got, _eager(twin, 12))
+            assert np.array_equal(sim.read_occupancy(), twin.read_occupancy())
+            twin.close()
+    sim.close()
+    ref.close()
+
+
+@pytest.mark.parametrize("precision,rails,sites", LONG_RANGE)
+def test_a_captured_first_run_changes_nothing_until_it_is_replayed(precision, rails, sites):
+    ph = _long_range(precision, sites)
+    sim, ref = (_sim(ph, rails, [sites] * 2) for _ in range(2))
+    start = sim.read_occupancy().copy()
+    for s in (sim, ref):
+        s.set_bias_protocol(*constant(1.0))
+    graph, _ = _capture(sim, 12)
+    _eager(ref, 12)
+    _load(ref, start)
+    # (the second plane still holds whatever it held before the load)
+    assert np.array_equal(_eager(sim, 12), _eager(ref, 12))
+    assert np.array_equal(sim.read_occupancy(), ref.read_occupancy())
+    sim.close()
+    ref.close()
