@@ -23,6 +23,7 @@ struct QueueWords {
     uint32_t ready[32];   // steps whose end has been written
 };
 constexpr uint32_t kQueueAbort = 0x80000000u;
+constexpr int64_t kGateTicks = 1000;  // 10 us per step of the launch: what the wait at its gate may cost
 constexpr int kQueueWords = (int)(sizeof(QueueWords) / sizeof(uint32_t));
 
 #if defined(__HIPCC__)

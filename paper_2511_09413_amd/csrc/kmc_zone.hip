@@ -337,7 +337,6 @@ constexpr int kZoneAccStride = 72;        // 64-bit words per row (zones, then n
 constexpr int kZoneRunSteps = 4096;       // steps per launch (the biased sums stay below 2^40)
 constexpr int kZonePairsMixed = 1;        // rail pairs of a wavefront whose work is interleaved
 constexpr int kZoneRunMaxPairs = 16;      // rail pairs per wavefront
-constexpr int64_t kZoneGateTicks = 1000;  // 10 us per step: what the wait at the gate may cost
 constexpr int64_t kZoneBias = 1 << 20;    // above any workgroup's change in one step
 
 struct ZoneRunArgs {
@@ -661,16 +660,22 @@ __global__ __launch_bounds__(1024) void zone_queue(ZoneRunArgs a) {
     const PhiloxLane lc = philox_lane((uint32_t)l, 2u << 1, a.key0, a.key1);
     unsigned long long *row_of_wg = a.acc + (blockIdx.x % kZoneAcc) * kZoneAccStride;
     int at_step = -1;  // whose thresholds the LDS holds
+    bool ended = false;  // the workgroup has ended the step before at_step
     for (;;) {
+        // (one block of thread 0 between two barriers: with two of them and only
+        // the back edge between, the compiler may send the other lanes on alone)
         if (tid == 0) {
+            if (ended) __hip_atomic_store(a.queue->ready, (uint32_t)at_step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const uint32_t v = __hip_atomic_fetch_add(a.queue->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s.ticket = v;
             s.go = v < (uint32_t)a.n_steps * (uint32_t)a.n_tiles &&
                    kmc::queue_wait(a.queue->ready, v / (uint32_t)a.n_tiles, a.bad, a.wait_limit);
         }
         __syncthreads();
-        if (!s.go) return;
-        const int k = (int)(s.ticket / (uint32_t)a.n_tiles), tile = (int)(s.ticket - (uint32_t)k * (uint32_t)a.n_tiles);
+        const uint32_t ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)s.ticket);
+        if (!__builtin_amdgcn_readfirstlane(s.go)) return;
+        ended = false;
+        const int k = (int)(ticket / (uint32_t)a.n_tiles), tile = (int)(ticket - (uint32_t)k * (uint32_t)a.n_tiles);
         if (k != at_step && tid < Z) {
             s.thr[0][tid] = word_threshold(kmc::queue_load(a.table + Z + tid));
             s.thr[1][tid] = word_threshold(kmc::queue_load(a.table + tid));
@@ -705,7 +710,7 @@ __global__ __launch_bounds__(1024) void zone_queue(ZoneRunArgs a) {
             s.last = __hip_atomic_fetch_add(a.queue->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
                      (uint32_t)(k + 1) * (uint32_t)a.n_tiles;
         __syncthreads();
-        if (!s.last) continue;
+        if (!__builtin_amdgcn_readfirstlane((int)s.last)) continue;
         // every tile of step k is done
         if (tid < Z) s.pop[tid] = (int32_t)kmc::queue_load(a.pop + tid);
         if (tid <= Z) {
@@ -721,9 +726,8 @@ __global__ __launch_bounds__(1024) void zone_queue(ZoneRunArgs a) {
         const double V = protocol_voltage(s.kt, s.kv, a.n_knots, (double)(a.n0 + k + 1 - a.n_set) * a.dt);
         zone_end_step<true>(s, k, V, true);
         kmc::queue_stores_done();
-        if (tid == 0)
-            __hip_atomic_store(a.queue->ready, (uint32_t)(k + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         at_step = k + 1;  // zone_end_step left its thresholds in the LDS
+        ended = true;
     }
 }
 
@@ -1159,7 +1163,7 @@ kmc_status kmc_zone_run_steps(kmc_zone_ctx *c, int64_t n_steps, int32_t *net_dev
             r.n0 = c->n + k;
             r.row0 = k;
             r.n_steps = (int32_t)std::min<int64_t>(kZoneRunSteps, n_steps - k);
-            r.gate_ticks = (int32_t)std::min<int64_t>(c->gate_ticks, kZoneGateTicks * std::max(r.n_steps, 16));
+            r.gate_ticks = (int32_t)std::min<int64_t>(c->gate_ticks, kmc::kGateTicks * std::max(r.n_steps, 16));
             unsigned long long *acc = c->at<unsigned long long>(c->off_acc);
             kmc::QueueWords *queue = c->at<kmc::QueueWords>(c->off_queue);
             const int set = (int)(k / kZoneRunSteps) & 1;
