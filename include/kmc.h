@@ -347,9 +347,13 @@ kmc_status kmc_fit_decay(const double *t, const double *m, int64_t n, double t0,
  *     half-steps that changed them.  Needs every device's rails to fit 64
  *     lanes (at least max(rail_range, 1) rails per tile unless the device is
  *     one tile) and every single device's tiling co-resident.
- *   KMC_LAUNCH_AUTO (default): WAVE when it fits (for rails of more than 2048
- *     padded sites with 64 sites per lane, which only AUTO chooses), else
- *     PERSISTENT when it fits, else HALF_STEP.
+ *   KMC_LAUNCH_AUTO (default): WAVE when it fits, else PERSISTENT when it
+ *     fits, else HALF_STEP.  Where only 64 sites per lane fit (rails of more
+ *     than 2048 padded sites), AUTO alone chooses wave tiles, call by call:
+ *     kmc_get_launch_mode then reads WAVE, kmc_set_launch_mode refuses it, and a
+ *     call for which the wave tiles would not pay runs as without them.  Such a
+ *     launch begins only when all its workgroups are resident, else its steps
+ *     are taken from a queue (kmc_set_gate_limit).
  * All give bit-identical trajectories. */
 typedef enum {
     KMC_LAUNCH_AUTO = 0,
@@ -386,6 +390,14 @@ kmc_status kmc_set_persistent_group_limit(kmc_ctx *ctx, int32_t max_tiles);
  * context (the state is invalid).  For tests of that path and for callers
  * that prefer a shorter bound.  Takes effect for launches enqueued after it. */
 kmc_status kmc_set_wait_limit(kmc_ctx *ctx, int32_t polls);
+
+/* How long at most the workgroups of a launch in wave tiles of 64 sites per lane
+ * wait for one another to be resident before they leave its steps to a queue of
+ * tiles that any free part of the GPU takes (default 100 ms, and never longer
+ * than 10 us per step of the launch or 160 us; 0: a launch of more than one
+ * workgroup leaves at once).  The results are the same.  In [0, 10^7]
+ * microseconds.  Takes effect for launches enqueued after it. */
+kmc_status kmc_set_gate_limit(kmc_ctx *ctx, int32_t microseconds);
 
 /* Target number of (padded) sites per workgroup tile, 0 = built-in default,
  * else in [16, 65536]; tiles are whole rails.  For KMC_LAUNCH_WAVE, 1024 and

@@ -103,6 +103,7 @@ def lib():
         L.kmc_get_persistent_groups.argtypes = [vp, P(C.c_int32)]
         L.kmc_set_persistent_group_limit.argtypes = [vp, C.c_int32]
         L.kmc_set_wait_limit.argtypes = [vp, C.c_int32]
+        L.kmc_set_gate_limit.argtypes = [vp, C.c_int32]
         L.kmc_dense_potential.argtypes = [vp, vp]
         L.kmc_fixed_potential.argtypes = [vp, vp, C.c_int32, P(C.c_int32)]
         L.kmc_set_electrodes.argtypes = [vp, C.c_int32, C.c_int32, C.c_double, C.c_double, C.c_double,
@@ -129,7 +130,7 @@ def lib():
                      "kmc_set_bias_protocol", "kmc_run_steps", "kmc_read_occupancy", "kmc_read_current",
                      "kmc_read_threshold_log", "kmc_get_step", "kmc_set_launch_mode", "kmc_get_launch_mode",
                      "kmc_set_tile_sites", "kmc_score_replay", "kmc_get_persistent_groups",
-                     "kmc_set_persistent_group_limit", "kmc_set_wait_limit", "kmc_dense_potential", "kmc_fixed_potential",
+                     "kmc_set_persistent_group_limit", "kmc_set_wait_limit", "kmc_set_gate_limit", "kmc_dense_potential", "kmc_fixed_potential",
                      "kmc_set_electrodes",
                      "kmc_autotune", "kmc_fit_decay", "kmc_score_replay_noalloc", "kmc_record_bytes",
                      "kmc_record_hops", "kmc_zone_workspace_bytes",
@@ -464,6 +465,11 @@ class Simulator:
         """Polls before a persistent kernel's neighbour wait is declared hung
         (kmc_set_wait_limit; 0: every wait fails at once)."""
         _check(lib().kmc_set_wait_limit(C.c_void_p(self.ctx), polls))
+
+    def set_gate_limit(self, microseconds: int) -> None:
+        """Longest wait for the workgroups of a launch with a gate to be resident
+        together (kmc_set_gate_limit; 0: leave its steps to the queue)."""
+        _check(lib().kmc_set_gate_limit(C.c_void_p(self.ctx), microseconds))
 
     def set_group_limit(self, max_tiles: int) -> None:
         """At most max_tiles workgroup tiles per persistent launch (0 = what fits)."""

@@ -19,6 +19,7 @@
 #include "kmc_internal.h"
 #include "kmc_electrode.h"
 #include "kmc_phifix.h"
+#include "kmc_queue.h"
 
 namespace kmc {
 hipError_t launch_hop(const HopArgs &a, size_t lds_bytes, bool fp64, hipStream_t st);
@@ -48,6 +49,8 @@ hipError_t launch_zero_i32(int32_t *p, int64_t n, hipStream_t st);
 hipError_t launch_persistent(const PArgs &a, int block, size_t lds, bool fp64, hipStream_t st);
 hipError_t persistent_capacity(int block, size_t lds, bool fp64, int *blocks_per_cu);
 hipError_t launch_zero_i64(int64_t *p, int64_t n, hipStream_t st);
+hipError_t launch_hop_queue(const HopArgs &a, const HopQueueArgs &q, int grid, size_t lds_bytes, bool fp64, hipStream_t st);
+hipError_t launch_class_weights(const int8_t *occ_pad, const DevInfo *devs, int n_dev, double beta, double *sums, hipStream_t st);
 hipError_t launch_wave(const PArgs &a, int spl, size_t lds, bool fp64, int open_tiles, hipStream_t st);
 hipError_t wave_capacity(int spl, size_t lds, bool fp64, int open_tiles, int *blocks_per_cu);
 size_t wave_lds_bytes(int spl, int rail_range, int cut, bool fp64, int open_tiles);
@@ -76,6 +79,7 @@ constexpr int64_t kMaxPTiles = 2048;
 constexpr int kPTileSites = 4096;  // default padded sites per persistent tile
 constexpr int kStepWin = 128;      // per-step table window of the persistent kernel
 constexpr int64_t kMaxWaveTiles = 8192;  // wave kernel: tiles per launch (publication memory)
+constexpr int kQueueGrid = 512;    // workgroups of the half-step queue, at most
 constexpr double kElementaryCharge = 1.602176634e-19;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -83,7 +87,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 struct Layout {
     size_t occ_a, occ_b, devs, tiles, knot_t, knot_v, ktab64, ktab32, ctl, tally_net, tally_dec, dec_run,
         net_total, log_count, log_entries, scratch, rail_dev, rail_idx, n_ions, ptiles, pub, status,
-        rp_a, rp_b, score_log, rec, hops, hop_ctl, phi, ktiles, dtiles, ctiles, ticket, phifix, kfix, electrodes, rtiles, total;
+        rp_a, rp_b, score_log, rec, hops, hop_ctl, phi, ktiles, dtiles, ctiles, ticket, queue, phifix, kfix, electrodes, rtiles, total;
     size_t dr_lists, dr_hops, dr_cnt, dr_thr, dr_volt, dr_ktiles, phifix_b;  // half-steps by low draws
     int64_t max_ptiles, pub_stride;  // persistent kernel: tiles per launch (ring slots), words per ring
     int64_t max_wtiles, wpub_stride;  // wave kernel: tiles per launch, publication words per tile
@@ -237,6 +241,7 @@ Layout layout_for(const kmc_params *p) {
     L.wtiles = take(sizeof(PTile) * (size_t)rails);  // every wave tile is at least one rail
     L.status = take(sizeof(int32_t) * 4);
     L.ticket = take(sizeof(uint32_t) * kTicketWords);  // wave kernel: tiles that ended the launch
+    L.queue = take(sizeof(QueueWords) * 2);  // used in turn by the launches with a gate
     L.electrodes = take(sizeof(Electrode) * D);       // open-electrode reservoirs per device
     // score replay: its own pair of state planes, a discarded event count, the
     // Coulomb part of every bond's energy change (path precision) and the list
@@ -334,6 +339,9 @@ struct kmc_ctx {
     int w_spl = 0;                     // sites per lane of the wave tiling
     size_t w_lds = 0;
     bool w_ok = false;                 // wave tiling fits co-resident on this GPU
+    int w_queue = 0;                   // set of queue words of the next launch with a gate
+    int32_t gate_us = 100000;          // longest wait at the gate
+    std::vector<double> class_weight;  // mean over a device's sites of exp(-beta (class barrier - lowest)); empty: not known
     int w_open_tiles = 0;              // tiles of every device when open electrodes run in wave tiles, else 0
     size_t w_lds_open = 0;
     int mode = 0;                      // KMC_LAUNCH_AUTO / _HALF_STEP / _PERSISTENT
@@ -633,6 +641,42 @@ int launch_kind(const kmc_ctx *c) {
 }
 
 
+// Whether the context's stream is being captured into a graph.
+bool capturing(const kmc_ctx *c) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Whether the call goes by wave tiles of 64 sites per lane, under AUTO where no
+// narrower wave tiling exists.  Such a tile holds one long rail, and its time
+// grows with the words that pass their threshold in it, while the half-step
+// launches spread them over the GPU.  Against half-step launches (us per step,
+// 512 x 3001 in binary32 with 0.3, 2 and 6 such words per rail and half-step):
+// 7.2 against 15.0, 17.2 against 17.6, 33 against 29; 2000 x 4096 with 2.8 and
+// 19.5: 22 against 33, 79 against 69 (20 steps).  Where the persistent kernel
+// fits it is the faster one at every barrier tried (64 x 3001: 3.0 against 3.1
+// at 0.3 eV, 9.0 against 17.2 at 0.2); a single step takes 40 us as a call
+// against 36.  Captured calls keep to half-steps: a replay would meet
+// its own publications of the time before.
+bool wave64_pays(const kmc_ctx *c, int64_t n_steps) {
+    if (c->p_ok || n_steps < 4 || c->class_weight.empty() || capturing(c)) return false;
+    const double beta = 1.0 / c->p.kT_ev, c0 = c->p.nu0_hz * c->p.dt_s;
+    // (windows wider than a wavefront: a survivor at a time; 512 x 3001, cutoff
+    // 40, with 2 words: 21 us per step against 19)
+    const double limit = (2.0 + (double)c->lay.total_sites / 6e6) * (kernel_diff_width(c->lay.cut) > 0 ? 1.0 : 0.5);
+    std::vector<int> rails(c->p.n_devices, 0);
+    for (const PTile &t : c->wtiles) rails[t.d] = std::max(rails[t.d], t.nr);
+    for (int d = 0; d < c->p.n_devices; ++d) {
+        const DevInfo &dv = c->devs[d];
+        const double field = std::fabs(c->p.field_coupling) * c->vmax[d] / (double)dv.sites;
+        const double p = c0 * std::exp(-beta * (dv.ea_min - 0.5 * (field + dv.coul_bound))) * c->class_weight[d];
+        if (!(std::min(p, 1.0) * 0.5 * (double)dv.sites * rails[d] <= limit)) return false;
+    }
+    return true;
+}
+
 // Whether a run with open electrodes goes by wave tiles: where a device's
 // tiles fit one workgroup (make_wtiles), unless another strategy was asked
 // for.  (kmc_get_launch_mode reports HALF_STEP for every context with open
@@ -764,14 +808,6 @@ DenseArgs dense_args(kmc_ctx *c, const int8_t *occ, float *phi, int64_t phi_row)
 bool wave_finishes(int d0, int d1, int steps) {
     const int series = (d1 - d0) * (kDeciles + 1);
     return series <= 64 && (int64_t)series * steps <= 4096;
-}
-
-// Whether the context's stream is being captured into a graph.
-bool capturing(const kmc_ctx *c) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return false;
 }
 
 // Whether the half-steps of a long-range context go by low draws, and with
@@ -918,7 +954,9 @@ kmc_status enqueue_draws(kmc_ctx *c, const HopArgs &h, const Ctl &ctl, int64_t d
 kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t *dec_out, bool *exported) {
     const int D = c->p.n_devices;
     HopArgs a = hop_args(c);
-    const int kind = launch_kind(c);
+    int kind = launch_kind(c);
+    const bool gated = kind == KMC_LAUNCH_WAVE && c->w_spl == 64;
+    if (gated && !wave64_pays(c, n_steps)) kind = c->p_ok ? KMC_LAUNCH_PERSISTENT : KMC_LAUNCH_HALF_STEP;
     const bool open_wave = open_by_wave(c);
     const bool wave = kind == KMC_LAUNCH_WAVE || open_wave;
     const bool persistent = wave || kind == KMC_LAUNCH_PERSISTENT;
@@ -977,6 +1015,8 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
     // the fixed-point path's hop counts start at zero (a score replay in
     // between leaves its own there)
     if (c->phifix && !draws) KMC_HIP(c, launch_zero_i64(c->at<int64_t>(c->lay.hop_ctl), 2, c->stream));
+    // (a launch that left at its gate ends no tally rows)
+    auto finishes = [&](int d0, int d1, int steps) { return !gated && wave_finishes(d0, d1, steps); };
     int64_t done = 0;
     while (done < n_steps) {
         const int chunk = (int)std::min<int64_t>(kTallySteps, n_steps - done);
@@ -1006,11 +1046,32 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
                 pa.fin.d0 = tl[g.first].d;
                 pa.fin.d1 = tl[g.first + g.second - 1].d + 1;
                 pa.ticket = nullptr;
-                if (wave && wave_finishes(pa.fin.d0, pa.fin.d1, chunk)) pa.ticket = c->at<uint32_t>(c->lay.ticket);
+                if (wave && finishes(pa.fin.d0, pa.fin.d1, chunk)) pa.ticket = c->at<uint32_t>(c->lay.ticket);
                 else all_finished = false;
+                if (wave && gated) {
+                    QueueWords *words = c->at<QueueWords>(c->lay.queue);
+                    pa.queue = words + c->w_queue;
+                    c->w_queue ^= 1;
+                    pa.queue_next = words + c->w_queue;
+                    pa.gate_ticks = (int32_t)std::min<int64_t>(100 * (int64_t)c->gate_us, kGateTicks * std::max(chunk, 16));
+                }
                 if (wave) KMC_HIP(c, launch_wave(pa, c->w_spl, open_wave ? c->w_lds_open : c->w_lds, c->fp64,
                                                 open_wave ? c->w_open_tiles : 0, c->stream));
                 else KMC_HIP(c, launch_persistent(pa, c->p_block, c->p_lds, c->fp64, c->stream));
+                if (wave && gated) {
+                    // the half-step tiles of the launch's devices
+                    HopArgs h = a;
+                    const auto of = [&](int d) {
+                        return std::lower_bound(c->tiles.begin(), c->tiles.end(), d, [](const Tile &t, int x) { return t.d < x; }) -
+                               c->tiles.begin();
+                    };
+                    const int64_t t0 = of(pa.fin.d0);
+                    h.tiles += t0;
+                    h.n_tiles = (int32_t)(of(pa.fin.d1) - t0);
+                    const int per = (h.n_tiles + kQueueGrid - 1) / kQueueGrid;
+                    const HopQueueArgs q{pa.queue, c->cur, c->nxt, c->occ_user, pa.status, chunk, c->spin_limit, per};
+                    KMC_HIP(c, launch_hop_queue(h, q, (h.n_tiles + per - 1) / per, c->hop_lds, c->fp64, c->stream));
+                }
             }
             if (wave && !all_finished) {
                 // the groups whose launches did not end their rows
@@ -1018,7 +1079,7 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
                     FinishArgs f = fa;
                     f.d0 = c->wtiles[g.first].d;
                     f.d1 = c->wtiles[g.first + g.second - 1].d + 1;
-                    if (!wave_finishes(f.d0, f.d1, chunk)) KMC_HIP(c, launch_finish_chunk(f, c->stream));
+                    if (!finishes(f.d0, f.d1, chunk)) KMC_HIP(c, launch_finish_chunk(f, c->stream));
                 }
             }
         }
@@ -1364,6 +1425,7 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
     chk(launch_zero_i64(c->at<int64_t>(lay.pub), pub_words(lay), st), "zero publication ring");
     chk(launch_zero_i32(c->at<int32_t>(lay.status), 4, st), "zero status");
     chk(launch_zero_i32(c->at<int32_t>(lay.ticket), kTicketWords, st), "zero ticket");
+    chk(launch_zero_i32(c->at<int32_t>(lay.queue), 2 * kQueueWords, st), "zero queue words");
     c->el.assign(D, Electrode{});
     chk(hipMemcpyAsync(c->ws + lay.electrodes, c->el.data(), sizeof(Electrode) * D, hipMemcpyHostToDevice, st),
         "closed electrodes");
@@ -1378,8 +1440,9 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
         chk(launch_barrier_range(ea_dev, c->fp64, c->at<DevInfo>(lay.devs), D,
                                  c->at<unsigned long long>(lay.scratch), st),
             "barrier range");
-    if (ea_dev && c->dr_ok) {
-        // the lowest barriers, for the choice of low-draw half-steps
+    if (ea_dev && (c->dr_ok || (c->w_ok && c->w_spl == 64 && !c->p_ok))) {
+        // the lowest barriers, for the choice of low-draw half-steps or of wave
+        // tiles of 64 sites per lane
         std::vector<DevInfo> back(D);
         chk(hipMemcpyAsync(back.data(), c->ws + lay.devs, sizeof(DevInfo) * D, hipMemcpyDeviceToHost, st), "read barrier ranges");
         chk(hipStreamSynchronize(st), "read barrier ranges");
@@ -1387,6 +1450,16 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
     }
     chk(launch_import(occ_dev, c->cur, c->at<DevInfo>(lay.devs), D, lay.total_pad, ea_dev, c->fp64, st),
         "import occupancy");
+    if (!ea_dev) c->class_weight.assign(D, 1.0);
+    if (ea_dev && c->w_ok && c->w_spl == 64 && !c->p_ok) {
+        c->class_weight.resize(D);
+        chk(launch_class_weights(c->cur, c->at<DevInfo>(lay.devs), D, 1.0 / params->kT_ev, c->at<double>(lay.scratch), st),
+            "barrier classes");
+        chk(hipMemcpyAsync(c->class_weight.data(), c->ws + lay.scratch, sizeof(double) * D, hipMemcpyDeviceToHost, st),
+            "read barrier classes");
+        chk(hipStreamSynchronize(st), "read barrier classes");
+        for (int d = 0; d < D; ++d) c->class_weight[d] /= (double)c->devs[d].rails * c->devs[d].sites;
+    }
     if (ok == KMC_OK) ok = after_state_change(c);
     if (ok != KMC_OK) {
         delete c;
@@ -1534,7 +1607,8 @@ kmc_status kmc_set_launch_mode(kmc_ctx *c, int32_t mode) {
         return fail(KMC_EUNSUPPORTED, "the persistent tiling does not fit co-resident on this GPU");
     // (64 sites per lane are the automatic strategy's own choice)
     if (mode == KMC_LAUNCH_WAVE && (!c->w_ok || c->w_spl == 64))
-        return fail(KMC_EUNSUPPORTED, "the wave tiling does not fit co-resident on this GPU");
+        return fail(KMC_EUNSUPPORTED, c->w_ok ? "rails this long run in wave tiles by KMC_LAUNCH_AUTO's choice alone"
+                                              : "the wave tiling does not fit co-resident on this GPU");
     c->mode = mode;
     return KMC_OK;
 }
@@ -1716,6 +1790,14 @@ kmc_status kmc_set_wait_limit(kmc_ctx *c, int32_t polls) {
     if (s != KMC_OK) return s;
     if (polls < 0) return fail(KMC_EINVAL, "polls must be >= 0");
     c->spin_limit = polls;
+    return KMC_OK;
+}
+
+kmc_status kmc_set_gate_limit(kmc_ctx *c, int32_t microseconds) {
+    kmc_status s = usable(c);
+    if (s != KMC_OK) return s;
+    if (microseconds < 0 || microseconds > 10000000) return fail(KMC_EINVAL, "microseconds must be in [0, 10^7]");
+    c->gate_us = microseconds;
     return KMC_OK;
 }
 

@@ -175,7 +175,8 @@ struct DenseArgs {
 
 // Arguments of the persistent kernel (several steps per launch, each
 // workgroup keeps its tile in LDS and talks to its two neighbours only).
-struct Electrode;  // kmc_electrode.h
+struct Electrode;   // kmc_electrode.h
+struct QueueWords;  // kmc_queue.h
 
 struct PArgs {
     int8_t *occ;               // padded state: read at launch start, written at the end
@@ -213,6 +214,20 @@ struct PArgs {
     const Electrode *el;       // [D], read by the tiles of an open-electrode launch
     uint32_t *ticket;
     FinishArgs fin;
+    // 64 sites per lane: the launch's gate (kmc_queue.h) and the words of the
+    // one after it, which it clears
+    QueueWords *queue, *queue_next;
+    int32_t gate_ticks;
+};
+
+// The steps of a wave launch that left at its gate (a.tiles and a.n_tiles: the
+// half-step tiles of its devices).
+struct HopQueueArgs {
+    QueueWords *words;
+    int8_t *plane_a, *plane_b;   // the state; the other plane
+    int8_t *occ_user;
+    int32_t *status;
+    int32_t n_steps, wait_limit, tiles_per_ticket;
 };
 
 }  // namespace kmc

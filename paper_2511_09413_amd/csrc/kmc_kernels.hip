@@ -4,7 +4,7 @@
 // set-up and bookkeeping kernels.  The persistent kernels are in
 // kmc_persistent.hip and kmc_wave.hip.
 //
-// hop_half_step: one launch decides every bond of one parity
+// hop_half_step (hop_tile for each tile): one launch decides every bond of one parity
 // (a half-step of the pair checkerboard) for every device, reading the state
 // at the start of the half-step from one buffer and writing the new state to
 // the other.  One workgroup owns whole rails of one device ("tile"), one lane
@@ -43,8 +43,34 @@
 
 #include "kmc_device.h"
 #include "kmc_internal.h"
+#include "kmc_queue.h"
 
 namespace kmc {
+
+// What a half-step of one tile reads and writes.
+struct HopAt {
+    const int8_t *in;   // padded state before the half-step
+    int8_t *out;        // and after it
+    int64_t n;          // step
+    int8_t *user;       // null, or the caller's occupancy to write too
+};
+
+// 16 sites of a state plane; kQueue: as other workgroups of the launch wrote them.
+template <bool kQueue>
+__device__ __forceinline__ uint4 load_sites(const int8_t *p) {
+    if constexpr (!kQueue) return *reinterpret_cast<const uint4 *>(p);
+    const uint64_t lo = queue_load(reinterpret_cast<const uint64_t *>(p)), hi = queue_load(reinterpret_cast<const uint64_t *>(p) + 1);
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
+template <bool kQueue>
+__device__ __forceinline__ void store_sites(int8_t *p, uint4 v) {
+    if constexpr (!kQueue) {
+        *reinterpret_cast<uint4 *>(p) = v;
+    } else {
+        queue_store(reinterpret_cast<uint64_t *>(p), (uint64_t)v.x | (uint64_t)v.y << 32);
+        queue_store(reinterpret_cast<uint64_t *>(p) + 1, (uint64_t)v.z | (uint64_t)v.w << 32);
+    }
+}
 
 struct HopShared {
     double score[kBlock / 64][4];  // score replay: per-wave partial sums
@@ -65,13 +91,10 @@ struct HopShared {
 // The survivors' Philox words and barriers are read again where they are
 // needed (a rare path), which keeps the LDS per workgroup small.
 // ------------------------------------------------------------------------
-template <typename Real, int H, int kMode>
-__global__ __launch_bounds__(kBlock) void hop_half_step(HopArgs a) {
+template <typename Real, int H, int kMode, bool kQueue>
+__device__ __forceinline__ void hop_tile(const HopArgs &a, const HopAt &at, const Tile tile, unsigned char *smem,
+                                         HopShared &sh) {
     constexpr bool kScore = kMode == 1;  // score replay
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ HopShared sh;
-
-    const Tile tile = a.tiles[tile_of_block(blockIdx.x, a.n_tiles)];
     const DevInfo &dv = a.devs[tile.d];
     const int R = dv.rails, L = dv.sites, pitch = dv.pitch;
     const int m = a.rail_range;
@@ -90,8 +113,8 @@ __global__ __launch_bounds__(kBlock) void hop_half_step(HopArgs a) {
                                                             : reinterpret_cast<const Real *>(a.ktab32);
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const int64_t n = kScore ? a.n_abs : a.ctl.n_base + a.step_in_chunk;
-    const int8_t *src_dev = a.occ_in + dv.off_pad;
+    const int64_t n = at.n;
+    const int8_t *src_dev = at.in + dv.off_pad;
 
     // 1. issue the loads of the lane's chunk and of one halo chunk
     const bool has_chunk = tid < n_chunks;
@@ -101,8 +124,10 @@ __global__ __launch_bounds__(kBlock) void hop_half_step(HopArgs a) {
     uint32_t nxt = 0;
     if (has_chunk) {
         const int8_t *rp = src_dev + (int64_t)(tile.r0 + row) * pitch;
-        v = *reinterpret_cast<const uint4 *>(rp + s0);
-        if (H == 1 && s0 + kChunkSites < pitch) nxt = (uint32_t)(uint8_t)rp[s0 + kChunkSites];
+        v = load_sites<kQueue>(rp + s0);
+        if (H == 1 && s0 + kChunkSites < pitch)
+            nxt = kQueue ? (uint32_t)queue_load(reinterpret_cast<const uint8_t *>(rp) + s0 + kChunkSites)
+                         : (uint32_t)(uint8_t)rp[s0 + kChunkSites];
     }
     auto halo_lds_row = [&](int i) { const int hr = i / p16; return hr < m ? hr : hr + tile.nr; };
     auto halo_src = [&](int i) {
@@ -112,7 +137,7 @@ __global__ __launch_bounds__(kBlock) void hop_half_step(HopArgs a) {
         return src_dev + (int64_t)rail * pitch + (i - (i / p16) * p16) * kChunkSites;
     };
     uint4 hv = make_uint4(0, 0, 0, 0);
-    if (tid < n_halo) hv = *reinterpret_cast<const uint4 *>(halo_src(tid));
+    if (tid < n_halo) hv = load_sites<kQueue>(halo_src(tid));
 
     // bias of this step and the prefilter thresholds per barrier class
     const double V = protocol_voltage(a.knot_t + tile.d * kMaxKnots, a.knot_v + tile.d * kMaxKnots, dv.n_knots,
@@ -143,7 +168,7 @@ __global__ __launch_bounds__(kBlock) void hop_half_step(HopArgs a) {
         *reinterpret_cast<uint4 *>(rows + halo_lds_row(tid) * pitch + (tid - (tid / p16) * p16) * kChunkSites) = hv;
     for (int i = tid + kBlock; i < n_halo; i += kBlock)
         *reinterpret_cast<uint4 *>(rows + halo_lds_row(i) * pitch + (i - (i / p16) * p16) * kChunkSites) =
-            *reinterpret_cast<const uint4 *>(halo_src(i));
+            load_sites<kQueue>(halo_src(i));
     __syncthreads();
 
     // 3. candidates and the exact two-stage prefilter
@@ -271,7 +296,11 @@ __global__ __launch_bounds__(kBlock) void hop_half_step(HopArgs a) {
                 if (hs + 1 >= s0 && hs + 1 < s0 + kChunkSites) flip_byte(v, hs + 1 - s0);
             }
         }
-        *reinterpret_cast<uint4 *>(a.occ_out + dv.off_pad + (int64_t)(tile.r0 + row) * pitch + s0) = v;
+        store_sites<kQueue>(at.out + dv.off_pad + (int64_t)(tile.r0 + row) * pitch + s0, v);
+        if (kQueue && at.user) {
+            int8_t *u = at.user + dv.off + (int64_t)(tile.r0 + row) * L + s0;
+            for (int k = 0; k < kChunkSites && s0 + k < L; ++k) u[k] = (int8_t)((word_of(v, k >> 2) >> (8 * (k & 3))) & 1u);
+        }
     }
 
     // 6. score replay: every candidate's term W g (y - p)/(1 - p), binary64.
@@ -396,6 +425,71 @@ __global__ __launch_bounds__(kBlock) void hop_half_step(HopArgs a) {
             if (sum != 0.0) atomicAdd(&a.score_grad[tile.d * 4 + tid], sum);
         }
     }
+}
+
+template <typename Real, int H, int kMode>
+__global__ __launch_bounds__(kBlock) void hop_half_step(HopArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ HopShared sh;
+    const HopAt at{a.occ_in, a.occ_out, kMode == 1 ? a.n_abs : a.ctl.n_base + a.step_in_chunk, nullptr};
+    hop_tile<Real, H, kMode, false>(a, at, a.tiles[tile_of_block(blockIdx.x, a.n_tiles)], smem, sh);
+}
+
+// Behind a launch of the wave kernel that left at its gate: the same steps as
+// half-steps of these tiles from a queue (kmc_queue.h), the state alternating
+// between the two planes.
+template <typename Real>
+__global__ __launch_bounds__(kBlock) void hop_queue(HopArgs a, HopQueueArgs q) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ HopShared sh;
+    __shared__ uint32_t s_ticket, s_go;
+    if (*q.status != 0 || (q.words->gate[0] & kQueueAbort) == 0) return;
+    // a ticket covers several tiles of a large lattice: one each, the counters'
+    // atomics alone took 100 us per half-step of 2000 tiles
+    const uint32_t per = (uint32_t)q.tiles_per_ticket, units = ((uint32_t)a.n_tiles + per - 1u) / per;
+    const uint32_t half_steps = 2u * (uint32_t)q.n_steps;
+    for (bool first = true;; first = false) {
+        // (the tile just done and the next ticket in one block of thread 0
+        // between two barriers: two blocks with only the back edge between them
+        // let the compiler send the other lanes on to the barrier alone)
+        if (threadIdx.x == 0) {
+            if (!first) __hip_atomic_fetch_add(q.words->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t v = __hip_atomic_fetch_add(q.words->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_ticket = v;
+            s_go = v < half_steps * units && queue_wait(q.words->done, v / units * units, q.status, q.wait_limit);
+        }
+        __syncthreads();
+        const uint32_t ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_ticket);
+        if (!__builtin_amdgcn_readfirstlane((int)s_go)) return;
+        const uint32_t hs = ticket / units, first_tile = (ticket - hs * units) * per;
+        const uint32_t end = min(first_tile + per, (uint32_t)a.n_tiles);
+        const HopAt at{hs & 1u ? q.plane_b : q.plane_a, hs & 1u ? q.plane_a : q.plane_b, a.ctl.n_base + (int64_t)(hs >> 1),
+                       hs + 1u == half_steps ? q.occ_user : nullptr};
+        for (uint32_t t = first_tile; t < end; ++t) {
+            const Tile tile = a.tiles[t];
+            if (hs & 1u) hop_tile<Real, 1, 0, true>(a, at, tile, smem, sh);
+            else hop_tile<Real, 0, 0, true>(a, at, tile, smem, sh);
+            queue_stores_done();
+        }
+    }
+}
+
+// Sum over a device's sites of exp(-beta (class barrier - lowest barrier)), for
+// the expected number of words that pass their site's threshold.  Grid
+// (blocks, devices); sums zero on entry.
+__global__ __launch_bounds__(256) void class_weights(const int8_t *occ_pad, const DevInfo *devs, double beta, double *sums) {
+    __shared__ double w[kClasses], part[4];
+    const DevInfo &dv = devs[blockIdx.y];
+    if (threadIdx.x < kClasses) w[threadIdx.x] = exp(-beta * ((double)threadIdx.x * dv.ea_step));
+    __syncthreads();
+    double sum = 0.0;
+    for (int r = blockIdx.x; r < dv.rails; r += gridDim.x)
+        for (int s = threadIdx.x; s < dv.sites; s += 256)
+            sum += w[(uint8_t)occ_pad[dv.off_pad + (int64_t)r * dv.pitch + s] >> 1];
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&sums[blockIdx.y], part[0] + part[1] + part[2] + part[3]);
 }
 
 // ------------------------------------------------------------------------
@@ -1141,6 +1235,22 @@ hipError_t set_hop_lds_limit(size_t lds_bytes, size_t score_lds_bytes) {
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+hipError_t launch_hop_queue(const HopArgs &a, const HopQueueArgs &q, int grid, size_t lds_bytes, bool fp64, hipStream_t st) {
+    const void *fn = fp64 ? (const void *)hop_queue<double> : (const void *)hop_queue<float>;
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    if (e != hipSuccess) return e;
+    HopArgs args = a;
+    HopQueueArgs qargs = q;
+    void *kargs[] = {&args, &qargs};
+    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(kBlock), kargs, lds_bytes, st);
+}
+
+hipError_t launch_class_weights(const int8_t *occ_pad, const DevInfo *devs, int n_dev, double beta, double *sums, hipStream_t st) {
+    hipLaunchKernelGGL(zero_i64, dim3((unsigned)((n_dev + 255) / 256)), dim3(256), 0, st, reinterpret_cast<int64_t *>(sums), (int64_t)n_dev);
+    hipLaunchKernelGGL(class_weights, dim3(64, n_dev), dim3(256), 0, st, occ_pad, devs, beta, sums);
+    return hipGetLastError();
 }
 
 hipError_t launch_import(const int8_t *src, int8_t *dst, const DevInfo *devs, int n_dev, int64_t total_pad,

@@ -65,6 +65,7 @@
 #include "kmc_device.h"
 #include "kmc_electrode.h"
 #include "kmc_internal.h"
+#include "kmc_queue.h"
 
 namespace kmc {
 
@@ -336,13 +337,23 @@ __global__ __launch_bounds__(64 * (Open ? kWaveOpenTiles : kWaveTilesPerWG), SPL
         const int n = wave_table_entries(a.rail_range, a.cutoff, Open);
         for (int i = threadIdx.x; i < n; i += blockDim.x) reinterpret_cast<Real *>(smem)[i] = tab[i];
     }
-    __syncthreads();
     // the tile's LDS (after the kernel table when that is in LDS)
     auto lds_of = [&](KArgs ka) -> WaveLds<Real, SPL, Open> & {
         return reinterpret_cast<WaveLds<Real, SPL, Open> *>(smem + wave_table_bytes(ka->rail_range, ka->cutoff, sizeof(Real), Open) +
                                                             (Open ? kPlaneBytes : 0))[wave];
     };
     WaveLds<Real, SPL, Open> &w = lds_of(kargs());
+    if constexpr (SPL == 64) {
+        // all workgroups are resident, or none runs (hop_queue then takes the
+        // steps); the answer goes through the first tile's LDS
+        uint32_t *go = (&w - wave)->snap;
+        if (threadIdx.x == 0) *go = queue_gate(a.queue->gate, gridDim.x, a.gate_ticks) ? 1u : 0u;
+        if (blockIdx.x == 0)
+            for (int i = threadIdx.x; i < kQueueWords; i += blockDim.x) reinterpret_cast<uint32_t *>(a.queue_next)[i] = 0u;
+        __syncthreads();
+        if (*go == 0u) return;
+    }
+    __syncthreads();
 
     if (ti >= a.n_tiles) return;  // no barrier follows
 
