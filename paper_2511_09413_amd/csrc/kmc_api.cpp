@@ -362,6 +362,7 @@ struct kmc_ctx {
     int dr_bins = 1, dr_per_bin = 1;   // column blocks that hold bonds; resolving workgroups of each
     bool planes_equal = false;         // both state (and potential) planes hold the current state
     bool captured = false;             // some of its work is in a graph: replays change the planes unseen
+    int64_t dr_old_steps = 0, dr_short_calls = 0;  // see draws_pay
     bool any_open = false;             // some device has open electrodes: half-step launches or wave tiles (open_by_wave)
     // recording of accepted hops for the score replay (kmc_record_hops), in
     // the caller's buffer: per half-step counts, then a flag for the replay's
@@ -861,6 +862,36 @@ void plan_draws(kmc_ctx *c) {
     c->dr_fit = true;
 }
 
+// Whether a call of n_steps goes by low draws (where plan_draws allows them).
+// What they cost beside the half-steps: threshold table, first draws and settling
+// (10 to 15 us a call), and the copy of the second plane when the planes differ.
+//   * fixed: a step saves 3 to 20 us, so a call of one step takes 5 to 15 us more
+//     than in the other form (10^5 sites 41 against 37, 10^7 sites 81 against 66,
+//     3.4e7 sites 125 against 115), one of two is level and one of four gains.  The
+//     copy takes 10 us and 4 per 10^6 sites (3.4e7 sites 134; the first call after a
+//     load 250 us against 116 for one step, 282 against 170 for two).
+//   * dense: a step saves more than that on all but the smallest lattices (8192
+//     sites, one step after a load: 57 us against 53; 10^5 sites 60 against 84).
+// Short calls between others stay with the draws until the copy that they would
+// cause is paid for, and the steps of longer calls in the other form count
+// towards one.
+bool draws_pay(kmc_ctx *c, int64_t n_steps) {
+    if (!c->dr_fit) return false;
+    const double sites = (double)c->lay.total_sites;
+    const bool equal = c->planes_equal && !c->captured;
+    bool pays;
+    if (c->dense) {
+        pays = equal || n_steps > 1 || sites >= 5e4;
+    } else if (equal) {
+        c->dr_short_calls = n_steps < 4 ? c->dr_short_calls + 1 : 0;
+        pays = (double)c->dr_short_calls <= 1.0 + sites / 3e6;
+    } else {
+        pays = (double)(n_steps + (c->captured ? 0 : c->dr_old_steps)) >= 8.0 + sites / 2e6;
+    }
+    c->dr_old_steps = pays ? 0 : c->dr_old_steps + (n_steps < 4 ? 0 : n_steps);
+    return pays;
+}
+
 // The chunk's half-steps by low draws; done steps of the call's n_steps are
 // enqueued already.
 kmc_status enqueue_draws(kmc_ctx *c, const HopArgs &h, const Ctl &ctl, int64_t done, int64_t n_steps, int chunk) {
@@ -1010,7 +1041,7 @@ kmc_status enqueue_steps(kmc_ctx *c, int64_t n_steps, int32_t *net_out, int32_t 
     }
     if (c->dr_stale) plan_draws(c);
     if (c->dr_ok && capturing(c)) c->captured = true;
-    const bool draws = c->dr_fit;
+    const bool draws = draws_pay(c, n_steps);
     kmc_status s = KMC_OK;
     // the fixed-point path's hop counts start at zero (a score replay in
     // between leaves its own there)
@@ -1144,6 +1175,7 @@ kmc_status check_status(kmc_ctx *c) {
 kmc_status after_state_change(kmc_ctx *c) {
     c->rec_on = false;  // a recording describes the trajectory from its own start state
     c->planes_equal = false;
+    c->dr_old_steps = c->dr_short_calls = 0;
     if (c->dr_ok && capturing(c)) c->captured = true;
     if (c->phifix) KMC_HIP(c, launch_phifix_update(phifix_args(c, c->cur, true, 0), c->stream));
     KMC_HIP(c, launch_count_deciles(c->cur, c->at<DevInfo>(c->lay.devs), c->p.n_devices,
