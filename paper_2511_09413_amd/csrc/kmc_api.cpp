@@ -56,7 +56,7 @@ hipError_t wave_capacity(int spl, size_t lds, bool fp64, int open_tiles, int *bl
 size_t wave_lds_bytes(int spl, int rail_range, int cut, bool fp64, int open_tiles);
 int wave_band_words(int spl);
 hipError_t launch_copy_bytes(const void *src, void *dst, size_t bytes, hipStream_t st);
-hipError_t launch_replay_ec_full(const PhiArgs &a, int max_pitch, bool fp64, hipStream_t st);
+hipError_t launch_replay_ec_full(const PhiArgs &a, int max_pitch, int64_t rails_total, bool fp64, hipStream_t st);
 hipError_t launch_replay_ec_update(const PhiArgs &a, bool fp64, hipStream_t st, int64_t hops_known = -1);
 hipError_t launch_dense_phi(const DenseArgs &a, hipStream_t st);
 hipError_t launch_dense_decide(const HopArgs &a, int pitch, hipStream_t st);
@@ -1921,7 +1921,7 @@ kmc_status enqueue_replay(kmc_ctx *c, const int8_t *occ0_dev, int64_t step0, int
     pa.hops = b.hops;
     pa.hop_cap = c->lay.hop_cap;
     KMC_HIP(c, launch_zero_i64(b.hop_ctl, 2, c->stream));
-    KMC_HIP(c, launch_replay_ec_full(pa, c->lay.max_pitch, c->fp64, c->stream));
+    KMC_HIP(c, launch_replay_ec_full(pa, c->lay.max_pitch, c->lay.rails_total, c->fp64, c->stream));
     // The recorded half-steps keep the state as one bit per site in the plane
     // not holding it (packed when they begin, unpacked into the byte plane,
     // whose barrier classes are unchanged, before a half-step drawn again).

@@ -922,8 +922,12 @@ __device__ __forceinline__ double window_dot(const uint8_t *w, const double *dr,
 // 102 multiply-adds with a byte read each (+-1 rail, cutoff 16).  The bonds are
 // taken parity by parity, so that neighbouring lanes write neighbouring parts.
 // 6.7e7 bonds: 2.29 ms with window_dot, 0.49 here, of which the 268 MB written
-// take 0.06.
-constexpr int kEcRails = 16;
+// take 0.06.  What bounds smaller lattices is one workgroup's chain (table, rows,
+// bonds), so they take units of four rails, a wavefront each, and the table is
+// summed from differences held in LDS (64 devices of 8 x 64, a replay of one step:
+// 66 us, with window_dot's kernel 148).  A few devices of few rails are left to
+// window_dot's kernel (launch_replay_ec_full).
+constexpr int kEcRails = 16, kEcFewRails = 4;  // rails of a unit
 constexpr int kEcBitCut = 31;
 constexpr int kEcMargin = 64;  // zero bits before a rail
 
@@ -931,30 +935,37 @@ __host__ __device__ inline int ec_chunks(int cut) { return (2 * cut + 2 + 7) / 8
 __host__ __device__ inline int ec_row_words(int pitch) { return (pitch + 31) / 32 + kEcMargin / 32 + 3; }
 
 template <typename Real>
-__global__ __launch_bounds__(256) void replay_ec_start(PhiArgs a) {
+__global__ __launch_bounds__(256) void replay_ec_start(PhiArgs a, int unit_rails) {
     extern __shared__ __align__(16) unsigned char ec_smem[];
+    __shared__ double diff[(kMaxRailRange + 1) * 64];  // [dist][x], x < wn (0 from there to the last chunk's end)
     Real *ec = reinterpret_cast<Real *>(a.ec);
     const int cut = a.cutoff, m = a.rail_range, chunks = ec_chunks(cut), wn = 2 * cut + 2;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double *tab = reinterpret_cast<double *>(ec_smem);  // [m + 1][chunks][256]
     uint32_t *bits = reinterpret_cast<uint32_t *>(tab + (m + 1) * chunks * 256);
-    for (int i = threadIdx.x; i < (m + 1) * chunks * 256; i += 256) {
-        const int dist = i / (chunks * 256), c = i / 256 % chunks, pat = i & 255;
+    for (int i = threadIdx.x; i < (m + 1) * 64; i += 256) {
+        const int dist = i >> 6, x = i & 63;
         const double *kr = a.ktab64 + dist * (cut + 1);
-        double acc = 0.0;
-        for (int b = 0; b < 8; ++b) {
-            const int x = 8 * c + b;
-            if (!((pat >> b) & 1) || x >= wn) continue;
-            const int dt = x - cut - 1 < 0 ? cut + 1 - x : x - cut - 1, dO = x - cut < 0 ? cut - x : x - cut;
-            acc += ((dt > cut || (dist == 0 && dt == 0)) ? 0.0 : kr[dt]) - ((dO > cut || (dist == 0 && dO == 0)) ? 0.0 : kr[dO]);
-        }
-        tab[i] = acc;
+        const int dt = x - cut - 1 < 0 ? cut + 1 - x : x - cut - 1, dO = x - cut < 0 ? cut - x : x - cut;
+        diff[i] = x >= wn ? 0.0
+                          : ((dt > cut || (dist == 0 && dt == 0)) ? 0.0 : kr[dt]) -
+                                ((dO > cut || (dist == 0 && dO == 0)) ? 0.0 : kr[dO]);
     }
-    // a unit: kEcRails rails of one device
+    __syncthreads();
+    // (a thread per pattern; the bits in increasing order)
+    for (int q = 0; q < (m + 1) * chunks; ++q) {
+        const double *dq = diff + q / chunks * 64 + q % chunks * 8;
+        double acc = 0.0;
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+            if ((threadIdx.x >> b) & 1) acc += dq[b];
+        tab[q * 256 + threadIdx.x] = acc;
+    }
+    // a unit: unit_rails rails of one device
     auto unit = [&](int d, int u) {
         const DevInfo &dv = a.devs[d];
         const int R = dv.rails, L = dv.sites, rw = ec_row_words(dv.pitch), n_nbr = dv.n_nbr;
-        const int r0 = u * kEcRails, nr = min(kEcRails, R - r0);
+        const int r0 = u * unit_rails, nr = min(unit_rails, R - r0);
         __syncthreads();  // the table is written; the previous unit's rows are no longer read
         // rows r0 - m .. r0 + nr + m - 1 (mod R), 16 sites per thread
         const int halves = 2 * rw;
@@ -1001,7 +1012,7 @@ __global__ __launch_bounds__(256) void replay_ec_start(PhiArgs a) {
     // longer than their bonds)
     int64_t next = blockIdx.x, first = 0;
     for (int d0 = 0; d0 < a.n_devices; d0 += 64) {
-        const int mine = d0 + lane < a.n_devices ? (a.devs[d0 + lane].rails + kEcRails - 1) / kEcRails : 0;
+        const int mine = d0 + lane < a.n_devices ? (a.devs[d0 + lane].rails + unit_rails - 1) / unit_rails : 0;
         int64_t end = mine;  // inclusive prefix sum
 #pragma unroll
         for (int off = 1; off < 64; off *= 2) {
@@ -1338,18 +1349,30 @@ hipError_t launch_copy_bytes(const void *src, void *dst, size_t bytes, hipStream
 
 constexpr int kEcGrid = 2048;  // workgroups of the replay's Coulomb-part kernels
 
-hipError_t launch_replay_ec_full(const PhiArgs &a, int max_pitch, bool fp64, hipStream_t st) {
+hipError_t launch_replay_ec_full(const PhiArgs &a, int max_pitch, int64_t rails_total, bool fp64, hipStream_t st) {
     if (a.occ_bits) return hipErrorInvalidValue;  // the start-up reads a byte per site
     const int cut = a.cutoff;
-    if (cut <= kEcBitCut) {
+    // window_dot's kernel has no table to build and a workgroup per 256 bonds, but
+    // each of its workgroups walks the devices before its own: for few devices of
+    // few rails it is the faster one, the more so the larger the table (a replay
+    // of one step, us, it and the other: 1 x 512 x 512, +-1 rail, cutoff 16, 110 and
+    // 117; 1 x 1024 x 512 114 and 116, 1 x 2048 x 512 126 and 120; 4 x 8 x 64 71 and 66;
+    // +-4 rails, cutoff 31: 1 x 64 x 200 87 and 107, 1 x 2048 x 512 291 and 303,
+    // 8 x 64 x 200 105 and 112, 12 x 64 x 200 115 and 112)
+    const bool few = rails_total <= 512 * (a.rail_range + 1) && a.n_devices <= 2 * a.rail_range + 1;
+    if (cut <= kEcBitCut && !few) {
+        // 16 rails to a unit where that fills the grid
+        int unit_rails = rails_total >= (int64_t)kEcGrid * kEcRails ? kEcRails : kEcFewRails;
         const size_t lds = sizeof(double) * (size_t)(a.rail_range + 1) * ec_chunks(cut) * 256 +
-                           sizeof(uint32_t) * (size_t)(kEcRails + 2 * a.rail_range) * ec_row_words(max_pitch);
+                           sizeof(uint32_t) * (size_t)(unit_rails + 2 * a.rail_range) * ec_row_words(max_pitch);
         const void *fn = fp64 ? (const void *)replay_ec_start<double> : (const void *)replay_ec_start<float>;
         const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         PhiArgs args = a;
-        void *kargs[] = {&args};
-        return hipLaunchKernel(fn, dim3(kEcGrid), dim3(256), kargs, lds, st);
+        void *kargs[] = {&args, &unit_rails};
+        // no more workgroups than units: each builds the table
+        const int64_t units = rails_total / unit_rails + a.n_devices;
+        return hipLaunchKernel(fn, dim3((unsigned)std::min<int64_t>(units, kEcGrid)), dim3(256), kargs, lds, st);
     }
     // LDS of the window rows and the difference table (none beyond kEcMaxCut,
     // where every bond is summed from global memory)
