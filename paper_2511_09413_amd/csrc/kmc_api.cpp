@@ -339,6 +339,7 @@ struct kmc_ctx {
     int w_spl = 0;                     // sites per lane of the wave tiling
     size_t w_lds = 0;
     bool w_ok = false;                 // wave tiling fits co-resident on this GPU
+    std::vector<int> w_rails;          // most rails of a tile, per device
     int w_queue = 0;                   // set of queue words of the next launch with a gate
     int32_t gate_us = 100000;          // longest wait at the gate
     std::vector<double> class_weight;  // mean over a device's sites of exp(-beta (class barrier - lowest)); empty: not known
@@ -616,6 +617,8 @@ void make_wtiles(kmc_ctx *c) {
             c->wtiles[i].next -= g.first;
         }
     c->w_ok = true;
+    c->w_rails.assign(c->p.n_devices, 0);
+    for (const PTile &t : c->wtiles) c->w_rails[t.d] = std::max(c->w_rails[t.d], (int)t.nr);
     // Open electrodes: wave tiles where every device's tiles are the same
     // number and fit one workgroup, so that no tile ever waits for another
     // workgroup's and the launch is as independent of what else runs on the
@@ -667,13 +670,11 @@ bool wave64_pays(const kmc_ctx *c, int64_t n_steps) {
     // (windows wider than a wavefront: a survivor at a time; 512 x 3001, cutoff
     // 40, with 2 words: 21 us per step against 19)
     const double limit = (2.0 + (double)c->lay.total_sites / 6e6) * (kernel_diff_width(c->lay.cut) > 0 ? 1.0 : 0.5);
-    std::vector<int> rails(c->p.n_devices, 0);
-    for (const PTile &t : c->wtiles) rails[t.d] = std::max(rails[t.d], t.nr);
     for (int d = 0; d < c->p.n_devices; ++d) {
         const DevInfo &dv = c->devs[d];
         const double field = std::fabs(c->p.field_coupling) * c->vmax[d] / (double)dv.sites;
         const double p = c0 * std::exp(-beta * (dv.ea_min - 0.5 * (field + dv.coul_bound))) * c->class_weight[d];
-        if (!(std::min(p, 1.0) * 0.5 * (double)dv.sites * rails[d] <= limit)) return false;
+        if (!(std::min(p, 1.0) * 0.5 * (double)dv.sites * c->w_rails[d] <= limit)) return false;
     }
     return true;
 }
@@ -925,7 +926,6 @@ kmc_status enqueue_draws(kmc_ctx *c, const HopArgs &h, const Ctl &ctl, int64_t d
     a.nb = L.dense_nb;
     a.rows = c->dr_rows;
     a.pitch = c->devs[0].pitch;
-    a.sites = c->sites[0];
     a.k10 = c->k10;
     a.kfix = c->phifix ? c->at<int64_t>(L.kfix) : nullptr;
     a.k10fix = c->k10fix;

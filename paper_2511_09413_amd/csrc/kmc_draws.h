@@ -52,7 +52,7 @@ struct DrawArgs {
     // dense: the kernel's MFMA fragments for the parity's column blocks
     const void *ktiles;
     int32_t nb, rows;                    // 32-site blocks per rail; survivors per product (32 or 16)
-    int32_t pitch, sites;
+    int32_t pitch;
     float k10;
     // fixed: the potential, in two planes like the state
     const int64_t *phi;

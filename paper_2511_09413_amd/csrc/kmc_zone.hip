@@ -335,7 +335,6 @@ __global__ __launch_bounds__(kZoneBlock) void zone_step(ZoneArgs a) {
 constexpr int kZoneAcc = 8;               // accumulator rows (workgroup index modulo 8: one XCD each)
 constexpr int kZoneAccStride = 72;        // 64-bit words per row (zones, then net)
 constexpr int kZoneRunSteps = 4096;       // steps per launch (the biased sums stay below 2^40)
-constexpr int kZonePairsMixed = 1;        // rail pairs of a wavefront whose work is interleaved
 constexpr int kZoneRunMaxPairs = 16;      // rail pairs per wavefront
 constexpr int64_t kZoneBias = 1 << 20;    // above any workgroup's change in one step
 
@@ -559,7 +558,7 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
     const int mine = (int)(pairs - pair0 < P ? (pairs - pair0 > 0 ? pairs - pair0 : 0) : P);  // pairs of this wavefront
     const int odd_at = (a.rails & 1) ? (int)(pairs - 1 - pair0 < P ? pairs - 1 - pair0 : P) : P;  // the pair without a second rail
     const PhiloxLane lc = philox_lane((uint32_t)l, 2u << 1, a.key0, a.key1);
-    for (int i = tid; i < 2 * kZoneAcc * (kZoneMaxZones + 1); i += blockDim.x) (&s.before[0][0])[i] = 0;  // each its own reader
+    for (int i = tid; i < 2 * kZoneAcc * (kZoneMaxZones + 1); i += blockDim.x) (&s.before[0][0])[i] = 0;  // (the first step's barrier precedes their use)
     for (int k = 0; k < a.n_steps; ++k) {
         const int par = k & 1;
         // opaque: what is derived from these for every pair is not held over the steps
@@ -577,8 +576,8 @@ __global__ __launch_bounds__(1024) void zone_run(ZoneRunArgs a) {
                 net += zone_pair(x0[q], x1[q], z0[q], z1[q], w, has0 & v, has1 & v, wall, last_lane, &s.thr[0][0],
                                  s.dpop[par], zone_at);
             }
-            // no mixing of more pairs: their words would spill
-            if (q % kZonePairsMixed == kZonePairsMixed - 1) __builtin_amdgcn_sched_barrier(0);
+            // no mixing of pairs: their words would spill
+            __builtin_amdgcn_sched_barrier(0);
         }
         if (lane == 0 && net != 0) atomicAdd(&s.dnet[par], net);
         kmc::lds_barrier();
