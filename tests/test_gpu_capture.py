@@ -136,3 +136,47 @@ def test_a_captured_first_run_changes_nothing_until_it_is_replayed(precision, ra
     assert np.array_equal(sim.read_occupancy(), ref.read_occupancy())
     sim.close()
     ref.close()
+
+
+def test_captured_open_electrodes_replay():
+    ph = Physics(precision=FP32, seed=6, ea_ev=0.12)
+    sim, ref = (_sim(ph, [24, 24], [80, 80]) for _ in range(2))
+    start = sim.read_occupancy().copy()
+    for s in (sim, ref):
+        s.set_bias_protocol(*constant(1.0))
+        s.set_electrodes(0.12, 0.08, 0.12, -0.08)
+    graph, net = _capture(sim, 9)
+    expect = _eager(ref, 9)
+    for _ in range(3):
+        _load(sim, start)
+        _replay(sim, graph)
+        assert np.array_equal(net.cpu().numpy(), expect)
+        assert np.array_equal(sim.read_occupancy(), ref.read_occupancy())
+    sim.close()
+    ref.close()
+
+
+@pytest.mark.parametrize("gate", [100000, 0])
+def test_captured_zone_runs_replay(gate):
+    """(constant bias: the table of a loaded state is that of the captured steps)"""
+    import torch
+    from paper_2511_09413_amd import lib
+    from test_gpu_zone import _pair
+    with torch.cuda.stream(torch.cuda.Stream()):
+        sim, p, X = _pair(601, 50, 21, 10, 0.7, 1e-3, seed=11)
+        sim.set_bias_protocol(*constant(2.0))
+    sim.set_gate_limit(gate)
+    start = sim.read_occupancy().copy()
+    import oracle
+    out = oracle.zone_run(p, constant(2.0), X, 0, 25)
+    net = torch.zeros(25, dtype=torch.int32, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=sim.stream):
+        assert lib().kmc_zone_run_steps(sim.ctx, 25, net.data_ptr(), None) == 0
+    for _ in range(3):
+        _load(sim, start)
+        _replay(sim, graph)
+        assert np.array_equal(net.cpu().numpy(), out["net"])
+        assert np.array_equal(sim.read_positions(), X)
+    sim.close()
