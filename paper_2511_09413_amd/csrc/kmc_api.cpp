@@ -659,17 +659,21 @@ bool capturing(const kmc_ctx *c) {
 // launches spread them over the GPU.  Against half-step launches (us per step,
 // 512 x 3001 in binary32 with 0.3, 2 and 6 such words per rail and half-step):
 // 7.2 against 15.0, 17.2 against 17.6, 33 against 29; 2000 x 4096 with 2.8 and
-// 19.5: 22 against 33, 79 against 69 (20 steps).  Where the persistent kernel
-// fits it is the faster one at every barrier tried (64 x 3001: 3.0 against 3.1
-// at 0.3 eV, 9.0 against 17.2 at 0.2); a single step takes 40 us as a call
-// against 36.  Captured calls keep to half-steps: a replay would meet
-// its own publications of the time before.
+// 19.5: 22 against 33, 79 against 69 (20 steps); a single step takes 40 us as a
+// call against 36.  Where the persistent kernel fits, whose workgroups share a
+// tile's words, wave tiles are the faster ones only while such words are rare
+// and the call long enough for their start (us per step in 200-step calls,
+// binary32, 4 to 256 rails: 0.03 words at 2351 sites 2.2 against 2.6, 0.04 at
+// 3001 2.5 against 2.7, 0.06 at 4096 2.9 against 2.8, 0.3 at 3001 6.0 against
+// 4.2; 20-step calls in binary64 at 0.03 to 0.06 words: 1.07 to 0.92 of the
+// persistent kernel's speed).  Captured calls keep to the other forms: a replay
+// would meet its own publications of the time before.
 bool wave64_pays(const kmc_ctx *c, int64_t n_steps) {
-    if (c->p_ok || n_steps < 4 || c->class_weight.empty() || capturing(c)) return false;
+    if (n_steps < (c->p_ok ? 20 : 4) || c->class_weight.empty() || capturing(c)) return false;
     const double beta = 1.0 / c->p.kT_ev, c0 = c->p.nu0_hz * c->p.dt_s;
     // (windows wider than a wavefront: a survivor at a time; 512 x 3001, cutoff
     // 40, with 2 words: 21 us per step against 19)
-    const double limit = (2.0 + (double)c->lay.total_sites / 6e6) * (kernel_diff_width(c->lay.cut) > 0 ? 1.0 : 0.5);
+    const double limit = c->p_ok ? 0.04 : (2.0 + (double)c->lay.total_sites / 6e6) * (kernel_diff_width(c->lay.cut) > 0 ? 1.0 : 0.5);
     for (int d = 0; d < c->p.n_devices; ++d) {
         const DevInfo &dv = c->devs[d];
         const double field = std::fabs(c->p.field_coupling) * c->vmax[d] / (double)dv.sites;
@@ -1472,7 +1476,7 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
         chk(launch_barrier_range(ea_dev, c->fp64, c->at<DevInfo>(lay.devs), D,
                                  c->at<unsigned long long>(lay.scratch), st),
             "barrier range");
-    if (ea_dev && (c->dr_ok || (c->w_ok && c->w_spl == 64 && !c->p_ok))) {
+    if (ea_dev && (c->dr_ok || (c->w_ok && c->w_spl == 64))) {
         // the lowest barriers, for the choice of low-draw half-steps or of wave
         // tiles of 64 sites per lane
         std::vector<DevInfo> back(D);
@@ -1483,7 +1487,7 @@ kmc_status kmc_init_device(const kmc_params *params, int8_t *occ_dev, const void
     chk(launch_import(occ_dev, c->cur, c->at<DevInfo>(lay.devs), D, lay.total_pad, ea_dev, c->fp64, st),
         "import occupancy");
     if (!ea_dev) c->class_weight.assign(D, 1.0);
-    if (ea_dev && c->w_ok && c->w_spl == 64 && !c->p_ok) {
+    if (ea_dev && c->w_ok && c->w_spl == 64) {
         c->class_weight.resize(D);
         chk(launch_class_weights(c->cur, c->at<DevInfo>(lay.devs), D, 1.0 / params->kT_ev, c->at<double>(lay.scratch), st),
             "barrier classes");

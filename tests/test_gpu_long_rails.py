@@ -72,6 +72,32 @@ def test_long_rails(rails, sites, cut, precision, gate):
     ref.close()
 
 
+# lattices that the persistent kernel holds too, which takes the calls of less
+# than 20 steps: words on both sides of the rule's line, per-site barriers and one
+@pytest.mark.parametrize("gate", [100000, 0])
+@pytest.mark.parametrize("rails,sites,cut,precision,words,sigma", [
+    ([26], [2351], 16, FP32, 0.03, 0.0), ([8], [4096], 16, FP64, 0.03, 0.004), ([64], [2049], 40, FP32, 0.02, 0.004),
+    ([40, 30], [3001, 2100], 16, FP64, 0.03, 0.0), ([64], [2500], 16, FP32, 0.3, 0.0)])
+def test_long_rails_that_the_persistent_kernel_holds(rails, sites, cut, precision, words, sigma, gate):
+    from paper_2511_09413_amd import Simulator
+    ph = Physics(precision=precision, seed=5, cutoff_sites=cut)
+    ph = ph.replace(ea_ev=_barrier(ph, max(sites), words))
+    ea = None
+    if sigma:
+        n = sum(r * l for r, l in zip(rails, sites))
+        ea = gaussian_barriers((n,), ph.ea_ev, sigma, seed=3, dtype=np.float32 if precision == FP32 else np.float64)
+    sim, ref = Simulator(ph, rails, sites, ea=ea), Simulator(ph, rails, sites, ea=ea, mode="half_step")
+    sim.set_launch_mode("persistent")
+    sim.set_launch_mode("auto")
+    for s in (sim, ref):
+        s.fill_random([0.35] * len(rails))
+        s.set_protocols([triangle(2.0, 60e-12), constant(-0.8)][:len(rails)])
+    sim.set_gate_limit(gate)
+    assert sum(_same(sim, ref, steps) for steps in (20, 19, 1500, 3, 21)) > 0
+    sim.close()
+    ref.close()
+
+
 def test_which_calls_wait_for_neighbours():
     """With no polls a neighbour wait is declared hung: the calls in wave tiles
     report it, those in half-steps have no such wait."""
