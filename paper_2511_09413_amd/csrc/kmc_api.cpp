@@ -873,8 +873,12 @@ void plan_draws(kmc_ctx *c) {
 //   * fixed: a step saves 3 to 20 us, so a call of one step takes 5 to 15 us more
 //     than in the other form (10^5 sites 41 against 37, 10^7 sites 81 against 66,
 //     3.4e7 sites 125 against 115), one of two is level and one of four gains.  The
-//     copy takes 10 us and 4 per 10^6 sites (3.4e7 sites 134; the first call after a
-//     load 250 us against 116 for one step, 282 against 170 for two).
+//     copy takes 10 us and 4 per 10^6 sites (3.4e7 sites 134), so the first call
+//     after a load is level at about 4 steps and one more per 9 10^6 sites (us, at
+//     0.3 eV: 7 10^5 sites, 4 steps 104 against 102, 5 steps 116 against 122;
+//     3.4e7 sites, 1 step 246 against 113, 6 steps 406 against 377, 8 steps 472
+//     against 482; at 0.2 eV, where a step saves more, 7 10^5 sites, 2 steps 79
+//     against 88).
 //   * dense: a step saves more than that on all but the smallest lattices (8192
 //     sites, one step after a load: 57 us against 53; 10^5 sites 60 against 84).
 // Short calls between others stay with the draws until the copy that they would
@@ -891,7 +895,7 @@ bool draws_pay(kmc_ctx *c, int64_t n_steps) {
         c->dr_short_calls = n_steps < 4 ? c->dr_short_calls + 1 : 0;
         pays = (double)c->dr_short_calls <= 1.0 + sites / 3e6;
     } else {
-        pays = (double)(n_steps + (c->captured ? 0 : c->dr_old_steps)) >= 8.0 + sites / 2e6;
+        pays = (double)(n_steps + (c->captured ? 0 : c->dr_old_steps)) >= 3.4 + sites / 9e6;
     }
     c->dr_old_steps = pays ? 0 : c->dr_old_steps + (n_steps < 4 ? 0 : n_steps);
     return pays;
