@@ -241,7 +241,6 @@ Layout layout_for(const kmc_params *p) {
     L.wtiles = take(sizeof(PTile) * (size_t)rails);  // every wave tile is at least one rail
     L.status = take(sizeof(int32_t) * 4);
     L.ticket = take(sizeof(uint32_t) * kTicketWords);  // wave kernel: tiles that ended the launch
-    L.queue = take(sizeof(QueueWords) * 2);  // used in turn by the launches with a gate
     L.electrodes = take(sizeof(Electrode) * D);       // open-electrode reservoirs per device
     // score replay: its own pair of state planes, a discarded event count, the
     // Coulomb part of every bond's energy change (path precision) and the list
@@ -291,6 +290,9 @@ Layout layout_for(const kmc_params *p) {
         if (dense) L.dr_ktiles = take((size_t)16 * 256 * (m + 1) * (2 * L.dense_nb - 1));
         else L.phifix_b = take(sizeof(int64_t) * (size_t)pad);
     }
+    // (last: the planes before it keep their places; 1 KiB ahead of the fixed
+    // form's planes cost 4 % of a step at 3 x 83 x 401, 12.5 against 12.0 us)
+    L.queue = take(sizeof(QueueWords) * 2);  // used in turn by the launches with a gate
     L.total = off;
     return L;
 }
